@@ -41,7 +41,7 @@ enum {
     ST_FINF = 0,      // ||f||inf
     ST_DIV = 1,       // max |D u_out|
     ST_NONFIN = 2,    // max over outputs of |.| (NaN/Inf show up here)
-    ST_SOLVE0 = 8     // per solve s: [8+4s] ||rhs||, [9+4s] ||e||, [10+4s] ||p||
+    ST_SOLVE0 = 8     // per solve s: [9+4s] ||e||, [10+4s] ||p||
 };
 
 // Division by a runtime constant d < 2^16 for numerators a < 2^16 via a
@@ -78,7 +78,6 @@ struct Dom {
     int tk, ntk;                      // y-pass columns per tile, k tiles
     int zg, zlpw, nzt;                // z lanes per line, lines per WG, z tiles
     MGeo mg[2];                       // marching tiles: [0] RHS and residual, [1] correction
-    int ndiv_tiles;                   // divergence-only tiles (NT cells each)
     int mth, yth, xth;                // threads of the marching, y and x workgroups
     FastDiv dnx, dny, dtj, dtk, dnyc, dM, dH1, dM1, dhy; // dH1: M/2+1, dM1: M+1, dhy: ny/2
     double dx, dy, idx, idy, dt, rho0, irho0, lz, scale;
@@ -99,7 +98,7 @@ struct Dom {
     double *ppart;                    // per x-tile wave dzf-weighted sums of p
     double *pmean;                    // [0]: volume mean of p after the last xinv pass
     double *xpart;                    // per x-tile wave max |update|, max |p| (NULL: atomics)
-    double *spart;                    // per x-tile wave max |f| or |r| of the fused stencil passes
+    double *spart;                    // per x-tile wave max |f| of the fused RHS pass
 };
 
 // Partial-result slots of the x inverse: one per wave of each x tile.  They
@@ -111,6 +110,13 @@ __host__ __device__ inline int xslots(const Dom &d) { return d.ntj * d.nz * (d.x
 // partial-maximum slots of the fused stencil x passes: one per wave, one
 // wave per row of a tile
 __host__ __device__ inline int sslots(const Dom &d) { return d.ntj * d.nz * d.tj; }
+// Workgroups of the divergence-only pass: a wave per row, at most 2048
+// workgroups (8 per CU).
+__host__ __device__ inline int div_wgs(const Dom &d)
+{
+    const int v = (d.ny * d.nz + NT / 64 - 1) / (NT / 64);
+    return v > 2048 ? 2048 : v;
+}
 // workgroups of the reduction of those slots (pass_xmax), at most XMAX_WG
 __host__ __device__ inline int xmax_wgs(const Dom &d)
 {
@@ -464,6 +470,18 @@ __device__ __forceinline__ void staged_copy(int total, Get get, Put put)
 }
 
 // ------------------------------------------------------------- reductions
+// Raises *slot to the non-negative value v (NaN as the quiet pattern: larger
+// than any number).  The slot is read first and the atomic skipped when it
+// could not raise it: atomics on one address run one after another (about
+// 6.5 ns each, all XCDs together), and most workgroups come after the
+// maximum is there.  A value read early is only ever too small (the slots
+// are cleared by an earlier kernel and rise within this one).
+__device__ __forceinline__ void raise_to(unsigned long long *slot, double v)
+{
+    const unsigned long long key = (unsigned long long)__double_as_longlong(v);
+    if (key > __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(slot, key);
+}
+
 // Block-wide max of non-negative values (NaN propagates), then one atomicMax
 // on the uint64 bit pattern (order-preserving for non-negative doubles).
 template <int NTH = NT>
@@ -484,7 +502,7 @@ __device__ __forceinline__ void block_max_to(unsigned long long *slot, double v,
     if (threadIdx.x == 0) {
         double m = red[0];
         for (int i = 1; i < NTH / 64; ++i) m = (red[i] != red[i] || red[i] > m) ? red[i] : m;
-        atomicMax(slot, (unsigned long long)__double_as_longlong(m));
+        raise_to(slot, m);
     }
 }
 
@@ -525,8 +543,12 @@ __device__ __forceinline__ void block_max2_to(unsigned long long *sa, double a, 
 {
     block_max2<NTH>(a, b, red);
     if (threadIdx.x == 0) {
-        if (sa) atomicMax(sa, (unsigned long long)__double_as_longlong(a));
-        if (sb) atomicMax(sb, (unsigned long long)__double_as_longlong(b));
+        // both reads in flight together
+        const unsigned long long ka = (unsigned long long)__double_as_longlong(a), kb = (unsigned long long)__double_as_longlong(b);
+        const unsigned long long ca = sa ? __hip_atomic_load(sa, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : ~0ull;
+        const unsigned long long cb = sb ? __hip_atomic_load(sb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : ~0ull;
+        if (ka > ca) atomicMax(sa, ka);
+        if (kb > cb) atomicMax(sb, kb);
     }
 }
 

@@ -183,6 +183,26 @@ void choose_shapes(const pcx_grid &g, int prec, const TuneParams *tp, Shapes &sh
     sh.batch = batch;
 }
 
+// Planes per chunk of a marching launch of txy tiles per plane that has the
+// device (256 CUs, occ workgroups each) to itself: a workgroup takes about
+// one memory latency per plane and three to start, so the launch takes
+// rounds x (planes + 3).  At 32^3 the correction takes 13 us in 1-plane
+// chunks against 45 in 16-plane ones, at 108 x 162 x 75 33 (8) against 50
+// (16), at 256^3 220 (64) against 238 (16); at 512^3 1.69 ms (128) against
+// 1.86 (16), all in this order.
+static int lone_chunk(int nz, long txy, int occ)
+{
+    int best = nz;
+    long cost = -1;
+    for (int n = 1; n <= nz; ++n) {
+        const int ckc = (nz + n - 1) / n;
+        const long wgs = txy * ((nz + ckc - 1) / ckc), rounds = (wgs + 256L * occ - 1) / (256L * occ);
+        const long c = rounds * (ckc + 3);
+        if (cost < 0 || c < cost) { cost = c; best = ckc; }
+    }
+    return best;
+}
+
 // Domain descriptor and the host image of its device tables (eigenvalues, z
 // coefficients, twiddles); the table pointers of d are bound by bind_tables
 // once the image sits in device memory.
@@ -201,7 +221,6 @@ void make_domain(const pcx_grid &g, int prec, const Shapes &sh, const RadixChoic
     d.zg = sh.zg; d.zlpw = (NT / 64) * (64 / sh.zg);
     long nlines = (long)nl * ny;
     d.nzt = (int)((nlines + d.zlpw - 1) / d.zlpw);
-    d.ndiv_tiles = (int)(((long)nx * ny * nz + NT - 1) / NT);
     // marching stencils: TI x TJ cell tiles over chunks of ckc planes
     d.mth = sh.mth;
     // marching tiles: [0] RHS and residual with sh.mth threads, [1] the
@@ -214,14 +233,9 @@ void make_domain(const pcx_grid &g, int prec, const Shapes &sh, const RadixChoic
         m.ctj = std::max(1, std::min({ny, th / m.cti, 2 * th / 7 - m.cti}));
         m.cnti = (nx + m.cti - 1) / m.cti;
         m.cntj = (ny + m.ctj - 1) / m.ctj;
-        if (sh.batch) {
-            m.ckc = nz; // whole columns: batch items stay large
-        } else {
-            long txy = (long)m.cnti * m.cntj;
-            long target = 2048L * 512 / th;
-            long chunks = std::max(1L, std::min((long)std::max(1, nz / 16), (target + txy - 1) / txy));
-            m.ckc = (int)((nz + chunks - 1) / chunks);
-        }
+        if (sh.batch) m.ckc = nz; // whole columns: batch items stay large
+        else if (sh.ckc[q] > 0) m.ckc = (nz + (nz + sh.ckc[q] - 1) / sh.ckc[q] - 1) / ((nz + sh.ckc[q] - 1) / sh.ckc[q]);
+        else m.ckc = lone_chunk(nz, (long)m.cnti * m.cntj, q == 0 ? 2 : 1);
         m.cnk = (nz + m.ckc - 1) / m.ckc;
         m.ntiles = m.cnti * m.cntj * m.cnk;
         m.dcti = mkdiv(m.cti);
@@ -677,7 +691,7 @@ extern "C" pcx_status pcx_step(pcx_plan P, double dt, double rho0, const double 
     if (P->fuse_rhs) {
         HIPCHK(launch_sx(d, P->prec, SRC_RHS_ST, P->lx, s));
         tmark(P, s, "rhs_fftx");
-        HIPCHK(launch_smax(d, ST_FINF, ST_SOLVE0, s));
+        HIPCHK(launch_smax(d, s));
         tmark(P, s, "f_max");
     } else {
         HIPCHK(launch_rhs(d, s));
@@ -692,10 +706,8 @@ extern "C" pcx_status pcx_step(pcx_plan P, double dt, double rho0, const double 
         if (P->fuse_resid) {
             HIPCHK(launch_sx(d, P->prec, SRC_RESID_ST, P->lx, s));
             tmark(P, s, "resid_fftx");
-            HIPCHK(launch_smax(d, ST_SOLVE0 + 4 * solve, -1, s));
-            tmark(P, s, "r_max");
         } else {
-            HIPCHK(launch_resid(d, solve, s));
+            HIPCHK(launch_resid(d, s));
             tmark(P, s, "resid_stencil");
             HIPCHK(launch_xfwd(d, P->prec, SRC_RESID, P->lx, s));
             tmark(P, s, "x_fft_fwd_resid");

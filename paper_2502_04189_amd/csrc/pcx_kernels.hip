@@ -35,12 +35,12 @@ __global__ __launch_bounds__(MT) void k_rhs(Dom d)
     pass_rhs<MT, TWO>(d, t, (char *)sm);
 }
 
-__global__ __launch_bounds__(MT) void k_resid(Dom d, int solve)
+__global__ __launch_bounds__(MT) void k_resid(Dom d)
 {
-    __shared__ double sm[16 + 2 * MT];
+    __shared__ double sm[2 * MT];
     const int t = xcd_tile(d.mg[0].ntiles);
     if (t >= d.mg[0].ntiles) return;
-    pass_resid<MT>(d, t, (char *)sm, solve);
+    pass_resid<MT>(d, t, (char *)sm);
 }
 
 template <typename T, int SRC, int NTH>
@@ -82,10 +82,10 @@ __global__ __launch_bounds__(NTH) void k_sx(Dom d)
     pass_xfwd<T, SRC, NTH>(d, t, smem);
 }
 
-__global__ __launch_bounds__(NT) void k_smax(Dom d, int sa, int sb)
+__global__ __launch_bounds__(NT) void k_smax(Dom d)
 {
     __shared__ double red[2 * NT / 64];
-    pass_smax(d, sa, sb, blockIdx.x, gridDim.x, (char *)red);
+    pass_smax(d, blockIdx.x, gridDim.x, (char *)red);
 }
 
 template <typename T, bool INV, int NTH>
@@ -123,7 +123,7 @@ __global__ __launch_bounds__(MTC) void k_corr(Dom d, int divcheck)
 __global__ __launch_bounds__(NT) void k_div(Dom d)
 {
     __shared__ double red[NT / 64];
-    pass_div(d, blockIdx.x, (char *)red);
+    pass_div(d, blockIdx.x, gridDim.x, (char *)red);
 }
 
 __global__ __launch_bounds__(NT) void k_xmax(Dom d, int solve)
@@ -198,9 +198,9 @@ hipError_t launch_rhs(const Dom &d, hipStream_t s)
     PCX_LAUNCH_B(k_rhs<false>, xcd_grid(d.mg[0].ntiles), MT, 0, s, d);
 }
 
-hipError_t launch_resid(const Dom &d, int solve, hipStream_t s)
+hipError_t launch_resid(const Dom &d, hipStream_t s)
 {
-    PCX_LAUNCH_B(k_resid, xcd_grid(d.mg[0].ntiles), MT, 0, s, d, solve);
+    PCX_LAUNCH_B(k_resid, xcd_grid(d.mg[0].ntiles), MT, 0, s, d);
 }
 
 template <int NTH> static hipError_t launch_xfwd_t(const Dom &d, int prec, int src, size_t lds, hipStream_t s)
@@ -244,11 +244,11 @@ hipError_t launch_sx(const Dom &d, int prec, int src, size_t lds, hipStream_t s)
     PCX_LAUNCH_B((k_sx<float, SRC_RESID_ST, 1024>), grid, 1024, lds, s, d);
 }
 
-hipError_t launch_smax(const Dom &d, int sa, int sb, hipStream_t s)
+hipError_t launch_smax(const Dom &d, hipStream_t s)
 {
     const int v = (sslots(d) + 4 * NT - 1) / (4 * NT);
     const int nwg = v < 1 ? 1 : (v > XMAX_WG ? XMAX_WG : v);
-    PCX_LAUNCH(k_smax, nwg, 0, s, d, sa, sb);
+    PCX_LAUNCH(k_smax, nwg, 0, s, d);
 }
 
 hipError_t launch_y(const Dom &d, int prec, bool inv, size_t lds, hipStream_t s)
@@ -321,7 +321,7 @@ hipError_t launch_pmean(const Dom &d, hipStream_t s)
 
 hipError_t launch_div(const Dom &d, hipStream_t s)
 {
-    PCX_LAUNCH(k_div, d.ndiv_tiles, 0, s, d);
+    PCX_LAUNCH(k_div, div_wgs(d), 0, s, d);
 }
 
 hipError_t launch_plane_sums(const double *p, int nxy, int nz, double *out, hipStream_t s)
@@ -419,8 +419,8 @@ __global__ __launch_bounds__(MT) void kg_rhs(GArgs a)
 
 __global__ __launch_bounds__(MT) void kg_resid(GArgs a)
 {
-    __shared__ double sm[16 + 2 * MT];
-    gloop(a, [&](const Dom &d, int t) { pass_resid<MT>(d, t, (char *)sm, a.solve); });
+    __shared__ double sm[2 * MT];
+    gloop(a, [&](const Dom &d, int t) { pass_resid<MT>(d, t, (char *)sm); });
 }
 
 template <bool TWO>
@@ -596,7 +596,7 @@ __global__ __launch_bounds__(NT) void k_persist(PersistArgs a)
         for (int tile = tile0; tile < tile0 + count; ++tile) {
             switch (kind) {
             case PK_RHS: pass_rhs(d, tile, smem); break;
-            case PK_RESID: pass_resid(d, tile, smem, sv); break;
+            case PK_RESID: pass_resid(d, tile, smem); break;
             case PK_XFWD_RHS: pass_xfwd<T, SRC_RHS, NT, false>(d, tile, smem); break;
             case PK_XFWD_RESID: pass_xfwd<T, SRC_RESID, NT, false>(d, tile, smem); break;
             case PK_YF: pass_y<T, false, NT, false>(d, tile, smem); break;

@@ -147,6 +147,16 @@ __device__ __forceinline__ Halo rhs_halo(const Dom &d, const MGeo &g, int tile, 
     return H;
 }
 
+// Flux of (1 - rho0/rho) G p* through a z face (lo, hi: the cells below and
+// above), with the fused multiply-adds written out: a chunk of planes
+// evaluates the face below its first plane again, and must round it as the
+// chunk below did, wherever the chunks are cut.
+__device__ __forceinline__ double rhs_zflux(double rr0, double Rlo, double Rhi, double wlo, double whi, double Plo,
+                                            double Phi, double idzc)
+{
+    return fma(-rr0, rcp_nr(fma(Rlo, wlo, Rhi * whi)), 1.0) * (Phi - Plo) * idzc;
+}
+
 // f = (rho0/dt) D u* + D[(1 - rho0/rho_face) G p*], stored in FP64 to d.f.
 // Marching in k; the neighbours in x and y come through LDS (the tile's own
 // plane) or from the halo; the z flux and w* below are carried from the
@@ -186,7 +196,7 @@ __device__ __forceinline__ void pass_rhs(const Dom &d, int tile, char *smem)
     if (!(d.bcz == BC_WALL && k == 0)) {
         const int km = (k == 0) ? nz - 1 : k - 1;
         const double Pm = d.ps[km * sz + col], Rm = d.rho[km * sz + col];
-        Fb = (1.0 - rr0 * rcp_nr(Rm * d.rzlo[km] + Rc * d.rzhi[km])) * (Pc - Pm) * d.idzc[km];
+        Fb = rhs_zflux(rr0, Rm, Rc, d.rzlo[km], d.rzhi[km], Pm, Pc, d.idzc[km]);
         Wb = d.w[km * sz + col];
     }
     double amax = 0.0;
@@ -216,7 +226,7 @@ __device__ __forceinline__ void pass_rhs(const Dom &d, int tile, char *smem)
         const double Fw = n.ww ? 0.0 : (1.0 - tr0 * rcp_nr(Rw + Rc)) * (Pc - Pw);
         const double Fn = n.wn ? 0.0 : (1.0 - tr0 * rcp_nr(Rc + Rn)) * (Pn - Pc);
         const double Fs = n.ws ? 0.0 : (1.0 - tr0 * rcp_nr(Rs + Rc)) * (Pc - Ps);
-        const double Ft = wt ? 0.0 : (1.0 - rr0 * rcp_nr(Rc * ztab(d.rzlo, k) + Rp * ztab(d.rzhi, k))) * (Pp - Pc) * ztab(d.idzc, k);
+        const double Ft = wt ? 0.0 : rhs_zflux(rr0, Rc, Rp, ztab(d.rzlo, k), ztab(d.rzhi, k), Pc, Pp, ztab(d.idzc, k));
         const double ue = n.we ? 0.0 : U, uwf = n.ww ? 0.0 : uw;
         const double vn = n.wn ? 0.0 : V, vsf = n.ws ? 0.0 : vs;
         const double wt_ = wt ? 0.0 : W;
@@ -234,7 +244,7 @@ __device__ __forceinline__ void pass_rhs(const Dom &d, int tile, char *smem)
         U = U1; V = V1; W = W1;
         h0 = g0; h1 = g1;
     }
-    block_max2_to<NTH>(d.stats + ST_FINF, amax, d.stats + ST_SOLVE0, amax, red);
+    block_max_to<NTH>(d.stats + ST_FINF, amax, red);
 }
 
 // r = f - L p (FP64, 7-point operator with variable z spacing) -> d.r.
@@ -242,11 +252,10 @@ __device__ __forceinline__ void pass_rhs(const Dom &d, int tile, char *smem)
 // halo (p on the four sides of the tile, 2 (TI + TJ) items: north row,
 // south row, east column, west column); the z gradient below is carried.
 template <int NTH = NT>
-__device__ __forceinline__ void pass_resid(const Dom &d, int tile, char *smem, int solve)
+__device__ __forceinline__ void pass_resid(const Dom &d, int tile, char *smem)
 {
     constexpr int MG = 0;
-    double *red = (double *)smem;
-    double *sP = red + 16, *hal = sP + NTH;
+    double *sP = (double *)smem, *hal = sP + NTH;
     const MGeo &g = d.mg[MG];
     const MTile t = march_tile(d, g, tile);
     const MNbr n = march_nbr(d, g, t);
@@ -283,7 +292,6 @@ __device__ __forceinline__ void pass_resid(const Dom &d, int tile, char *smem, i
         const int km = (k == 0) ? nz - 1 : k - 1;
         Gb = (Pc - d.po[km * sz + col]) * d.idzc[km];
     }
-    double amax = 0.0;
     for (; k < t.ke; ++k) {
         const int k1 = march_next(k, t);
         const double P2 = d.po[kp(k1) * sz + col], F1 = ld_stream(d.f + k1 * sz + col), hn = d.po[k1 * sz + hoff];
@@ -301,14 +309,10 @@ __device__ __forceinline__ void pass_resid(const Dom &d, int tile, char *smem, i
         const double gn = n.wn ? 0.0 : Pn - Pc, gs = n.ws ? 0.0 : Pc - Ps;
         const double Gt = wt ? 0.0 : (Pp - Pc) * ztab(d.idzc, k);
         const double r = F - ((ge - gw) * idx2 + (gn - gs) * idy2 + (Gt - Gb) * ztab(d.idzf, k));
-        if (t.act) {
-            st_stream(d.r + c, r);
-            amax = amax_nan(amax, r);
-        }
+        if (t.act) st_stream(d.r + c, r);
         Gb = Gt;
         Pc = Pp; Pp = P2; F = F1; hc = hn;
     }
-    block_max_to<NTH>(d.stats + ST_SOLVE0 + 4 * solve, amax, red);
 }
 
 // Halo of a marching tile: the cells just outside its TI x TJ extent that
@@ -461,25 +465,32 @@ __device__ __forceinline__ void pass_corr(const Dom &d, int tile, char *smem, bo
     block_max2_to<NTH>(divcheck ? d.stats + ST_DIV : nullptr, dmax, d.stats + ST_NONFIN, omax, red);
 }
 
-// Divergence of the stored output velocity (used when outputs alias inputs);
-// tiles of NT consecutive cells (d.ndiv_tiles of them).
-__device__ __forceinline__ void pass_div(const Dom &d, int tile, char *smem)
+// Divergence of the stored output velocity (used when outputs alias inputs).
+// Each wave takes rows (j, k) of the grid, wg * (NT / 64) + wave first and
+// then every nwg * (NT / 64)-th, its lanes along x; the workgroups are few
+// (div_wgs), since each ends with one atomic on the same address.
+__device__ __forceinline__ void pass_div(const Dom &d, int wg, int nwg, char *smem)
 {
     double *red = (double *)smem;
-    const size_t ncell = (size_t)d.nx * d.ny * d.nz;
-    const size_t c = (size_t)tile * NT + threadIdx.x;
+    const int nx = d.nx, ny = d.ny, nz = d.nz, lane = threadIdx.x & 63;
+    const size_t plane = (size_t)nx * ny;
+    const int nrows = ny * nz;
     double dmax = 0.0;
-    if (c < ncell) {
-        size_t plane = (size_t)d.nx * d.ny;
-        int k = (int)(c / plane);
-        size_t rem = c - (size_t)k * plane;
-        int j = (int)(rem / d.nx);
-        int i = (int)(rem - (size_t)j * d.nx);
-        double fw = (i > 0) ? d.uo[c - 1] : (d.bcx == BC_WALL ? 0.0 : d.uo[c + d.nx - 1]);
-        double fs = (j > 0) ? d.vo[c - d.nx] : (d.bcy == BC_WALL ? 0.0 : d.vo[c + (size_t)(d.ny - 1) * d.nx]);
-        double fb = (k > 0) ? d.wo[c - plane] : (d.bcz == BC_WALL ? 0.0 : d.wo[c + (size_t)(d.nz - 1) * plane]);
-        double dv = (d.uo[c] - fw) * d.idx + (d.vo[c] - fs) * d.idy + (d.wo[c] - fb) * d.idzf[k];
-        dmax = fabs(dv);
+    for (int r = __builtin_amdgcn_readfirstlane(wg * (NT / 64) + (int)(threadIdx.x >> 6)); r < nrows; r += nwg * (NT / 64)) {
+        const int k = r / ny, j = r - k * ny;
+        const size_t c0 = (size_t)r * nx;
+        // rows below in y and z; across a wall the face is 0 (any valid row)
+        const bool ws = j == 0 && d.bcy == BC_WALL, wb = k == 0 && d.bcz == BC_WALL;
+        const double *vs = d.vo + (j > 0 ? c0 - nx : (ws ? c0 : c0 + (size_t)(ny - 1) * nx));
+        const double *wl = d.wo + (k > 0 ? c0 - plane : (wb ? c0 : c0 + (size_t)(nz - 1) * plane));
+        const double idzf = ztab(d.idzf, k);
+        for (int i = lane; i < nx; i += 64) {
+            const bool ww = i == 0 && d.bcx == BC_WALL;
+            const double u = d.uo[c0 + i], um = d.uo[c0 + (i > 0 ? i - 1 : nx - 1)];
+            const double v = d.vo[c0 + i], vm = vs[i], w = d.wo[c0 + i], wm = wl[i];
+            const double dv = (u - (ww ? 0.0 : um)) * d.idx + (v - (ws ? 0.0 : vm)) * d.idy + (w - (wb ? 0.0 : wm)) * idzf;
+            dmax = amax_nan(dmax, dv);
+        }
     }
     block_max_to(d.stats + ST_DIV, dmax, red);
 }
@@ -492,7 +503,7 @@ __device__ __forceinline__ void pass_div(const Dom &d, int tile, char *smem)
 // pass_resid; the neighbours in y and z are read from memory (the tiles of
 // the neighbouring rows and planes run at the same time, so these reads are
 // mostly cache hits), the x neighbours of a pair are its two outer cells.
-// Returns the lane's max |value|.
+// Returns the lane's max |f| (RHS only).
 struct SxRow {
     int c, cn, cs, cu, cd;       // offsets of row j / j+1 / j-1 of plane k, row j of planes k+1 / k-1
     bool wn, ws, wt, wb;         // wall faces north, south, top, bottom
@@ -600,15 +611,14 @@ __device__ __forceinline__ double stencil_row(const Dom &d, int j, int k, int la
                 r[q] = (q ? F.y : F.x) - ((gee - gww) * idx2 + (gn - gs) * idy2 + (Gt - Gb) * idzf);
             }
             put(h, double2{r[0], r[1]});
-            amax = amax_nan(amax_nan(amax, r[0]), r[1]);
         }
     }
     return amax;
 }
 
-// Maximum of the fused stencil passes' per-wave partials into stats slot
-// sa (and sb when >= 0): workgroup wg of nwg takes every nwg-th block.
-__device__ __forceinline__ void pass_smax(const Dom &d, int sa, int sb, int wg, int nwg, char *smem)
+// Maximum of the fused RHS pass's per-wave partials into ST_FINF: workgroup
+// wg of nwg takes every nwg-th block.
+__device__ __forceinline__ void pass_smax(const Dom &d, int wg, int nwg, char *smem)
 {
     double *red = (double *)smem;
     const int nt = sslots(d);
@@ -621,7 +631,7 @@ __device__ __forceinline__ void pass_smax(const Dom &d, int sa, int sb, int wg, 
         for (int u = 0; u < 8; ++u)
             if (q0 + u * nwg * NT + (int)threadIdx.x < nt) a = (v[u] != v[u] || v[u] > a) ? v[u] : a;
     }
-    block_max2_to<NT>(d.stats + sa, a, sb >= 0 ? d.stats + sb : nullptr, a, red);
+    block_max_to<NT>(d.stats + ST_FINF, a, red);
 }
 
 // ------------------------------------------------------------------ xfwd
@@ -702,14 +712,16 @@ __device__ __forceinline__ void pass_xfwd(const Dom &d, int tile, char *smem)
             C *row = buf + wid * ldr;
             if constexpr (ST) {
                 const double m = stencil_row<SRC>(d, j0 + wid, k, lane, [&](int h, double2 s) { put_pair(row, h, s); });
-                const double wm = wave_max1(m);
-                if (lane == 0) d.spart[tile * NW + wid] = wm;
+                if constexpr (SRC == SRC_RHS_ST) {
+                    const double wm = wave_max1(m);
+                    if (lane == 0) d.spart[tile * NW + wid] = wm;
+                }
             } else {
                 const double2 *sr = src2 + (size_t)wid * hx;
                 staged_copy_t<64, 8, double2>(
                     lane, hx, [&](int h) { return sr[h]; }, [&](int h, double2 s) { put_pair(row, h, s); });
             }
-        } else if (ST && lane == 0 && wid < NW) {
+        } else if (SRC == SRC_RHS_ST && lane == 0 && wid < NW) {
             d.spart[tile * NW + wid] = 0.0;
         }
         tws.put(ltw, d.fx);
