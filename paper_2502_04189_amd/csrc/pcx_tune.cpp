@@ -98,6 +98,9 @@ static std::vector<std::vector<int>> radix_variants(int n)
 }
 
 namespace {
+// items of a timed grouped launch, at least (see prep_group)
+constexpr long GFILL = 1024;
+
 struct Scratch {
     std::vector<void *> ptrs;
     ~Scratch()
@@ -137,14 +140,17 @@ pcx_status autotune_class(const pcx_grid &g, int prec, hipStream_t s, TuneParams
     // partial sums of the x inverse: at most one per wave of a 1024-thread
     // workgroup per row, plus the mean
     double *ppart = (double *)sc.alloc(((size_t)g.ny * g.nz * 16 + PMEAN_LEN) * 8);
-    if (!s1 || !s2 || !f || !rr || !stats || !ppart) return fail(PCX_ERR_NOMEM, "autotune scratch allocation failed");
+    // and its partial maxima, as a plan or batch has them (without them the
+    // tiles' atomics on one address would be timed instead of the transforms)
+    double *xpart = (double *)sc.alloc((size_t)g.ny * g.nz * 16 * 2 * 8);
+    if (!s1 || !s2 || !f || !rr || !stats || !ppart || !xpart) return fail(PCX_ERR_NOMEM, "autotune scratch allocation failed");
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) return fail(PCX_ERR_HIP, "hipEventCreate");
     // grouped launches (the batch's kernels): a one-entry domain table and an
     // item list of every tile of the pass, as the batch builds them
     Dom *ddom = (Dom *)sc.alloc(sizeof(Dom));
     const size_t max_items = (size_t)std::max<long>({(long)g.ny * g.nz, (long)nlx * g.nz, (long)nlx * g.ny,
-                                                     (long)(ncell / 64 + 64)}) + 64;
+                                                     (long)(ncell / 64 + 64), GFILL}) + 64;
     GItem *ditems = (GItem *)sc.alloc(max_items * sizeof(GItem));
     if (!ddom || !ditems) return fail(PCX_ERR_NOMEM, "autotune scratch allocation failed");
     std::vector<GItem> hitems;
@@ -152,14 +158,25 @@ pcx_status autotune_class(const pcx_grid &g, int prec, hipStream_t s, TuneParams
     auto prep_group = [&](const Dom &d, int kind, int smax, GVariant &v, GArgs &a, size_t &lds) {
         const long t = group_tiles(d, kind);
         if (t <= 0 || (size_t)t > max_items) return false;
-        hitems.resize(t);
-        for (long q = 0; q < t; ++q) hitems[q] = GItem{0u, (uint32_t)(kind == PK_Z ? t - 1 - q : q)};
+        // A small domain's tiles leave most of the device idle, and the shape
+        // that spreads them best is not the one that does the least work per
+        // cell, which is what counts when a batch fills the device: the list
+        // is repeated up to GFILL items (equal values written twice at the
+        // same place; the z solve's scratch lines are solved again).
+        const long reps = std::max(1L, GFILL / t);
+        hitems.resize(t * reps);
+        for (long q = 0; q < t * reps; ++q) hitems[q] = GItem{0u, (uint32_t)(kind == PK_Z ? t - 1 - q % t : q % t)};
         if (hipMemcpy(ddom, &d, sizeof(Dom), hipMemcpyHostToDevice) != hipSuccess) return false;
-        if (hipMemcpy(ditems, hitems.data(), t * sizeof(GItem), hipMemcpyHostToDevice) != hipSuccess) return false;
+        if (hipMemcpy(ditems, hitems.data(), t * reps * sizeof(GItem), hipMemcpyHostToDevice) != hipSuccess) return false;
         v = variant_of(d, kind, smax);
-        a = GArgs{ddom, ditems, (int)t, 0};
+        a = GArgs{ddom, ditems, (int)(t * reps), 0};
         lds = group_lds(d, kind, prec);
         return true;
+    };
+    // times of a candidate are per item, times the items of one pass
+    auto per_pass = [&](const Dom &d, int kind, float t) {
+        const long n = group_tiles(d, kind);
+        return grouped ? t / (float)std::max(1L, GFILL / n) : t;
     };
     // launches of pass kinds k1 (and k2) of d, grouped or single-domain
     auto passes = [&](const Dom &d, int smax, size_t lx, size_t ly, size_t lz, int k1, int k2) {
@@ -177,7 +194,7 @@ pcx_status autotune_class(const pcx_grid &g, int prec, hipStream_t s, TuneParams
             hipError_t e = hipSuccess;
             if (grouped) {
                 for (auto &x : gl)
-                    if (e == hipSuccess) e = launch_group(x.first, prec, x.second.first, group_tiles(d, x.first.kind),
+                    if (e == hipSuccess) e = launch_group(x.first, prec, x.second.first, x.second.first.nitems,
                                                           x.second.second, s);
                 return e;
             }
@@ -205,6 +222,7 @@ pcx_status autotune_class(const pcx_grid &g, int prec, hipStream_t s, TuneParams
         d.rho = fld[0]; d.ps = fld[1]; d.u = fld[2]; d.v = fld[3]; d.w = fld[4];
         d.uo = fld[5]; d.vo = fld[6]; d.wo = fld[7]; d.po = fld[8];
         d.f = f; d.r = rr; d.s1 = s1; d.s2 = s2; d.stats = stats;
+        d.xpart = xpart;
         d.ppart = prec == PREC_F32 ? ppart : nullptr;
         d.pmean = prec == PREC_F32 ? ppart + (size_t)xslots(d) : nullptr;
         lx = lds_x(d, prec); ly = lds_y(d, prec); lz = lds_z(d, prec); smax = sh.smax;
@@ -246,7 +264,7 @@ pcx_status autotune_class(const pcx_grid &g, int prec, hipStream_t s, TuneParams
                 if (make(tp, rc, d, tb, lx, ly, lz, smax) != PCX_OK) { if (tb.dev) (void)hipFree(tb.dev); continue; }
                 // x forward and inverse have the same tiles, so the item list is shared
                 auto fn = passes(d, smax, lx, ly, lz, PK_XFWD_RHS, PK_XINV_STORE);
-                float t = fn ? timeit(fn) : 1e30f;
+                float t = fn ? per_pass(d, PK_XFWD_RHS, timeit(fn)) : 1e30f;
                 (void)hipFree(tb.dev);
                 if (t < bt) { bt = t; best.tj = tj; brc.x = rx; }
             }
@@ -266,7 +284,7 @@ pcx_status autotune_class(const pcx_grid &g, int prec, hipStream_t s, TuneParams
                 Dom d; DomTables tb; size_t lx, ly, lz; int smax;
                 if (make(tp, rc, d, tb, lx, ly, lz, smax) != PCX_OK) { if (tb.dev) (void)hipFree(tb.dev); continue; }
                 auto fn = passes(d, smax, lx, ly, lz, PK_YF, PK_YI);
-                float t = fn ? timeit(fn) : 1e30f;
+                float t = fn ? per_pass(d, PK_YF, timeit(fn)) : 1e30f;
                 (void)hipFree(tb.dev);
                 if (t < bt) { bt = t; best.tk = tk; brc.y = ry; }
             }
@@ -282,7 +300,7 @@ pcx_status autotune_class(const pcx_grid &g, int prec, hipStream_t s, TuneParams
             Dom d; DomTables tb; size_t lx, ly, lz; int smax;
             if (make(tp, brc, d, tb, lx, ly, lz, smax) != PCX_OK) { if (tb.dev) (void)hipFree(tb.dev); continue; }
             auto fn = passes(d, smax, lx, ly, lz, PK_Z, -1);
-            float t = fn ? timeit(fn) : 1e30f;
+            float t = fn ? per_pass(d, PK_Z, timeit(fn)) : 1e30f;
             (void)hipFree(tb.dev);
             if (t < bt) { bt = t; best.zg = G; }
         }
