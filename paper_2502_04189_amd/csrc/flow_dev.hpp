@@ -65,20 +65,19 @@ __device__ __forceinline__ bool wallf(const FGrid &G, int d, int s) { return !G.
 template <int C>
 __device__ __forceinline__ double fv(const FGrid &G, const double *q, int i, int j, int k)
 {
-    int ix[3] = {i, j, k};
+    // the load is at a valid cell and under no branch, so that a thread's
+    // loads do not wait for one another; the rules then select
+    const int ix[3] = {i, j, k};
     double sg = 1.0;
+    bool zero = false;
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-        const int n = G.n[d];
-        if (d == C) {
-            if (G.per[d]) ix[d] = ix[d] < 0 ? ix[d] + n : (ix[d] >= n ? ix[d] - n : ix[d]);
-            else if (ix[d] < 0 || ix[d] >= n - 1) return 0.0;
-        } else if (ix[d] < 0 || ix[d] >= n) {
-            if (G.per[d]) ix[d] = ix[d] < 0 ? ix[d] + n : ix[d] - n;
-            else { ix[d] = ix[d] < 0 ? 0 : n - 1; sg = -sg; }
-        }
+        const int n = G.n[d], s = ix[d];
+        if (d == C) zero = zero || (!G.per[d] && (s < 0 || s >= n - 1));
+        else if (!G.per[d] && (s < 0 || s >= n)) sg = -sg;
     }
-    return sg * q[at(G, ix[0], ix[1], ix[2])];
+    const double v = q[at(G, cwrap(G, 0, i), cwrap(G, 1, j), cwrap(G, 2, k))];
+    return zero ? 0.0 : sg * v;
 }
 
 __device__ __forceinline__ double dzf_at(const FGrid &G, int k)
@@ -125,12 +124,13 @@ struct Gen {
     __device__ __forceinline__ double dzf(int s) const { return dzf_at(G, k + s); }
     __device__ __forceinline__ double dzc(int s) const { return dzc_at(G, k + s); }
     __device__ __forceinline__ double h(int d) const { return G.h[d]; }
-    // reciprocals: 1/h, 1/dzf(s), 1/dzc(s), 1/(dzc(0) + dzc(-1)), 1/(dzf(0) + dzf(1))
-    __device__ __forceinline__ double ih(int d) const { return 1.0 / G.h[d]; }
-    __device__ __forceinline__ double izf(int s) const { return 1.0 / dzf(s); }
-    __device__ __forceinline__ double izc(int s) const { return 1.0 / dzc(s); }
-    __device__ __forceinline__ double izc2() const { return 1.0 / (dzc(0) + dzc(-1)); }
-    __device__ __forceinline__ double izf2() const { return 1.0 / (dzf(0) + dzf(1)); }
+    // reciprocals from the host tables (as Fast): 1/h, 1/dzf(s) for s in
+    // {0, 1}, 1/dzc(s) for s in {-1, 0}, 1/(dzc(0) + dzc(-1)), 1/(dzf(0) + dzf(1))
+    __device__ __forceinline__ double ih(int d) const { return G.ih[d]; }
+    __device__ __forceinline__ double izf(int s) const { return G.rz[6 * (size_t)k + s]; }
+    __device__ __forceinline__ double izc(int s) const { return G.rz[6 * (size_t)k + 3 + s]; }
+    __device__ __forceinline__ double izc2() const { return G.rz[6 * (size_t)k + 4]; }
+    __device__ __forceinline__ double izf2() const { return G.rz[6 * (size_t)k + 5]; }
     __device__ __forceinline__ size_t idx(int a, int b, int c) const
     {
         return at(G, cwrap(G, 0, i + a), cwrap(G, 1, j + b), cwrap(G, 2, k + c));
@@ -308,19 +308,20 @@ __device__ __forceinline__ void normal_cell(const X &x, PS psi, double &nx, doub
 template <int D, class X, class PH, class PS, class ND>
 __device__ __forceinline__ double flux_face(const X &x, const FParams &P, PH phi, PS psi, ND nd)
 {
-    if (x.template wall<D>(0)) return 0.0;
     // (1 - tanh^2 z) / 4 = y / (1 + y)^2 with y = exp(-2 |z|): one
     // exponential instead of a hyperbolic tangent, and no cancellation
     // where tanh z is near +-1
     const double y = exp(-2.0 * fabs(cface<D>(x, psi, 0) * P.ihe));
     const double w = y / ((1.0 + y) * (1.0 + y));
-    return P.gamma * (P.eps * cgrad<D>(x, phi, 0) - w * cface<D>(x, nd, 0));
+    const double f = P.gamma * (P.eps * cgrad<D>(x, phi, 0) - w * cface<D>(x, nd, 0));
+    return x.template wall<D>(0) ? 0.0 : f;
 }
 
 // normal component D on the +D face of the cell s steps along D (0 on walls)
 template <int D, class X, class ND> __device__ __forceinline__ double nface(const X &x, ND nd, int s)
 {
-    return x.template wall<D>(s) ? 0.0 : cface<D>(x, nd, s);
+    const double f = cface<D>(x, nd, s);
+    return x.template wall<D>(s) ? 0.0 : f;
 }
 
 // curvature -div n_f at the cell
@@ -339,8 +340,8 @@ template <class X, class NV> __device__ __forceinline__ double curvature_cell(co
 template <int D, class X, class PH, class VD, class AD>
 __device__ __forceinline__ double jface(const X &x, PH phi, VD vel, AD ad, int s)
 {
-    if (x.template wall<D>(s)) return 0.0;
-    return x.template fv<D>(vel, DOFF(D, s)) * cface<D>(x, phi, s) - x.cv(ad, DOFF(D, s));
+    const double f = x.template fv<D>(vel, DOFF(D, s)) * cface<D>(x, phi, s) - x.cv(ad, DOFF(D, s));
+    return x.template wall<D>(s) ? 0.0 : f;
 }
 
 // -div(u phi_f - a) at the cell
@@ -379,10 +380,9 @@ template <int C, int D, class X, class Q> __device__ __forceinline__ double a_at
         return x.cv(ad, 0, 0, 0);
     } else {
         constexpr int ci = C == 0, cj = C == 1, ck = C == 2, di = D == 0, dj = D == 1, dk = D == 2;
-        double s = 0.0;
-        if (!x.template wall<D>(0)) s += x.cv(ad, 0, 0, 0) + x.cv(ad, ci, cj, ck);
-        if (!x.template wall<D>(-1)) s += x.cv(ad, -di, -dj, -dk) + x.cv(ad, ci - di, cj - dj, ck - dk);
-        return 0.25 * s;
+        const double up = x.cv(ad, 0, 0, 0) + x.cv(ad, ci, cj, ck);
+        const double dn = x.cv(ad, -di, -dj, -dk) + x.cv(ad, ci - di, cj - dj, ck - dk);
+        return 0.25 * ((x.template wall<D>(0) ? 0.0 : up) + (x.template wall<D>(-1) ? 0.0 : dn));
     }
 }
 

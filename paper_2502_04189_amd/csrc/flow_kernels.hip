@@ -27,9 +27,10 @@ __global__ __launch_bounds__(FT) void k_flow_psi(FArgs A)
 
 // the normals on the tiles along the walls (the interior tiles' flux kernel
 // evaluates its own)
-__global__ __launch_bounds__(FT) void k_flow_normals(TileBox b, int, FArgs A)
+__global__ __launch_bounds__(FT) void k_flow_normals(BoxList L, FArgs A)
 {
-    const FTile t = btile(A.G, b);
+    const BoxPick p = box_pick<false>(L);
+    const FTile t = btile(A.G, p.b, p.w);
     if (!t.act) return;
     double nx, ny, nz;
     with_acc<false>(A.G, t, [&](const auto &x) { normal_cell(x, A.psi, nx, ny, nz); });
@@ -45,9 +46,11 @@ __global__ __launch_bounds__(FT) void k_flow_normals(TileBox b, int, FArgs A)
 // step along two) instead of being stored by a normals pass and read back:
 // 6 GiB less HBM traffic per substep at 512^3.  The box's cells next to a
 // wall box store their own normal, which the wall tiles read.
-template <bool FAST> __global__ __launch_bounds__(FT) void k_flow_flux(TileBox b, int, FArgs A)
+template <bool FAST> __global__ __launch_bounds__(FT) void k_flow_flux(BoxList L, FArgs A)
 {
-    const FTile t = btile(A.G, b);
+    const BoxPick p = box_pick<FAST>(L);
+    const TileBox &b = p.b;
+    const FTile t = btile(A.G, b, p.w);
     if (!t.act) return;
     const size_t c = at(A.G, t.i, t.j, t.k);
     if constexpr (FAST) {
@@ -171,9 +174,10 @@ __device__ __forceinline__ void key_to_slot(unsigned long long key, unsigned lon
 
 // Phase-field right-hand side only (the phase right-hand side entry point;
 // the substep's update runs in the momentum pass)
-template <bool FAST> __global__ __launch_bounds__(FT) void k_flow_phase(TileBox b, int, FArgs A)
+template <bool FAST> __global__ __launch_bounds__(FT) void k_flow_phase(BoxList L, FArgs A)
 {
-    const FTile t = btile(A.G, b);
+    const BoxPick p = box_pick<FAST>(L);
+    const FTile t = btile(A.G, p.b, p.w);
     if (!t.act) return;
     double r = 0.0;
     if constexpr (FAST) {
@@ -216,6 +220,8 @@ __device__ __forceinline__ double mom_rhs(const FArgs &A, const X &x, const FTil
                                           const AV &a)
 {
     const int s = C == 0 ? t.i : (C == 1 ? t.j : t.k);
+    // a branch, not a select: it keeps the three components apart (merged,
+    // the interior kernel takes 160 VGPRs, 3 waves per SIMD instead of 4)
     return wallf(A.G, C, s) ? 0.0 : mom_face<C>(x, A.P, phi, kap, vel, a);
 }
 
@@ -287,9 +293,10 @@ __device__ __forceinline__ void stage_fields(const FArgs &A, int i0, int j0, int
 // the kernel also takes the phase field's right-hand side and update (the
 // substep), whose stencil reads only values the momentum stages already
 // hold: a separate phase pass read phi, u, v, w and a again.
-template <bool FAST, bool PH> __device__ __forceinline__ void momentum_body(const TileBox &b, int slot0, const FArgs &A)
+template <bool FAST, bool PH> __device__ __forceinline__ void momentum_body(const BoxList &L, const FArgs &A)
 {
-    const FTile t = btile(A.G, b);
+    const BoxPick p = box_pick<FAST>(L);
+    const FTile t = btile(A.G, p.b, p.w);
     double m0 = 0.0, m1 = 0.0, m2 = 0.0;
     unsigned long long key = ~0ull;
     if constexpr (FAST) {
@@ -351,17 +358,17 @@ template <bool FAST, bool PH> __device__ __forceinline__ void momentum_body(cons
         if (A.pstar) put(A.pstar + c, (1.0 + A.r) * A.p1[c] - A.r * A.p2[c]);
         if constexpr (PH) phase_put(A, c, r, A.phi[c], A.first ? 0.0 : own(A.hphi + c), key);
     }
-    if constexpr (PH) key_to_slot(key, A.rho_part + slot0 + blockIdx.x);
+    if constexpr (PH) key_to_slot(key, A.rho_part + p.slot);
 }
 
-template <bool FAST> __global__ __launch_bounds__(FT) void k_flow_momentum(TileBox b, int slot0, FArgs A)
+template <bool FAST> __global__ __launch_bounds__(FT) void k_flow_momentum(BoxList L, FArgs A)
 {
-    momentum_body<FAST, false>(b, slot0, A);
+    momentum_body<FAST, false>(L, A);
 }
 // the substep's momentum predictor with the phase update
-template <bool FAST> __global__ __launch_bounds__(FT) void k_flow_mom_phase(TileBox b, int slot0, FArgs A)
+template <bool FAST> __global__ __launch_bounds__(FT) void k_flow_mom_phase(BoxList L, FArgs A)
 {
-    momentum_body<FAST, true>(b, slot0, A);
+    momentum_body<FAST, true>(L, A);
 }
 
 __global__ void k_flow_key_reset(unsigned long long *k) { *k = ~0ull; }
@@ -377,13 +384,9 @@ hipError_t launch_normals(const FArgs &A, const TilePlan &tp, hipStream_t s)
     if (e != hipSuccess) return e;
     // the tiles along the walls only: the interior box's flux kernel
     // evaluates its normals itself
-    for (int b = 0; b < tp.n; ++b) {
-        if (tp.fast[b]) continue;
-        hipLaunchKernelGGL(k_flow_normals, dim3(box_grid(tp.box[b])), dim3(FT), 0, s, tp.box[b], tp.slot0[b], A);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    const BoxList out = box_list(tp, false);
+    if (out.n) hipLaunchKernelGGL(k_flow_normals, dim3(out.grid), dim3(FT), 0, s, out, A);
+    return hipGetLastError();
 }
 hipError_t launch_flux(const FArgs &A, const TilePlan &tp, hipStream_t s)
 {

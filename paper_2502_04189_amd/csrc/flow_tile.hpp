@@ -145,12 +145,58 @@ __host__ __device__ inline void box_tile(const TileBox &b, long t, int &it, int 
     k = b.k0 + kb + q % nkc;
 }
 
-// the thread's cell in the launch over box b (act false past the box or the grid)
-__device__ __forceinline__ FTile btile(const FGrid &G, const TileBox &b)
+// The boxes of one launch: workgroup first[q] + w is workgroup w of box q
+// and owns partial-result slot slot0[q] + w (every box's workgroups are a
+// multiple of 8, so w & 7 is the workgroup's XCD as well).
+constexpr int MAXBOX = 6;
+struct BoxList {
+    int n, grid;
+    TileBox box[MAXBOX];
+    int slot0[MAXBOX], first[MAXBOX];
+};
+
+// The interior box (fast) or the boxes along the walls of a plan, as one
+// launch: run one after another, the wall boxes of a small grid each took
+// the time of one workgroup (45-60 us for the momentum at 144 x 54 x 50) and
+// left the device idle.
+inline BoxList box_list(const TilePlan &p, bool fast)
+{
+    BoxList L{};
+    for (int b = 0; b < p.n; ++b) {
+        if (p.fast[b] != fast) continue;
+        L.box[L.n] = p.box[b];
+        L.slot0[L.n] = p.slot0[b];
+        L.first[L.n] = L.grid;
+        L.grid += box_grid(p.box[b]);
+        ++L.n;
+    }
+    return L;
+}
+
+// the box of this workgroup, its number in the box and its slot
+struct BoxPick {
+    TileBox b;
+    unsigned w;
+    int slot;
+};
+template <bool FAST> __device__ __forceinline__ BoxPick box_pick(const BoxList &L)
+{
+    BoxPick p{L.box[0], blockIdx.x, L.slot0[0] + (int)blockIdx.x};
+    if constexpr (!FAST) { // the interior is one box
+#pragma unroll
+        for (int q = 1; q < MAXBOX; ++q)
+            if (q < L.n && (int)blockIdx.x >= L.first[q])
+                p = BoxPick{L.box[q], blockIdx.x - L.first[q], L.slot0[q] + (int)blockIdx.x - L.first[q]};
+    }
+    return p;
+}
+
+// the thread's cell in workgroup w of box b (act false past the box or the grid)
+__device__ __forceinline__ FTile btile(const FGrid &G, const TileBox &b, unsigned w)
 {
     const long n = box_tiles(b);
     const long per = (n + 7) >> 3;
-    const long t = (long)(blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    const long t = (long)(w & 7) * per + (w >> 3);
     FTile c;
     c.act = false;
     c.valid = t < n;
@@ -186,21 +232,16 @@ __device__ __forceinline__ void stage_regs(const FGrid &G, const FTile &t, const
         for (int n = 0; n < 27; ++n) rg[q][n] = src[q][f.idx(n % 3 - 1, (n / 3) % 3 - 1, n / 9 - 1)];
 }
 
-// Launches kernel<true> on the interior box and kernel<false> on the others;
-// every kernel takes (box, first slot, args...).
+// Launches kernel<true> on the interior box and kernel<false> on the others
+// together; every kernel takes (box list, args...).
 #define FLOW_LAUNCH_PLAN(TP, KERNEL, STREAM, ...)                                                          \
     ([&]() -> hipError_t {                                                                                \
-        for (int b_ = 0; b_ < (TP).n; ++b_) {                                                             \
-            if ((TP).fast[b_])                                                                            \
-                hipLaunchKernelGGL(KERNEL<true>, dim3(box_grid((TP).box[b_])), dim3(FT), 0, (STREAM),     \
-                                   (TP).box[b_], (TP).slot0[b_], __VA_ARGS__);                            \
-            else                                                                                          \
-                hipLaunchKernelGGL(KERNEL<false>, dim3(box_grid((TP).box[b_])), dim3(FT), 0, (STREAM),    \
-                                   (TP).box[b_], (TP).slot0[b_], __VA_ARGS__);                            \
-            const hipError_t e_ = hipGetLastError();                                                      \
-            if (e_ != hipSuccess) return e_;                                                              \
-        }                                                                                                 \
-        return hipSuccess;                                                                                \
+        const BoxList in_ = box_list((TP), true), out_ = box_list((TP), false);                           \
+        if (in_.n) hipLaunchKernelGGL(KERNEL<true>, dim3(in_.grid), dim3(FT), 0, (STREAM), in_, __VA_ARGS__); \
+        hipError_t e_ = hipGetLastError();                                                                \
+        if (e_ != hipSuccess) return e_;                                                                  \
+        if (out_.n) hipLaunchKernelGGL(KERNEL<false>, dim3(out_.grid), dim3(FT), 0, (STREAM), out_, __VA_ARGS__); \
+        return hipGetLastError();                                                                         \
     }())
 
 } // namespace flow

@@ -44,20 +44,20 @@ __device__ __forceinline__ void block_sum2(double &a, double &b)
     }
 }
 
-__device__ __forceinline__ void put2(const VRed &R, int slot0, double a, double b)
+__device__ __forceinline__ void put2(const VRed &R, int slot, double a, double b)
 {
     block_sum2(a, b);
     if (threadIdx.x == 0) {
-        R.part[slot0 + blockIdx.x] = a;
-        R.part[R.nb + slot0 + blockIdx.x] = b;
+        R.part[slot] = a;
+        R.part[R.nb + slot] = b;
     }
 }
 
 // (1/rho_f) G p on the +D face of the cell s steps along D; 0 on a wall face
 template <int D, class X, class R, class P> __device__ __forceinline__ double bflux(const X &x, R rho, P p, int s)
 {
-    if (x.template wall<D>(s)) return 0.0;
-    return cgrad<D>(x, p, s) / cface<D>(x, rho, s);
+    const double f = cgrad<D>(x, p, s) / cface<D>(x, rho, s);
+    return x.template wall<D>(s) ? 0.0 : f;
 }
 
 // D((1/rho_f) G p) at the cell
@@ -79,10 +79,11 @@ __device__ __forceinline__ double div_cell(const X &x, const double *u, const do
 
 // out = sign D((1/rho_f) G p); with R, partial sums of dzf p out
 template <bool FAST>
-__global__ __launch_bounds__(FT) void k_vc_apply(TileBox bx, int slot0, FGrid G, const double *rho, const double *p, double *out,
+__global__ __launch_bounds__(FT) void k_vc_apply(BoxList L, FGrid G, const double *rho, const double *p, double *out,
                                                  double sign, VRed R, int want)
 {
-    const FTile t = btile(G, bx);
+    const BoxPick pk = box_pick<FAST>(L);
+    const FTile t = btile(G, pk.b, pk.w);
     double a = 0.0;
     if (t.act) {
         double q = 0.0;
@@ -99,15 +100,16 @@ __global__ __launch_bounds__(FT) void k_vc_apply(TileBox bx, int slot0, FGrid G,
         out[c] = q;
         a = G.dzf[t.k] * p[c] * q;
     }
-    if (want) put2(R, slot0, a, 0.0);
+    if (want) put2(R, pk.slot, a, 0.0);
 }
 
 // r = -(D u) / dt; partial sum of dzf r
 template <bool FAST>
-__global__ __launch_bounds__(FT) void k_vc_rhs(TileBox bx, int slot0, FGrid G, const double *u, const double *v, const double *w,
+__global__ __launch_bounds__(FT) void k_vc_rhs(BoxList L, FGrid G, const double *u, const double *v, const double *w,
                                                double idt, double *r, VRed R)
 {
-    const FTile t = btile(G, bx);
+    const BoxPick pk = box_pick<FAST>(L);
+    const FTile t = btile(G, pk.b, pk.w);
     double a = 0.0;
     if (t.act) {
         double q = 0.0;
@@ -115,7 +117,7 @@ __global__ __launch_bounds__(FT) void k_vc_rhs(TileBox bx, int slot0, FGrid G, c
         r[at(G, t.i, t.j, t.k)] = q;
         a = G.dzf[t.k] * q;
     }
-    put2(R, slot0, a, 0.0);
+    put2(R, pk.slot, a, 0.0);
 }
 
 // The vector kernels take the cells in memory order, one per thread, so a
@@ -149,7 +151,7 @@ __global__ __launch_bounds__(FT) void k_vc_center(FGrid G, double *r, VRed R)
         r[l.c] = q;
         a = G.dzf[l.k] * q * q;
     }
-    put2(R, 0, a, 0.0);
+    put2(R, (int)blockIdx.x, a, 0.0);
 }
 
 // d = -rho0 z (z: the constant-coefficient solve of r); partial dzf r d
@@ -163,7 +165,7 @@ __global__ __launch_bounds__(FT) void k_vc_dinit(FGrid G, const double *r, const
         d[l.c] = q;
         a = G.dzf[l.k] * r[l.c] * q;
     }
-    put2(R, 0, a, 0.0);
+    put2(R, (int)blockIdx.x, a, 0.0);
 }
 
 // p += alpha d; r -= alpha q; partial sums of dzf r and dzf r^2
@@ -181,7 +183,7 @@ __global__ __launch_bounds__(FT) void k_vc_update(FGrid G, double *p, const doub
         a = wz * rr;
         b = wz * rr * rr;
     }
-    put2(R, 0, a, b);
+    put2(R, (int)blockIdx.x, a, b);
 }
 
 // r -= m (the mean the residual drifted by); partial dzf r (-rho0 z)
@@ -194,7 +196,7 @@ __global__ __launch_bounds__(FT) void k_vc_dot(FGrid G, double *r, const double 
         r[l.c] = rr;
         a = G.dzf[l.k] * rr * (-rho0 * z[l.c]);
     }
-    put2(R, 0, a, 0.0);
+    put2(R, (int)blockIdx.x, a, 0.0);
 }
 
 // d = -rho0 z + beta d
@@ -207,7 +209,7 @@ __global__ __launch_bounds__(FT) void k_vc_dupd(FGrid G, const double *z, double
 __global__ __launch_bounds__(FT) void k_vc_pmean(FGrid G, const double *p, VRed R)
 {
     const LCell l = lcell(G);
-    put2(R, 0, l.act ? G.dzf[l.k] * p[l.c] : 0.0, 0.0);
+    put2(R, (int)blockIdx.x, l.act ? G.dzf[l.k] * p[l.c] : 0.0, 0.0);
 }
 
 __global__ __launch_bounds__(FT) void k_vc_pshift(FGrid G, double *p, VRed R)
@@ -218,11 +220,12 @@ __global__ __launch_bounds__(FT) void k_vc_pshift(FGrid G, double *p, VRed R)
 
 // u_out = u - dt (1/rho_f) G p on the +face of each direction, 0 on a wall face
 template <bool FAST>
-__global__ __launch_bounds__(FT) void k_vc_correct(TileBox bx, int slot0, FGrid G, const double *rho, const double *p, const double *u,
+__global__ __launch_bounds__(FT) void k_vc_correct(BoxList L, FGrid G, const double *rho, const double *p, const double *u,
                                                    const double *v, const double *w, double dt, double *uo,
                                                    double *vo, double *wo)
 {
-    const FTile t = btile(G, bx);
+    const BoxPick pk = box_pick<FAST>(L);
+    const FTile t = btile(G, pk.b, pk.w);
     if (!t.act) return;
     const size_t c = at(G, t.i, t.j, t.k);
     double gx = 0.0, gy = 0.0, gz = 0.0;
