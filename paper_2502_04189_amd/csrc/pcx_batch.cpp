@@ -24,6 +24,7 @@
 #include <vector>
 
 #include "pcx.h"
+#include "pcx_fplan.hpp"
 #include "pcx_launch.hpp"
 #include "pcx_plan.hpp"
 #include "pcx_tune.hpp"
@@ -104,9 +105,9 @@ static long tiles_of(const Dom &d, int kind)
     case PK_XFWD_RHS:
     case PK_XFWD_RESID:
     case PK_XINV_STORE:
-    case PK_XINV_ACCUM: return (long)d.ntj * d.nz;
+    case PK_XINV_ACCUM: return x_tiles(d);
     case PK_YF:
-    case PK_YI: return (long)d.ntk * d.nl;
+    case PK_YI: return y_tiles(d);
     case PK_Z: return d.nzt;
     case PK_PMEAN: return 1;
     default: return d.mg[0].ntiles;
@@ -129,7 +130,8 @@ namespace pcx {
 // Kernel variant of pass `kind` for domain d (see launch_group).
 GVariant variant_of(const Dom &d, int kind, int smax)
 {
-    GVariant v{kind, NT, 0, 0};
+    GVariant v{kind, NT, 0, 0, 0};
+    auto fixed = [](int n) { return n <= FSMALL ? 1 : n; };
     switch (kind) {
     case PK_RHS: v.nth = march_threads(0); v.two = 5 * (d.mg[0].cti + d.mg[0].ctj) > v.nth; break;
     case PK_RESID: v.nth = march_threads(0); break;
@@ -137,9 +139,9 @@ GVariant variant_of(const Dom &d, int kind, int smax)
     case PK_XFWD_RHS:
     case PK_XFWD_RESID:
     case PK_XINV_STORE:
-    case PK_XINV_ACCUM: v.nth = d.xth; break;
+    case PK_XINV_ACCUM: v.nth = d.xth; v.n = d.xlines ? fixed(d.M) : 0; break;
     case PK_YF:
-    case PK_YI: v.nth = d.yth; break;
+    case PK_YI: v.nth = d.yth; v.n = d.ylines ? fixed(d.ny) : 0; break;
     case PK_Z: v.smax = smax; break;
     case PK_PMEAN: v.nth = 64; break;
     default: break;
@@ -210,7 +212,7 @@ static pcx_status build_phased(pcx_batch B)
         for (int i : order) {
             const GVariant v = variant_of(B->doms[i], ph.kind, B->smaxs[i]);
             auto it = std::find_if(grp.begin(), grp.end(), [&](const std::pair<GVariant, std::vector<int>> &g) {
-                return g.first.nth == v.nth && g.first.two == v.two && g.first.smax == v.smax;
+                return g.first.nth == v.nth && g.first.two == v.two && g.first.smax == v.smax && g.first.n == v.n;
             });
             if (it == grp.end()) grp.push_back({v, {i}});
             else it->second.push_back(i);
@@ -236,7 +238,7 @@ static pcx_status build_phased(pcx_batch B)
                 lst.swap(perm);
             }
             int grid = (int)lst.size();
-            if (B->mode == 1) {
+            if (B->mode == 1 && !g.first.n) { // the fixed-plan passes take an item per workgroup
                 int per_cu = 0;
                 if (group_occupancy(g.first, B->prec, lds, &per_cu) != hipSuccess || per_cu < 1) per_cu = 1;
                 long cap = std::max(8L, ((long)prop.multiProcessorCount * per_cu) & ~7L);

@@ -79,6 +79,7 @@ struct Dom {
     int zg, zlpw, nzt;                // z lanes per line, lines per WG, z tiles
     MGeo mg[2];                       // marching tiles: [0] RHS and residual, [1] correction
     int mth, yth, xth;                // threads of the marching, y and x workgroups
+    int xlines, ylines;               // lines per tile of the fixed-plan x and y passes (0: general passes)
     FastDiv dnx, dny, dtj, dtk, dnyc, dM, dH1, dM1, dhy; // dH1: M/2+1, dM1: M+1, dhy: ny/2
     double dx, dy, idx, idy, dt, rho0, irho0, lz, scale;
     // z tables (FP64): dzf, 1/dzf, 1/dzc, rho interpolation weights
@@ -106,16 +107,24 @@ struct Dom {
 // pmean[8 ..]; pmean[0] is the mean (PMEAN_LEN doubles in all).
 constexpr int XMAX_WG = 64;
 constexpr int PMEAN_LEN = 8 + XMAX_WG;
-__host__ __device__ inline int xslots(const Dom &d) { return d.ntj * d.nz * (d.xth >> 6); }
+__host__ __device__ inline int x_tiles(const Dom &d)
+{
+    return d.xlines ? (d.ny * d.nz + d.xlines - 1) / d.xlines : d.ntj * d.nz;
+}
+__host__ __device__ inline int y_tiles(const Dom &d)
+{
+    return d.ylines ? (int)(((long)d.nl * d.nz + d.ylines - 1) / d.ylines) : d.ntk * d.nl;
+}
+__host__ __device__ inline int xslots(const Dom &d) { return x_tiles(d) * (d.xth >> 6); }
 // partial-maximum slots of the fused stencil x passes: one per wave, one
 // wave per row of a tile
 __host__ __device__ inline int sslots(const Dom &d) { return d.ntj * d.nz * d.tj; }
-// Workgroups of the divergence-only pass: a wave per row, at most 2048
-// workgroups (8 per CU).
+// Workgroups of the divergence-only pass: a wave per row, at most 1024
+// workgroups (4 per CU).
 __host__ __device__ inline int div_wgs(const Dom &d)
 {
     const int v = (d.ny * d.nz + NT / 64 - 1) / (NT / 64);
-    return v > 2048 ? 2048 : v;
+    return v > 1024 ? 1024 : v;
 }
 // workgroups of the reduction of those slots (pass_xmax), at most XMAX_WG
 __host__ __device__ inline int xmax_wgs(const Dom &d)
@@ -220,9 +229,54 @@ template <bool INV, typename C, typename T> __device__ __forceinline__ void bfly
     a[3] = cadd(e3, w3); a[7] = csub(e3, w3);
 }
 
+// a times (c, -s) (INV: its conjugate)
+template <bool INV, typename C, typename T> __device__ __forceinline__ C crot(C a, T c, T s)
+{
+    return INV ? C{a.x * c - a.y * s, a.x * s + a.y * c} : C{a.x * c + a.y * s, a.y * c - a.x * s};
+}
+
+// 6 = 2 x 3 and 9 = 3 x 3: output k1 + R1 k2 from the R1-point sums over
+// stride R2, turned by W_R^(n2 k1), then the R2-point sums over n2
+template <bool INV, typename C, typename T> __device__ __forceinline__ void bfly6(C *a)
+{
+    const T h = T(0.5), s = T(0.86602540378443864676); // cos, sin of 2 pi / 6
+    C x0 = a[0], x1 = a[1], x2 = a[2], y0 = a[3], y1 = a[4], y2 = a[5];
+    bfly2<INV>(x0, y0);
+    bfly2<INV>(x1, y1);
+    bfly2<INV>(x2, y2);
+    y1 = crot<INV, C, T>(y1, h, s);
+    y2 = crot<INV, C, T>(y2, -h, s);
+    bfly3<INV, C, T>(x0, x1, x2);
+    bfly3<INV, C, T>(y0, y1, y2);
+    a[0] = x0; a[2] = x1; a[4] = x2;
+    a[1] = y0; a[3] = y1; a[5] = y2;
+}
+
+template <bool INV, typename C, typename T> __device__ __forceinline__ void bfly9(C *a)
+{
+    // cos and sin of 2 pi e / 9, e = 1, 2, 4
+    const T c1 = T(0.76604444311897803520), s1 = T(0.64278760968653932632);
+    const T c2_ = T(0.17364817766693034885), s2_ = T(0.98480775301220805937);
+    const T c4 = T(-0.93969262078590838405), s4 = T(0.34202014332566873304);
+#pragma unroll
+    for (int n2 = 0; n2 < 3; ++n2) bfly3<INV, C, T>(a[n2], a[n2 + 3], a[n2 + 6]);
+    a[4] = crot<INV, C, T>(a[4], c1, s1);
+    a[7] = crot<INV, C, T>(a[7], c2_, s2_);
+    a[5] = crot<INV, C, T>(a[5], c2_, s2_);
+    a[8] = crot<INV, C, T>(a[8], c4, s4);
+#pragma unroll
+    for (int k1 = 0; k1 < 3; ++k1) bfly3<INV, C, T>(a[3 * k1], a[3 * k1 + 1], a[3 * k1 + 2]);
+    // a[3 k1 + k2] is output k1 + 3 k2
+    C t = a[1]; a[1] = a[3]; a[3] = t;
+    t = a[2]; a[2] = a[6]; a[6] = t;
+    t = a[5]; a[5] = a[7]; a[7] = t;
+}
+
 template <bool INV, int R, typename C, typename T> __device__ __forceinline__ void bfly(C *a)
 {
-    if constexpr (R == 2) bfly2<INV>(a[0], a[1]);
+    if constexpr (R == 6) bfly6<INV, C, T>(a);
+    else if constexpr (R == 9) bfly9<INV, C, T>(a);
+    else if constexpr (R == 2) bfly2<INV>(a[0], a[1]);
     else if constexpr (R == 3) bfly3<INV, C, T>(a[0], a[1], a[2]);
     else if constexpr (R == 4) bfly4<INV>(a[0], a[1], a[2], a[3]);
     else bfly8<INV, C, T>(a);
@@ -341,14 +395,13 @@ struct TwStage {
 };
 
 // ------------------------------------------------------ wave-level FFT
-// Lengths 256 and 512 (plans 4.4.4.4 or 8.8.4, and 8.8.8; see wave_plan) can also be
-// transformed by one wave per line: butterfly j of a stage is lane j mod 64,
-// every index is a compile-time shift or mask, and no workgroup barrier is
-// needed between stages (the LDS operations of one wave execute in order;
-// the fences keep the compiler from moving them across a stage boundary).
-// Same arithmetic, in the same order, as fft_stage with the same radices.
-__host__ __device__ constexpr bool wave_len(int n) { return n == 256 || n == 512; }
-
+// The fused stencil x passes transform rows of half length 256 and 512
+// (plans 4.4.4.4 or 8.8.4, and 8.8.8; see wave_plan) with one wave per line:
+// butterfly j of a stage is lane j mod 64, every index is a compile-time
+// shift or mask, and no workgroup barrier is needed between stages (the LDS
+// operations of one wave execute in order; the fences keep the compiler from
+// moving them across a stage boundary).  Same arithmetic, in the same order,
+// as fft_stage with the same radices.
 __device__ __forceinline__ void wave_sync()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -399,7 +452,6 @@ __device__ __forceinline__ void wstage(c2<T> *ln, const c2<T> *tw, int lane)
     wave_sync();
 }
 
-// Whole line of length n (wave_len(n)) by the calling wave.
 // The plans the wave path has: 256 as 4.4.4.4 (every lane holds one
 // butterfly in every stage) or 8.8.4, 512 as 8.8.8.
 __host__ __device__ inline bool wave_plan(const FftDesc &fd)
@@ -410,6 +462,7 @@ __host__ __device__ inline bool wave_plan(const FftDesc &fd)
     return fd.nst == 3 && fd.rad[0] == 8 && fd.rad[1] == 8 && fd.rad[2] == 4;
 }
 
+// Whole line by the calling wave (its descriptor has one of these plans).
 template <typename T, bool INV>
 __device__ __forceinline__ void wave_fft(c2<T> *ln, const c2<T> *tw, const FftDesc &fd, int lane)
 {

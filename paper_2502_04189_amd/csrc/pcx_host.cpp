@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "pcx.h"
+#include "pcx_fplan.hpp"
 #include "pcx_launch.hpp"
 #include "pcx_plan.hpp"
 #include "pcx_tune.hpp"
@@ -173,14 +174,15 @@ void choose_shapes(const pcx_grid &g, int prec, const TuneParams *tp, Shapes &sh
     sh.mth = batch ? NT : 512;
     sh.mthc = batch ? NT : 1024;
     // wider y workgroups when a tile holds many columns: more waves per CU
-    // 512-thread y workgroups when a tile holds many columns (more waves per
-    // CU), and when its columns fit one per wave on the wave-level FFT path
-    sh.yth = (!batch && ((long)sh.tk * (lds_line(g.ny) * (long)csz) > 48 * 1024 ||
-                         (wave_len(g.ny) && sh.tk > NT / 64 && sh.tk <= 8)))
-                 ? 512
-                 : NT;
+    sh.yth = !batch && (long)sh.tk * (lds_line(g.ny) * (long)csz) > 48 * 1024 ? 512 : NT;
     sh.xth = batch ? NT : 512;
     sh.batch = batch;
+    // lengths with a fixed plan (the one-kernel batch schedule has the
+    // general passes only)
+    sh.xfix = !batch && M <= FXMAX && fplan(M).n ? fft_lines(M, (int)csz) : 0;
+    sh.yfix = !batch && fplan(g.ny).n ? fft_lines(g.ny, (int)csz) : 0;
+    if (sh.xfix) sh.xth = fft_threads(M, (int)csz);
+    if (sh.yfix) sh.yth = fft_threads(g.ny, (int)csz);
 }
 
 // Planes per chunk of a marching launch of txy tiles per plane that has the
@@ -242,6 +244,8 @@ void make_domain(const pcx_grid &g, int prec, const Shapes &sh, const RadixChoic
     }
     d.yth = sh.yth;
     d.xth = sh.xth;
+    d.xlines = sh.xfix;
+    d.ylines = sh.yfix;
     d.dnx = mkdiv(nx); d.dny = mkdiv(ny); d.dtj = mkdiv(sh.tj); d.dtk = mkdiv(sh.tk); d.dnyc = mkdiv(ny);
     d.dM = mkdiv(M);
     d.dH1 = mkdiv(M / 2 + 1);
@@ -350,13 +354,20 @@ pcx_status build_domain(const pcx_grid &g, int prec, const Shapes &sh, const Rad
     return PCX_OK;
 }
 
+// LDS of the general x pass: rows, FFT roots, split twiddles, then (x
+// inverse) 16 reduction doubles
+size_t lds_x_general(const Dom &d, int prec)
+{
+    return ((size_t)d.tj * lds_line(d.nl) + tw_half(d.M) + d.M / 2 + 1) * (prec == PREC_F64 ? 16 : 8) + 128;
+}
 size_t lds_x(const Dom &d, int prec)
 {
-    // rows, FFT roots, split twiddles, then (x inverse) 16 reduction doubles
-    return ((size_t)d.tj * lds_line(d.nl) + tw_half(d.M) + d.M / 2 + 1) * (prec == PREC_F64 ? 16 : 8) + 128;
+    if (d.xlines) return fft_lds(d.M, prec == PREC_F64 ? 16 : 8, true);
+    return lds_x_general(d, prec);
 }
 size_t lds_y(const Dom &d, int prec)
 {
+    if (d.ylines) return fft_lds(d.ny, prec == PREC_F64 ? 16 : 8, false);
     return ((size_t)d.tk * lds_line(d.ny) + tw_half(d.ny)) * (prec == PREC_F64 ? 16 : 8) + 64;
 }
 size_t lds_z(const Dom &d, int prec)
@@ -689,7 +700,7 @@ extern "C" pcx_status pcx_step(pcx_plan P, double dt, double rho0, const double 
     HIPCHK(launch_zero(P->stats, NSTAT, s));
     int solves = 0;
     if (P->fuse_rhs) {
-        HIPCHK(launch_sx(d, P->prec, SRC_RHS_ST, P->lx, s));
+        HIPCHK(launch_sx(d, P->prec, SRC_RHS_ST, s));
         tmark(P, s, "rhs_fftx");
         HIPCHK(launch_smax(d, s));
         tmark(P, s, "f_max");
@@ -704,7 +715,7 @@ extern "C" pcx_status pcx_step(pcx_plan P, double dt, double rho0, const double 
     solves = 1;
     auto refine_once = [&](int solve) -> pcx_status {
         if (P->fuse_resid) {
-            HIPCHK(launch_sx(d, P->prec, SRC_RESID_ST, P->lx, s));
+            HIPCHK(launch_sx(d, P->prec, SRC_RESID_ST, s));
             tmark(P, s, "resid_fftx");
         } else {
             HIPCHK(launch_resid(d, s));

@@ -4,6 +4,7 @@
 // multi-domain kernel of the batched form.
 #include <algorithm>
 
+#include "pcx_fplan.hpp"
 #include "pcx_launch.hpp"
 #include "pcx_passes.hpp"
 
@@ -203,6 +204,17 @@ hipError_t launch_resid(const Dom &d, hipStream_t s)
     PCX_LAUNCH_B(k_resid, xcd_grid(d.mg[0].ntiles), MT, 0, s, d);
 }
 
+// A fixed-plan pass of a lone domain: one workgroup per tile.
+static hipError_t launch_fft(const void *fn, const Dom &d, int tiles, int threads, size_t lds, hipStream_t s, int resid = 0)
+{
+    if (!fn) return hipErrorInvalidValue;
+    hipError_t e = lds_attr(fn, lds);
+    if (e != hipSuccess) return e;
+    FftArgs a{d, GArgs{nullptr, nullptr, 0, 0}, resid};
+    void *args[] = {&a};
+    return hipLaunchKernel(fn, dim3(tiles), dim3(threads), args, lds, s);
+}
+
 template <int NTH> static hipError_t launch_xfwd_t(const Dom &d, int prec, int src, size_t lds, hipStream_t s)
 {
     const int grid = d.ntj * d.nz;
@@ -216,6 +228,7 @@ template <int NTH> static hipError_t launch_xfwd_t(const Dom &d, int prec, int s
 
 hipError_t launch_xfwd(const Dom &d, int prec, int src, size_t lds, hipStream_t s)
 {
+    if (d.xlines) return launch_fft(fft_xfwd_kernel(prec, d.M), d, x_tiles(d), d.xth, lds, s, src == SRC_RESID);
     return d.xth == 512 ? launch_xfwd_t<512>(d, prec, src, lds, s) : launch_xfwd_t<NT>(d, prec, src, lds, s);
 }
 
@@ -224,9 +237,10 @@ bool sx_supported(const Dom &d)
     return (d.tj == 8 || d.tj == 16) && wave_plan(d.fx) && d.spart != nullptr;
 }
 
-hipError_t launch_sx(const Dom &d, int prec, int src, size_t lds, hipStream_t s)
+hipError_t launch_sx(const Dom &d, int prec, int src, hipStream_t s)
 {
     if (!sx_supported(d)) return hipErrorInvalidValue;
+    const size_t lds = lds_x_general(d, prec);
     const int grid = (int)(((sx_order_len(d) + 7) >> 3) << 3);
     if (d.tj == 8) {
         if (prec == PREC_F64) {
@@ -253,6 +267,8 @@ hipError_t launch_smax(const Dom &d, hipStream_t s)
 
 hipError_t launch_y(const Dom &d, int prec, bool inv, size_t lds, hipStream_t s)
 {
+    if (d.ylines)
+        return launch_fft(inv ? fft_yinv_kernel(prec, d.ny) : fft_yfwd_kernel(prec, d.ny), d, y_tiles(d), d.yth, lds, s);
     const int grid = d.ntk * d.nl;
     if (d.yth == 512) {
         if (prec == PREC_F64) {
@@ -296,6 +312,9 @@ template <int NTH> static hipError_t launch_xinv_t(const Dom &d, int prec, int m
 
 hipError_t launch_xinv(const Dom &d, int prec, int mode, int solve, size_t lds, hipStream_t s)
 {
+    if (d.xlines)
+        return launch_fft(mode == XOUT_STORE ? fft_xinv_store_kernel(prec, d.M) : fft_xinv_accum_kernel(prec, d.M), d,
+                          x_tiles(d), d.xth, lds, s);
     return d.xth == 512 ? launch_xinv_t<512>(d, prec, mode, solve, lds, s)
                         : launch_xinv_t<NT>(d, prec, mode, solve, lds, s);
 }
@@ -496,6 +515,21 @@ static const void *group_fn(const GVariant &v)
     return nullptr;
 }
 
+// Kernel of a fixed-plan group (v.n: the length, 1 for FSMALL and below).
+static const void *group_fft_fn(const GVariant &v, int prec)
+{
+    const int n = v.n == 1 ? FSMALL : v.n;
+    switch (v.kind) {
+    case PK_XFWD_RHS:
+    case PK_XFWD_RESID: return fft_xfwd_kernel(prec, n);
+    case PK_XINV_STORE: return fft_xinv_store_kernel(prec, n);
+    case PK_XINV_ACCUM: return fft_xinv_accum_kernel(prec, n);
+    case PK_YF: return fft_yfwd_kernel(prec, n);
+    case PK_YI: return fft_yinv_kernel(prec, n);
+    }
+    return nullptr;
+}
+
 static int group_threads(const GVariant &v)
 {
     switch (v.kind) {
@@ -511,6 +545,15 @@ static int group_threads(const GVariant &v)
 
 hipError_t launch_group(const GVariant &v, int prec, const GArgs &a, int grid, size_t lds, hipStream_t s)
 {
+    if (v.n) {
+        const void *f = group_fft_fn(v, prec);
+        if (!f || grid != a.nitems) return hipErrorInvalidValue; // an item per workgroup
+        hipError_t e = lds_attr(f, lds);
+        if (e != hipSuccess) return e;
+        FftArgs arg{Dom{}, a, v.kind == PK_XFWD_RESID};
+        void *args[] = {&arg};
+        return hipLaunchKernel(f, dim3(grid), dim3(v.nth), args, lds, s);
+    }
     const void *fn = prec == PREC_F64 ? group_fn<double>(v) : group_fn<float>(v);
     if (!fn) return hipErrorInvalidValue;
     hipError_t e = lds_attr(fn, lds);
@@ -597,13 +640,13 @@ __global__ __launch_bounds__(NT) void k_persist(PersistArgs a)
             switch (kind) {
             case PK_RHS: pass_rhs(d, tile, smem); break;
             case PK_RESID: pass_resid(d, tile, smem); break;
-            case PK_XFWD_RHS: pass_xfwd<T, SRC_RHS, NT, false>(d, tile, smem); break;
-            case PK_XFWD_RESID: pass_xfwd<T, SRC_RESID, NT, false>(d, tile, smem); break;
-            case PK_YF: pass_y<T, false, NT, false>(d, tile, smem); break;
+            case PK_XFWD_RHS: pass_xfwd<T, SRC_RHS, NT>(d, tile, smem); break;
+            case PK_XFWD_RESID: pass_xfwd<T, SRC_RESID, NT>(d, tile, smem); break;
+            case PK_YF: pass_y<T, false, NT>(d, tile, smem); break;
             case PK_Z: pass_z<T, SMAX>(d, tile, smem); break;
-            case PK_YI: pass_y<T, true, NT, false>(d, tile, smem); break;
-            case PK_XINV_STORE: pass_xinv<T, XOUT_STORE, NT, false>(d, tile, smem, sv); break;
-            case PK_XINV_ACCUM: pass_xinv<T, XOUT_ACCUM, NT, false>(d, tile, smem, sv); break;
+            case PK_YI: pass_y<T, true, NT>(d, tile, smem); break;
+            case PK_XINV_STORE: pass_xinv<T, XOUT_STORE, NT>(d, tile, smem, sv); break;
+            case PK_XINV_ACCUM: pass_xinv<T, XOUT_ACCUM, NT>(d, tile, smem, sv); break;
             case PK_PMEAN:
                 pass_xmax(d, sv, 0, 1, smem);
                 __syncthreads();

@@ -5,6 +5,8 @@
 
 namespace pcx {
 
+// LDS bytes of the general x pass (the fused stencil passes run it)
+size_t lds_x_general(const Dom &d, int prec);
 hipError_t launch_zero(unsigned long long *p, int n, hipStream_t s);
 hipError_t launch_rhs(const Dom &d, hipStream_t s);
 hipError_t launch_resid(const Dom &d, hipStream_t s);
@@ -12,7 +14,7 @@ hipError_t launch_xfwd(const Dom &d, int prec, int src, size_t lds, hipStream_t 
 // fused stencil + forward x pass (src SRC_RHS_ST or SRC_RESID_ST); the
 // RHS's per-wave maxima are reduced by launch_smax into ST_FINF
 bool sx_supported(const Dom &d);
-hipError_t launch_sx(const Dom &d, int prec, int src, size_t lds, hipStream_t s);
+hipError_t launch_sx(const Dom &d, int prec, int src, hipStream_t s);
 hipError_t launch_smax(const Dom &d, hipStream_t s);
 hipError_t launch_y(const Dom &d, int prec, bool inv, size_t lds, hipStream_t s);
 hipError_t launch_z(const Dom &d, int prec, int smax, size_t lds, hipStream_t s);
@@ -48,7 +50,21 @@ struct GArgs {
 // thread; z: levels per lane).
 struct GVariant {
     int kind, nth, two, smax;
+    int n; // x and y passes with a fixed plan: the length, FSMALL and below as 1 (0: the general passes)
 };
+// Arguments of a fixed-plan x or y pass: a lone domain (items NULL, nitems
+// tiles) or the items of a batch; resid: the forward x pass takes r, not f.
+struct FftArgs {
+    Dom d;
+    GArgs g;
+    int resid;
+};
+// kernels of the fixed-plan passes for a length (pcx_fft_*.hip)
+const void *fft_xfwd_kernel(int prec, int n);
+const void *fft_xinv_store_kernel(int prec, int n);
+const void *fft_xinv_accum_kernel(int prec, int n);
+const void *fft_yfwd_kernel(int prec, int n);
+const void *fft_yinv_kernel(int prec, int n);
 hipError_t launch_group(const GVariant &v, int prec, const GArgs &a, int grid, size_t lds, hipStream_t s);
 // resident workgroups per CU of a group's kernel
 hipError_t group_occupancy(const GVariant &v, int prec, size_t lds, int *blocks_per_cu);

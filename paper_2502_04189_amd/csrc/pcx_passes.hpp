@@ -638,7 +638,7 @@ __device__ __forceinline__ void pass_smax(const Dom &d, int wg, int nwg, char *s
 // Tile = (j tile, k): rows j0 .. j0+rows-1 of plane k of f (or r).  Real
 // FFT by a half-length complex FFT of z[n] = s[2n] + i s[2n+1] and the split
 // X[l] = E + W^l O, X[M-l] = conj(E - W^l O); then the corner turn into S1.
-template <typename T, int SRC, int NTH = NT, bool WV = true>
+template <typename T, int SRC, int NTH = NT>
 __device__ __forceinline__ void pass_xfwd(const Dom &d, int tile, char *smem)
 {
     using C = c2<T>;
@@ -701,25 +701,18 @@ __device__ __forceinline__ void pass_xfwd(const Dom &d, int tile, char *smem)
         row[pidx(kk)] = C{a.x, T(0)};
         if (kk >= 1 && kk < M) row[pidx(nx - kk)] = C{-a.y, T(0)};
     };
-    // one wave per row when the tile has at most one row per wave and the
-    // half length has the fixed wave plan (which must be the descriptor's)
+    // the fused forms run one wave per row: the tile has at most one row per
+    // wave and the half length has the fixed wave plan (sx_supported)
     constexpr int NW = NTH / 64;
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const bool wv = WV && d.tj <= NW && wave_plan(d.fx);
-    if (ST && !wv) return; // the host enables the fused forms only on the wave path
-    if (wv) {
+    if constexpr (ST) {
+        if (!(d.tj <= NW && wave_plan(d.fx))) return;
         if (wid < rows) {
             C *row = buf + wid * ldr;
-            if constexpr (ST) {
-                const double m = stencil_row<SRC>(d, j0 + wid, k, lane, [&](int h, double2 s) { put_pair(row, h, s); });
-                if constexpr (SRC == SRC_RHS_ST) {
-                    const double wm = wave_max1(m);
-                    if (lane == 0) d.spart[tile * NW + wid] = wm;
-                }
-            } else {
-                const double2 *sr = src2 + (size_t)wid * hx;
-                staged_copy_t<64, 8, double2>(
-                    lane, hx, [&](int h) { return sr[h]; }, [&](int h, double2 s) { put_pair(row, h, s); });
+            const double m = stencil_row<SRC>(d, j0 + wid, k, lane, [&](int h, double2 s) { put_pair(row, h, s); });
+            if constexpr (SRC == SRC_RHS_ST) {
+                const double wm = wave_max1(m);
+                if (lane == 0) d.spart[tile * NW + wid] = wm;
             }
         } else if (SRC == SRC_RHS_ST && lane == 0 && wid < NW) {
             d.spart[tile * NW + wid] = 0.0;
@@ -780,7 +773,7 @@ __device__ __forceinline__ void pass_xfwd(const Dom &d, int tile, char *smem)
 // Y pass, tile = (k tile, l).  Forward: columns (k, l) of S1 -> LDS -> FFT
 // (DCT-II for a wall) -> corner turn into the z-lines of S2; inverse the
 // reverse.
-template <typename T, bool INV, int NTH = NT, bool WV = true>
+template <typename T, bool INV, int NTH = NT>
 __device__ __forceinline__ void pass_y(const Dom &d, int tile, char *smem)
 {
     using C = c2<T>;
@@ -804,19 +797,7 @@ __device__ __forceinline__ void pass_y(const Dom &d, int tile, char *smem)
     const int cols = min(tk, nz - k0);
     TwStage<T, NTH> tws;
     tws.fetch(d.fy);
-    // one wave per column when the tile has at most one column per wave and
-    // the length has the fixed wave plan (which must be the descriptor's)
-    constexpr int NW = NTH / 64;
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const bool wv = WV && tk <= NW && wave_plan(d.fy);
-    if (!INV && wv) {
-        if (wid < cols) {
-            const C *src = s1 + ((size_t)(k0 + wid) * nl + l) * ny;
-            C *col = buf + wid * ldc;
-            staged_copy_t<64, 8, C>(
-                lane, ny, [&](int j) { return ld_stream(src + j); }, [&](int j, C v) { col[pidx(pos(j))] = sgn(j, v); });
-        }
-    } else if (!INV) {
+    if (!INV) {
         staged_copy<NTH, 8, C>(
             cols * ny,
             [&](int e) {
@@ -838,7 +819,7 @@ __device__ __forceinline__ void pass_y(const Dom &d, int tile, char *smem)
                 const int m = (int)fdiv((uint32_t)e, dtk), c = e - m * tk;
                 if (c < cols) buf[c * ldc + pidx(m)] = v;
             });
-        if (wy && !wv) {
+        if (wy) {
             // inverse DCT-II of complex columns: V_k = conj(w_k)(X_k - i X_{N-k}),
             // V_{N-k} = i w_k (X_{N-k} - i X_k), w_k = W_{4N}^k, X_N = 0
             __syncthreads();
@@ -861,50 +842,9 @@ __device__ __forceinline__ void pass_y(const Dom &d, int tile, char *smem)
     }
     tws.put(ltw, d.fy);
     __syncthreads();
-    if (wv) {
-        if (wid < cols) {
-            C *col = buf + wid * ldc;
-            if (INV && wy) {
-                // inverse DCT-II pre-step of this column (as in the workgroup path below)
-                for (int kk = 1 + lane; kk <= hy; kk += 64) {
-                    const int kn = ny - kk;
-                    C w = wd[kk];
-                    C xk = col[pidx(kk)], xn = col[pidx(kn)];
-                    C a = {xk.x + xn.y, xk.y - xn.x};
-                    col[pidx(kk)] = cmul(cconj(w), a);
-                    if (kn != kk) {
-                        C b = {xn.x + xk.y, xn.y - xk.x};
-                        C wb = cmul(w, b);
-                        col[pidx(kn)] = C{-wb.y, wb.x};
-                    }
-                }
-            }
-            wave_fft<T, INV>(col, ltw, d.fy, lane);
-            if (!INV && wy) {
-                for (int kk = 1 + lane; kk <= hy; kk += 64) {
-                    const int kn = ny - kk;
-                    C w = wd[kk];
-                    C p = cmul(w, col[pidx(kk)]), q = cmul(cconj(w), col[pidx(kn)]);
-                    col[pidx(kk)] = C{T(0.5) * (p.x + q.x), T(0.5) * (p.y + q.y)};
-                    if (kn != kk) col[pidx(kn)] = C{T(-0.5) * (p.y - q.y), T(0.5) * (p.x - q.x)};
-                }
-            }
-            if (INV) {
-                // the column goes back to S1 by its own wave
-                wave_sync();
-                C *dst = s1 + ((size_t)(k0 + wid) * nl + l) * ny;
-                // eight LDS reads in flight per lane, then the stores
-                staged_copy_t<64, 8, C>(
-                    lane, ny, [&](int j) { return sgn(j, col[pidx(pos(j))]); }, [&](int j, C v) { st_stream(dst + j, v); });
-            }
-        }
-        if (INV) return;
-        __syncthreads();
-    } else {
-        lds_fft<T, INV, NTH>(buf, ldc, cols, d.fy, ltw);
-    }
+    lds_fft<T, INV, NTH>(buf, ldc, cols, d.fy, ltw);
     if (!INV) {
-        if (wy && !wv) {
+        if (wy) {
             // DCT-II of complex columns from the FFT V of the reordered data:
             // X_k = (w_k V_k + conj(w_k) V_{N-k}) / 2,
             // X_{N-k} = i (w_k V_k - conj(w_k) V_{N-k}) / 2, X_0 = V_0
@@ -1160,7 +1100,7 @@ __device__ __forceinline__ void pass_z(const Dom &d, int tile, char *smem)
 // ------------------------------------------------------------------ xinv
 // Tile = (j tile, k).  Inverse real FFT of rows j0.. of plane k from S1;
 // MODE store: p = value; accum: p += value (refinement update).
-template <typename T, int MODE, int NTH = NT, bool WV = true>
+template <typename T, int MODE, int NTH = NT>
 __device__ __forceinline__ void pass_xinv(const Dom &d, int tile, char *smem, int solve)
 {
     using C = c2<T>;
@@ -1199,17 +1139,11 @@ __device__ __forceinline__ void pass_xinv(const Dom &d, int tile, char *smem, in
     const int npair = rows * (d.nx >> 1);
     double2 oldv[PF];
     double2 *po2 = (double2 *)(d.po + ((size_t)k * d.ny + j0) * d.nx);
-    // one wave per row (see below) when the tile has at most one row per
-    // wave and the half length has the fixed wave plan
-    constexpr int NW = NTH / 64;
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const bool wv = WV && d.tj <= NW && wave_plan(d.fx) && (M >> 6) <= PF;
     if (MODE == XOUT_ACCUM) {
 #pragma unroll
         for (int q = 0; q < PF; ++q) {
-            // pair of this thread: (row wid, lane + 64 q) on the wave path
-            const int e = wv ? (wid < rows && lane + 64 * q < (M) ? wid * M + lane + 64 * q : npair)
-                             : threadIdx.x + q * NTH;
+            const int e = threadIdx.x + q * NTH;
             oldv[q] = e < npair ? po2[e] : double2{0.0, 0.0};
         }
     }
@@ -1271,55 +1205,37 @@ __device__ __forceinline__ void pass_xinv(const Dom &d, int tile, char *smem, in
         // a stored p is the update itself: its maximum is emax
         if (MODE != XOUT_STORE) pmax = amax_nan(amax_nan(pmax, pv.x), pv.y);
     };
-    if (wv) {
-        // one wave per row: pre-steps, transform and output of its row
-        if (wid < rows) {
-            C *row = buf + wid * ldr;
-            if (wx) {
-                for (int kk = lane; kk <= M; kk += 64) dct_pre(row, kk);
-                wave_sync();
-            }
-            for (int l = lane; l <= half; l += 64) c2r_pre(row, l);
-            wave_fft<T, true>(row, ltw, d.fx, lane);
-#pragma unroll
-            for (int q = 0; q < PF; ++q) {
-                const int h = lane + 64 * q;
-                if (h < hx) emit(wid * hx + h, value(row, h), MODE == XOUT_STORE ? double2{0.0, 0.0} : oldv[q]);
-            }
-        }
-    } else {
-        if (wx) {
-            for (int idx = threadIdx.x; idx < rows * (M + 1); idx += NTH) {
-                int r = (int)fdiv((uint32_t)idx, d.dM1);
-                dct_pre(buf + r * ldr, idx - r * (M + 1));
-            }
-            __syncthreads();
-        }
-        for (int idx = threadIdx.x; idx < rows * (half + 1); idx += NTH) {
-            int r = (int)fdiv((uint32_t)idx, d.dH1);
-            c2r_pre(buf + r * ldr, idx - r * (half + 1));
+    if (wx) {
+        for (int idx = threadIdx.x; idx < rows * (M + 1); idx += NTH) {
+            int r = (int)fdiv((uint32_t)idx, d.dM1);
+            dct_pre(buf + r * ldr, idx - r * (M + 1));
         }
         __syncthreads();
-        lds_fft<T, true, NTH>(buf, ldr, rows, d.fx, ltw);
-        if (MODE == XOUT_STORE) {
-            for (int e = threadIdx.x; e < rows * hx; e += NTH) {
-                int r = (int)fdiv((uint32_t)e, d.dM);
-                emit(e, value(buf + r * ldr, e - r * hx), double2{0.0, 0.0});
-            }
-        } else {
+    }
+    for (int idx = threadIdx.x; idx < rows * (half + 1); idx += NTH) {
+        int r = (int)fdiv((uint32_t)idx, d.dH1);
+        c2r_pre(buf + r * ldr, idx - r * (half + 1));
+    }
+    __syncthreads();
+    lds_fft<T, true, NTH>(buf, ldr, rows, d.fx, ltw);
+    if (MODE == XOUT_STORE) {
+        for (int e = threadIdx.x; e < rows * hx; e += NTH) {
+            int r = (int)fdiv((uint32_t)e, d.dM);
+            emit(e, value(buf + r * ldr, e - r * hx), double2{0.0, 0.0});
+        }
+    } else {
 #pragma unroll
-            for (int q = 0; q < PF; ++q) {
-                const int e = threadIdx.x + q * NTH;
-                if (e < npair) {
-                    int r = (int)fdiv((uint32_t)e, d.dM);
-                    emit(e, value(buf + r * ldr, e - r * hx), oldv[q]);
-                }
-            }
-            // pairs beyond the prefetched ones (tiles of more than PF x NTH pairs)
-            for (int e = threadIdx.x + PF * NTH; e < npair; e += NTH) {
+        for (int q = 0; q < PF; ++q) {
+            const int e = threadIdx.x + q * NTH;
+            if (e < npair) {
                 int r = (int)fdiv((uint32_t)e, d.dM);
-                emit(e, value(buf + r * ldr, e - r * hx), po2[e]);
+                emit(e, value(buf + r * ldr, e - r * hx), oldv[q]);
             }
+        }
+        // pairs beyond the prefetched ones (tiles of more than PF x NTH pairs)
+        for (int e = threadIdx.x + PF * NTH; e < npair; e += NTH) {
+            int r = (int)fdiv((uint32_t)e, d.dM);
+            emit(e, value(buf + r * ldr, e - r * hx), po2[e]);
         }
     }
     if (MODE == XOUT_STORE) pmax = emax;

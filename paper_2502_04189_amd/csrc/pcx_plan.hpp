@@ -14,6 +14,7 @@ struct Shapes {
     int tj = 8, tk = 8, zg = 64, smax = 8;
     int yth = 256, mth = 512, mthc = 1024, xth = 512;
     bool batch = false;
+    int xfix = 0, yfix = 0; // lines per tile of the fixed-plan passes (0: general passes)
     // planes per chunk of the marching passes ([0] RHS and residual, [1]
     // correction); 0: chosen for a domain that has the device to itself
     int ckc[2] = {0, 0};

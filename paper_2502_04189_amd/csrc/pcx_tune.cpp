@@ -249,8 +249,8 @@ pcx_status autotune_class(const pcx_grid &g, int prec, hipStream_t s, TuneParams
     best.tj = base.tj; best.tk = base.tk; best.zg = base.zg;
     brc.x = default_radices(M);
     brc.y = default_radices(g.ny);
-    // x passes
-    {
+    // x passes (the lengths with a fixed plan have one shape)
+    if (!base.xfix) {
         float bt = 1e30f;
         for (int tj = 1; tj <= 64; tj *= 2) {
             if ((long)tj * M > MAXPTS || (long)tj * lds_line(nlx) * (long)csz > cap) continue;
@@ -271,7 +271,7 @@ pcx_status autotune_class(const pcx_grid &g, int prec, hipStream_t s, TuneParams
         }
     }
     // y passes
-    {
+    if (!base.yfix) {
         float bt = 1e30f;
         for (int tk = 1; tk <= 64; tk *= 2) {
             if ((long)tk * g.ny > MAXPTS || (long)tk * lds_line(g.ny) * (long)csz > cap) continue;
