@@ -16,7 +16,7 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libpcx.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-SOURCES = ["pcx_fft_xf.hip", "pcx_fft_xi.hip", "pcx_fft_xa.hip", "pcx_fft_yf.hip", "pcx_fft_yi.hip", "pcx_kernels.hip", "pcx_host.cpp", "pcx_batch.cpp", "pcx_tune.cpp", "pcx_noalloc.cpp",
+SOURCES = ["pcx_fft_xf.hip", "pcx_fft_xi.hip", "pcx_fft_xa.hip", "pcx_fft_yf.hip", "pcx_fft_yi.hip", "pcx_z.hip", "pcx_kernels.hip", "pcx_host.cpp", "pcx_batch.cpp", "pcx_tune.cpp", "pcx_noalloc.cpp",
            "flow_kernels.hip", "flow_host.cpp", "varcoef_kernels.hip", "varcoef_host.cpp"]
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
          # no packed FP32 instructions anywhere in the device code

@@ -66,7 +66,6 @@ struct pcx_batch_s {
         size_t lds;
     };
     std::vector<Group> groups;
-    std::vector<int> smaxs;         // z levels per lane of each domain
 };
 
 static void batch_free(pcx_batch B)
@@ -128,7 +127,7 @@ static int batch_mode()
 namespace pcx {
 
 // Kernel variant of pass `kind` for domain d (see launch_group).
-GVariant variant_of(const Dom &d, int kind, int smax)
+GVariant variant_of(const Dom &d, int kind)
 {
     GVariant v{kind, NT, 0, 0, 0};
     auto fixed = [](int n) { return n <= FSMALL ? 1 : n; };
@@ -142,7 +141,7 @@ GVariant variant_of(const Dom &d, int kind, int smax)
     case PK_XINV_ACCUM: v.nth = d.xth; v.n = d.xlines ? fixed(d.M) : 0; break;
     case PK_YF:
     case PK_YI: v.nth = d.yth; v.n = d.ylines ? fixed(d.ny) : 0; break;
-    case PK_Z: v.smax = smax; break;
+    case PK_Z: v.smax = d.zlev; v.n = 1; break;
     case PK_PMEAN: v.nth = 64; break;
     default: break;
     }
@@ -210,7 +209,7 @@ static pcx_status build_phased(pcx_batch B)
         // domains of each kernel variant, in first-appearance order
         std::vector<std::pair<GVariant, std::vector<int>>> grp;
         for (int i : order) {
-            const GVariant v = variant_of(B->doms[i], ph.kind, B->smaxs[i]);
+            const GVariant v = variant_of(B->doms[i], ph.kind);
             auto it = std::find_if(grp.begin(), grp.end(), [&](const std::pair<GVariant, std::vector<int>> &g) {
                 return g.first.nth == v.nth && g.first.two == v.two && g.first.smax == v.smax && g.first.n == v.n;
             });
@@ -238,7 +237,7 @@ static pcx_status build_phased(pcx_batch B)
                 lst.swap(perm);
             }
             int grid = (int)lst.size();
-            if (B->mode == 1 && !g.first.n) { // the fixed-plan passes take an item per workgroup
+            if (B->mode == 1 && !g.first.n) { // the fixed-plan and z passes take an item per workgroup
                 int per_cu = 0;
                 if (group_occupancy(g.first, B->prec, lds, &per_cu) != hipSuccess || per_cu < 1) per_cu = 1;
                 long cap = std::max(8L, ((long)prop.multiProcessorCount * per_cu) & ~7L);
@@ -323,7 +322,6 @@ extern "C" pcx_status pcx_batch_create(const pcx_domain *domains, int32_t n, con
     TuneCache cache;
     if (o.tune_cache) cache.load(o.tune_cache);
     B->mode = batch_mode();
-    B->smaxs.assign(n, 4);
 
     // phases
     PhaseTab &tab = B->tab;
@@ -374,7 +372,6 @@ extern "C" pcx_status pcx_batch_create(const pcx_domain *domains, int32_t n, con
         // 12 to 32 planes take the same time from 8 domains to 192, 4 planes
         // 4 % longer, whole columns 4 % (192 domains) to 70 % (8) longer
         sh.ckc[0] = sh.ckc[1] = 16;
-        B->smaxs[i] = sh.smax;
         pcx_status st = build_domain(B->grids[i], B->prec, sh, have || o.autotune ? &rc : nullptr, B->tables[i], B->doms[i]);
         if (st != PCX_OK) { batch_free(B); return st; }
         B->smax = std::max(B->smax, sh.smax);
@@ -383,7 +380,7 @@ extern "C" pcx_status pcx_batch_create(const pcx_domain *domains, int32_t n, con
         const size_t nspec = (size_t)B->doms[i].nl * B->grids[i].ny * B->grids[i].nz;
         const size_t ncell = (size_t)B->grids[i].nx * B->grids[i].ny * B->grids[i].nz;
         off_s1[i] = take(nspec * csz);
-        off_s2[i] = take(nspec * csz);
+        off_s2[i] = take(nspec / B->grids[i].nz * B->doms[i].zs * csz);
         off_f[i] = take(ncell * 8);
         off_r[i] = B->prec == PREC_F32 ? take(ncell * 8) : 0;
         off_pp[i] = B->prec == PREC_F32 ? take(((size_t)xslots(B->doms[i]) + PMEAN_LEN) * 8) : 0;

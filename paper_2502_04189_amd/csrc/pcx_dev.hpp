@@ -10,8 +10,9 @@
 // Spectral data live in two workspace layouts, chosen so that every pass
 // reads or writes long contiguous runs and does its corner turn in LDS:
 //   S1 "y-columns": ((k*NL + l)*NY + j)   one (k,l) column contiguous in j/m
-//   S2 "z-lines"  : ((l*NY + m)*NZ + k)   one (l,m) line contiguous in k
-// with NL = nx/2 + 1 half-spectrum x modes.
+//   S2 "z-lines"  : ((l*NY + m)*ZS + k)   one (l,m) line contiguous in k
+// with NL = nx/2 + 1 half-spectrum x modes and ZS = nz rounded up to whole
+// 128-byte lines (so that the y passes' segments of k are aligned).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -77,6 +78,9 @@ struct Dom {
     int tj, ntj;                      // x-pass rows per tile, j tiles
     int tk, ntk;                      // y-pass columns per tile, k tiles
     int zg, zlpw, nzt;                // z lanes per line, lines per WG, z tiles
+    int zlev;                         // levels per lane of the z kernel: zg zlev >= nz
+    int zs;                           // stride of the z-lines in S2, >= nz
+    FastDiv dzs;
     MGeo mg[2];                       // marching tiles: [0] RHS and residual, [1] correction
     int mth, yth, xth;                // threads of the marching, y and x workgroups
     int xlines, ylines;               // lines per tile of the fixed-plan x and y passes (0: general passes)

@@ -419,7 +419,8 @@ template <typename T, int N> __device__ __forceinline__ void fft_yfwd(const Dom 
     F.last();
     const int c = threadIdx.x % L, q = q0 + c;
     const YLine y = yline(d, min(q, nlin - 1));
-    C *out = (C *)d.s2 + (size_t)y.l * N * nz + y.k;
+    const int zs = d.zs;
+    C *out = (C *)d.s2 + (size_t)y.l * N * zs + y.k;
     const C *z = buf + c * LDC;
     constexpr int K = (N + STEP - 1) / STEP;
     const bool on = q < nlin;
@@ -427,7 +428,7 @@ template <typename T, int N> __device__ __forceinline__ void fft_yfwd(const Dom 
 #pragma unroll
         for (int t = 0; t < K; ++t) {
             const int m = threadIdx.x / L + t * STEP;
-            if (on && (N % STEP == 0 || m < N)) st_stream(out + (size_t)m * nz, z[pidx(m)]);
+            if (on && (N % STEP == 0 || m < N)) st_stream(out + (size_t)m * zs, z[pidx(m)]);
         }
     } else {
         // X_m = (w_m V_m + conj(w_m) V_{N-m}) / 2, X_0 = V_0
@@ -439,7 +440,7 @@ template <typename T, int N> __device__ __forceinline__ void fft_yfwd(const Dom 
                 const C w = wd[m], p = cmul(w, v), g = cmul(cconj(w), z[pidx(N - m)]);
                 v = C{T(0.5) * (p.x + g.x), T(0.5) * (p.y + g.y)};
             }
-            if (on) st_stream(out + (size_t)m * nz, v);
+            if (on) st_stream(out + (size_t)m * zs, v);
         }
     }
 }
@@ -458,13 +459,14 @@ template <typename T, int N> __device__ __forceinline__ void fft_yinv(const Dom 
     C *s1 = (C *)d.s1;
     const int c = threadIdx.x % L;
     const YLine y = yline(d, min(q0 + c, nlin - 1));
-    const C *in = (const C *)d.s2 + (size_t)y.l * N * nz + y.k;
+    const int zs = d.zs;
+    const C *in = (const C *)d.s2 + (size_t)y.l * N * zs + y.k;
     tws.put(ltw, d.fy);
     const LineFft<T, true, N, L, NTH> F{buf, ltw};
     if (!wy) {
         // the first stage's threads take consecutive lines (thread % L is
         // their line in every round), whose points are contiguous in S2
-        F.template first<true, false>([&](int, int n) { return ld_stream(in + (size_t)n * nz); });
+        F.template first<true, false>([&](int, int n) { return ld_stream(in + (size_t)n * zs); });
         F.middles();
         F.last(
             [&](int line, int n, C v, int) {
@@ -479,7 +481,7 @@ template <typename T, int N> __device__ __forceinline__ void fft_yinv(const Dom 
     {
         C v[K];
 #pragma unroll
-        for (int t = 0; t < K; ++t) v[t] = ld_stream(in + (size_t)min((int)threadIdx.x / L + t * STEP, N - 1) * nz);
+        for (int t = 0; t < K; ++t) v[t] = ld_stream(in + (size_t)min((int)threadIdx.x / L + t * STEP, N - 1) * zs);
 #pragma unroll
         for (int t = 0; t < K; ++t) {
             const int m = threadIdx.x / L + t * STEP;

@@ -156,7 +156,15 @@ void choose_shapes(const pcx_grid &g, int prec, const TuneParams *tp, Shapes &sh
     int tk = pow2_floor(std::max(1, MAXPTS / g.ny));
     tk = std::min(tk, pow2_floor(lds_cap / (long)(lds_line(g.ny) * csz)));
     tk = std::min(tk, seg);
-    int G = std::min(64, pow2_floor(std::max(1, g.nz / 2)));
+    // z lanes per line: eight levels a lane, since every doubling of the
+    // lanes is another reduction step for all of them (256^3 FP64: 62 us with
+    // 8 levels, 74 with 4, 88 with 16, copy rate 49; 384 x 288 x 250 walls 92,
+    // 119, 130); grids that leave most of the device idle take four, a
+    // shorter chain (32^3: 11 us against 13).  By the grid alone: a batch's
+    // domains round as lone ones do.
+    const int levels = (int64_t)g.nx * g.ny * g.nz < 65536 ? 4 : 8;
+    int G = 1;
+    while (G < 64 && 2 * G <= std::max(1, g.nz / 2) && (g.nz + G - 1) / G > levels) G *= 2;
     if (tp) {
         if (tp->tj > 0) tj = tp->tj;
         if (tp->tk > 0) tk = tp->tk;
@@ -169,8 +177,7 @@ void choose_shapes(const pcx_grid &g, int prec, const TuneParams *tp, Shapes &sh
     sh.tj = std::max(1, tj);
     sh.tk = std::max(1, tk);
     sh.zg = G;
-    int smax_need = (g.nz + G - 1) / G;
-    sh.smax = smax_need <= 4 ? 4 : (smax_need <= 8 ? 8 : 16);
+    sh.smax = z_levels((g.nz + G - 1) / G);
     sh.mth = batch ? NT : 512;
     sh.mthc = batch ? NT : 1024;
     // wider y workgroups when a tile holds many columns: more waves per CU
@@ -223,6 +230,10 @@ void make_domain(const pcx_grid &g, int prec, const Shapes &sh, const RadixChoic
     d.zg = sh.zg; d.zlpw = (NT / 64) * (64 / sh.zg);
     long nlines = (long)nl * ny;
     d.nzt = (int)((nlines + d.zlpw - 1) / d.zlpw);
+    d.zlev = sh.smax;
+    const int zline = prec == PREC_F64 ? 8 : 16; // 128 bytes of complex values
+    d.zs = (nz + zline - 1) / zline * zline;
+    d.dzs = mkdiv(d.zs);
     // marching stencils: TI x TJ cell tiles over chunks of ckc planes
     d.mth = sh.mth;
     // marching tiles: [0] RHS and residual with sh.mth threads, [1] the
@@ -308,6 +319,12 @@ void make_domain(const pcx_grid &g, int prec, const Shapes &sh, const RadixChoic
         return b.add(c.data(), c.size() * 4);
     };
     size_t o_dzf = addd(dzf), o_idzf = addd(idzf), o_idzc = addd(idzc), o_rzlo = addd(rzlo), o_rzhi = addd(rzhi);
+    // levels past nz of the z kernel (zg zlev >= nz): rows of their own, with
+    // a diagonal that no mode's eigenvalue (<= 0) cancels
+    const size_t nlev = (size_t)d.zg * d.zlev;
+    za.resize(nlev, 0.0L);
+    zb.resize(nlev, -1.0L);
+    zcc.resize(nlev, 0.0L);
     size_t o_za = adds(za), o_zb = adds(zb), o_zc = adds(zcc), o_dzfs = adds(dzf);
     size_t o_lx = adds(lamx), o_ly = adds(lamy);
     size_t o_twr = addr(nx, false); // first M+1 entries of the nx roots are W_nx^l
@@ -372,7 +389,7 @@ size_t lds_y(const Dom &d, int prec)
 }
 size_t lds_z(const Dom &d, int prec)
 {
-    size_t e = (size_t)d.zlpw * d.nz;
+    size_t e = (size_t)d.zlpw * d.zg * d.zlev;
     return (e + e / 16 + 1) * (prec == PREC_F64 ? 16 : 8) + 64;
 }
 
@@ -446,7 +463,7 @@ WsLayout plan_layout(const pcx_plan_s *P)
         return o;
     };
     L.s1 = put(nspec * csz);
-    L.s2 = put(nspec * csz);
+    L.s2 = put(nspec / P->grid.nz * P->dom.zs * csz);
     L.f = put(ncell * sizeof(double));
     L.r = ref ? put(ncell * sizeof(double)) : 0;
     L.stats = put(NSTAT * sizeof(unsigned long long));
@@ -456,6 +473,15 @@ WsLayout plan_layout(const pcx_plan_s *P)
     L.spart = put((size_t)sslots(P->dom) * sizeof(double));
     L.total = off;
     return L;
+}
+
+WsLayout plan_layout_within(pcx_plan_s *P, size_t most)
+{
+    WsLayout L = plan_layout(P);
+    if (L.total <= most) return L;
+    P->dom.zs = P->grid.nz;
+    P->dom.dzs = mkdiv(P->grid.nz);
+    return plan_layout(P);
 }
 
 void plan_bind(pcx_plan_s *P, const HostTables &ht, char *tables, char *ws, const WsLayout &L)
@@ -627,7 +653,7 @@ static pcx_status solve_tail(pcx_plan P, const Dom &d, int solve, int mode, hipS
 {
     HIPCHK(launch_y(d, P->prec, false, P->ly, s));
     tmark(P, s, "y_fft_fwd");
-    HIPCHK(launch_z(d, P->prec, P->sh.smax, P->lzs, s));
+    HIPCHK(launch_z(d, P->prec, P->lzs, s));
     tmark(P, s, "z_solve");
     HIPCHK(launch_y(d, P->prec, true, P->ly, s));
     tmark(P, s, "y_fft_inv");

@@ -96,15 +96,6 @@ __global__ __launch_bounds__(NTH) void k_y(Dom d)
     pass_y<T, INV, NTH>(d, blockIdx.x, smem);
 }
 
-template <typename T, int SMAX>
-__global__ __launch_bounds__(NT) void k_z(Dom d)
-{
-    extern __shared__ __align__(16) char smem[];
-    // lines in the reverse of the order the forward y pass wrote them, so the
-    // first tiles read what the device-side cache still holds
-    pass_z<T, SMAX>(d, d.nzt - 1 - (int)blockIdx.x, smem);
-}
-
 template <typename T, int MODE, int NTH>
 __global__ __launch_bounds__(NTH) void k_xinv(Dom d, int solve)
 {
@@ -204,7 +195,7 @@ hipError_t launch_resid(const Dom &d, hipStream_t s)
     PCX_LAUNCH_B(k_resid, xcd_grid(d.mg[0].ntiles), MT, 0, s, d);
 }
 
-// A fixed-plan pass of a lone domain: one workgroup per tile.
+// A fixed-plan or z pass of a lone domain: one workgroup per tile.
 static hipError_t launch_fft(const void *fn, const Dom &d, int tiles, int threads, size_t lds, hipStream_t s, int resid = 0)
 {
     if (!fn) return hipErrorInvalidValue;
@@ -286,17 +277,9 @@ hipError_t launch_y(const Dom &d, int prec, bool inv, size_t lds, hipStream_t s)
     PCX_LAUNCH((k_y<float, false, NT>), grid, lds, s, d);
 }
 
-hipError_t launch_z(const Dom &d, int prec, int smax, size_t lds, hipStream_t s)
+hipError_t launch_z(const Dom &d, int prec, size_t lds, hipStream_t s)
 {
-    const int grid = d.nzt;
-    if (prec == PREC_F64) {
-        if (smax <= 4) PCX_LAUNCH((k_z<double, 4>), grid, lds, s, d);
-        if (smax <= 8) PCX_LAUNCH((k_z<double, 8>), grid, lds, s, d);
-        PCX_LAUNCH((k_z<double, 16>), grid, lds, s, d);
-    }
-    if (smax <= 4) PCX_LAUNCH((k_z<float, 4>), grid, lds, s, d);
-    if (smax <= 8) PCX_LAUNCH((k_z<float, 8>), grid, lds, s, d);
-    PCX_LAUNCH((k_z<float, 16>), grid, lds, s, d);
+    return launch_fft(z_kernel(prec, d.zlev), d, d.nzt, NT, lds, s);
 }
 
 template <int NTH> static hipError_t launch_xinv_t(const Dom &d, int prec, int mode, int solve, size_t lds, hipStream_t s)
@@ -463,13 +446,6 @@ __global__ __launch_bounds__(NTH) void kg_y(GArgs a)
     gloop(a, [&](const Dom &d, int t) { pass_y<T, INV, NTH>(d, t, smem); });
 }
 
-template <typename T, int SMAX>
-__global__ __launch_bounds__(NT) void kg_z(GArgs a)
-{
-    extern __shared__ __align__(16) char smem[];
-    gloop(a, [&](const Dom &d, int t) { pass_z<T, SMAX>(d, t, smem); });
-}
-
 template <typename T, int MODE, int NTH>
 __global__ __launch_bounds__(NTH) void kg_xinv(GArgs a)
 {
@@ -503,8 +479,6 @@ static const void *group_fn(const GVariant &v)
         return v.nth == 512 ? (const void *)kg_xfwd<T, SRC_RESID, 512> : (const void *)kg_xfwd<T, SRC_RESID, NT>;
     case PK_YF: return v.nth == 512 ? (const void *)kg_y<T, false, 512> : (const void *)kg_y<T, false, NT>;
     case PK_YI: return v.nth == 512 ? (const void *)kg_y<T, true, 512> : (const void *)kg_y<T, true, NT>;
-    case PK_Z:
-        return v.smax <= 4 ? (const void *)kg_z<T, 4> : (v.smax <= 8 ? (const void *)kg_z<T, 8> : (const void *)kg_z<T, 16>);
     case PK_XINV_STORE:
         return v.nth == 512 ? (const void *)kg_xinv<T, XOUT_STORE, 512> : (const void *)kg_xinv<T, XOUT_STORE, NT>;
     case PK_XINV_ACCUM:
@@ -515,11 +489,12 @@ static const void *group_fn(const GVariant &v)
     return nullptr;
 }
 
-// Kernel of a fixed-plan group (v.n: the length, 1 for FSMALL and below).
+// Kernel of a fixed-plan (v.n: the length, 1 for FSMALL and below) or z group.
 static const void *group_fft_fn(const GVariant &v, int prec)
 {
     const int n = v.n == 1 ? FSMALL : v.n;
     switch (v.kind) {
+    case PK_Z: return z_kernel(prec, v.smax);
     case PK_XFWD_RHS:
     case PK_XFWD_RESID: return fft_xfwd_kernel(prec, n);
     case PK_XINV_STORE: return fft_xinv_store_kernel(prec, n);
@@ -536,7 +511,6 @@ static int group_threads(const GVariant &v)
     case PK_RHS:
     case PK_RESID: return MT;
     case PK_CORR: return MTC;
-    case PK_Z:
     case PK_XMAX: return NT;
     case PK_PMEAN: return 64;
     default: return v.nth;

@@ -17,7 +17,7 @@ bool sx_supported(const Dom &d);
 hipError_t launch_sx(const Dom &d, int prec, int src, hipStream_t s);
 hipError_t launch_smax(const Dom &d, hipStream_t s);
 hipError_t launch_y(const Dom &d, int prec, bool inv, size_t lds, hipStream_t s);
-hipError_t launch_z(const Dom &d, int prec, int smax, size_t lds, hipStream_t s);
+hipError_t launch_z(const Dom &d, int prec, size_t lds, hipStream_t s);
 hipError_t launch_xinv(const Dom &d, int prec, int mode, int solve, size_t lds, hipStream_t s);
 hipError_t launch_corr(const Dom &d, bool divcheck, hipStream_t s);
 hipError_t launch_div(const Dom &d, hipStream_t s);
@@ -50,7 +50,7 @@ struct GArgs {
 // thread; z: levels per lane).
 struct GVariant {
     int kind, nth, two, smax;
-    int n; // x and y passes with a fixed plan: the length, FSMALL and below as 1 (0: the general passes)
+    int n; // x and y passes with a fixed plan: the length, FSMALL and below as 1 (0: the general passes); z: 1
 };
 // Arguments of a fixed-plan x or y pass: a lone domain (items NULL, nitems
 // tiles) or the items of a batch; resid: the forward x pass takes r, not f.
@@ -65,6 +65,10 @@ const void *fft_xinv_store_kernel(int prec, int n);
 const void *fft_xinv_accum_kernel(int prec, int n);
 const void *fft_yfwd_kernel(int prec, int n);
 const void *fft_yinv_kernel(int prec, int n);
+// kernel of the z solve with that many levels per lane (z_levels)
+const void *z_kernel(int prec, int levels);
+// levels per lane the z kernel has, at least s (2 to 16)
+inline int z_levels(int s) { return s <= 2 ? 2 : (s <= 8 ? s : (s + 1) & ~1); }
 hipError_t launch_group(const GVariant &v, int prec, const GArgs &a, int grid, size_t lds, hipStream_t s);
 // resident workgroups per CU of a group's kernel
 hipError_t group_occupancy(const GVariant &v, int prec, size_t lds, int *blocks_per_cu);

@@ -62,7 +62,7 @@ extern "C" pcx_status pcx_noalloc_scratch_need(const pcx_grid *grid, const pcx_o
     st = plan_prepare(&P, grid, o, ht);
     if (st != PCX_OK) return st;
     const size_t tab = (ht.bytes.size() + 255) & ~(size_t)255;
-    *bytes = tab + plan_layout(&P).total;
+    *bytes = tab + plan_layout_within(&P, PCX_NOALLOC_SCRATCH_BYTES - tab).total;
     return PCX_OK;
 }
 
@@ -84,7 +84,7 @@ extern "C" pcx_status pcx_step_noalloc(const pcx_grid *grid, const pcx_options *
     st = plan_prepare(&P, grid, o, ht);
     if (st != PCX_OK) return st;
     const size_t tab = (ht.bytes.size() + 255) & ~(size_t)255;
-    const WsLayout L = plan_layout(&P);
+    const WsLayout L = plan_layout_within(&P, PCX_NOALLOC_SCRATCH_BYTES - tab);
     if (tab + L.total > (size_t)PCX_NOALLOC_SCRATCH_BYTES)
         return fail(PCX_ERR_UNSUPPORTED, "grid needs " + std::to_string(tab + L.total) +
                                              " bytes of scratch; the allocation-free step holds " +

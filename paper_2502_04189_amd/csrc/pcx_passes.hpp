@@ -813,7 +813,7 @@ __device__ __forceinline__ void pass_y(const Dom &d, int tile, char *smem)
             tk * ny,
             [&](int e) {
                 const int m = (int)fdiv((uint32_t)e, dtk), c = e - m * tk;
-                return ld_stream(s2 + ((size_t)l * ny + m) * nz + k0 + min(c, cols - 1));
+                return ld_stream(s2 + ((size_t)l * ny + m) * d.zs + k0 + min(c, cols - 1));
             },
             [&](int e, C v) {
                 const int m = (int)fdiv((uint32_t)e, dtk), c = e - m * tk;
@@ -868,7 +868,7 @@ __device__ __forceinline__ void pass_y(const Dom &d, int tile, char *smem)
             },
             [&](int e, C v) {
                 const int m = (int)fdiv((uint32_t)e, dtk), c = e - m * tk;
-                if (c < cols) st_stream(s2 + ((size_t)l * ny + m) * nz + k0 + c, v);
+                if (c < cols) st_stream(s2 + ((size_t)l * ny + m) * d.zs + k0 + c, v);
             });
     } else {
         staged_copy<NTH, 8, C>(
@@ -908,7 +908,8 @@ __device__ __forceinline__ void pass_z(const Dom &d, int tile, char *smem)
     const long q0 = (long)tile * lpg;
     const int nlin = (int)min((long)lpg, nlines_tot - q0);
     C *s2 = (C *)d.s2;
-    const size_t gbase = (size_t)q0 * nz;
+    const int zs = d.zs, LS = G * d.zlev;        // line strides in S2 and in LDS
+    const size_t gbase = (size_t)q0 * zs;
     // Each wave stages, solves and writes back its own lines through its own
     // LDS region, with no workgroup barrier: the waves of a workgroup drift
     // apart, so one wave's loads overlap another's arithmetic.
@@ -916,11 +917,19 @@ __device__ __forceinline__ void pass_z(const Dom &d, int tile, char *smem)
     const int wl0 = wv * lpw;                    // first line of this wave
     const int wlines = min(lpw, nlin - wl0);
     if (wlines <= 0) return;
-    const int wb = wl0 * nz, wn = wlines * nz;   // element range of the wave
+    const int wb = wl0 * zs, wn = wlines * zs;   // element range of the wave in S2
     // padded LDS index: one spare slot per 16 elements
 #define ZP(e) ((e) + ((e) >> 4))
+    // element e of the wave's lines -> its place in LDS (-1: beyond the line)
+    auto place = [&](int e) {
+        const int line = (int)fdiv((uint32_t)e, d.dzs), k = e - line * zs;
+        return k < nz ? ZP((wl0 + line) * LS + k) : -1;
+    };
     staged_copy_t<64, 8, C>(lane, wn, [&](int e) { return s2[gbase + wb + e]; },
-                            [&](int e, C v) { buf[ZP(wb + e)] = v; });
+                            [&](int e, C v) {
+                                const int q = place(e);
+                                if (q >= 0) buf[q] = v;
+                            });
     wave_sync();
 
     const int t = lane & (G - 1);
@@ -938,7 +947,9 @@ __device__ __forceinline__ void pass_z(const Dom &d, int tile, char *smem)
     // The solve body, FULL: every lane holds SMAX levels and no line of the
     // wave is the singular mode (all but one wave of the grid), so the
     // per-level guards and the singular-mode steps fold away at compile
-    // time; CY: 1 periodic, 2 not, 0 decided at run time.
+    // time; levels past nz (not periodic) are rows of their own, p = 0 (the
+    // coefficient tables go on with them), so any nz takes this path.
+    // CY: 1 periodic, 2 not, 0 decided at run time.
     auto solve = [&](auto full_tag, auto cy_tag) {
         constexpr bool FULL = decltype(full_tag)::value;
         constexpr int CY = decltype(cy_tag)::value;
@@ -952,8 +963,9 @@ __device__ __forceinline__ void pass_z(const Dom &d, int tile, char *smem)
 #pragma unroll
         for (int s = 0; s < SMAX; ++s) {
             if (s < S) {
-                C v = buf[ZP(gls * nz + k0 + s)];
+                C v = buf[ZP(gls * LS + k0 + s)];
                 y[s] = C{v.x * scale, v.y * scale};
+                if (FULL && CY == 2 && k0 + s >= nz) y[s] = C{T(0), T(0)};
             }
         }
         // compatibility of the singular mode: remove the dzf-weighted mean
@@ -1083,17 +1095,17 @@ __device__ __forceinline__ void pass_z(const Dom &d, int tile, char *smem)
         if (active) {
 #pragma unroll
             for (int s = 0; s < SMAX; ++s)
-                if (s < S) buf[ZP(gl * nz + k0 + s)] = y[s];
+                if (s < S) buf[ZP(gl * LS + k0 + s)] = y[s];
         }
     };
     using std::integral_constant;
-    const bool full = rem == 0 && base == SMAX && !__any(sing_line ? 1 : 0);
+    const bool full = d.zlev == SMAX && (LS == nz || d.bcz != BC_PER) && !__any(sing_line ? 1 : 0);
     if (full && d.bcz == BC_PER) solve(integral_constant<bool, true>{}, integral_constant<int, 1>{});
     else if (full) solve(integral_constant<bool, true>{}, integral_constant<int, 2>{});
     else solve(integral_constant<bool, false>{}, integral_constant<int, 0>{});
     wave_sync();
-    staged_copy_t<64, 8, C>(lane, wn, [&](int e) { return buf[ZP(wb + e)]; },
-                            [&](int e, C v) { st_stream(s2 + gbase + wb + e, v); });
+    staged_copy_t<64, 8, C>(lane, wn, [&](int e) { return buf[max(place(e), 0)]; },
+                            [&](int e, C v) { st_stream(s2 + gbase + wb + e, v); }); // past nz: any value
 #undef ZP
 }
 

@@ -133,7 +133,7 @@ pcx_status autotune_class(const pcx_grid &g, int prec, hipStream_t s, TuneParams
         if (hipMemcpy(fld[i], ones.data(), ncell * 8, hipMemcpyHostToDevice) != hipSuccess)
             return fail(PCX_ERR_HIP, "autotune scratch copy failed");
     }
-    void *s1 = sc.alloc(nspec * csz), *s2 = sc.alloc(nspec * csz);
+    void *s1 = sc.alloc(nspec * csz), *s2 = sc.alloc((nspec / g.nz) * ((g.nz + 15) & ~15) * csz);
     double *f = (double *)sc.alloc(ncell * 8);
     double *rr = (double *)sc.alloc(ncell * 8);
     unsigned long long *stats = (unsigned long long *)sc.alloc(NSTAT * 8);
@@ -155,7 +155,7 @@ pcx_status autotune_class(const pcx_grid &g, int prec, hipStream_t s, TuneParams
     if (!ddom || !ditems) return fail(PCX_ERR_NOMEM, "autotune scratch allocation failed");
     std::vector<GItem> hitems;
     // uploads d and the tile list of pass `kind`; returns false when it does not fit
-    auto prep_group = [&](const Dom &d, int kind, int smax, GVariant &v, GArgs &a, size_t &lds) {
+    auto prep_group = [&](const Dom &d, int kind, GVariant &v, GArgs &a, size_t &lds) {
         const long t = group_tiles(d, kind);
         if (t <= 0 || (size_t)t > max_items) return false;
         // A small domain's tiles leave most of the device idle, and the shape
@@ -168,7 +168,7 @@ pcx_status autotune_class(const pcx_grid &g, int prec, hipStream_t s, TuneParams
         for (long q = 0; q < t * reps; ++q) hitems[q] = GItem{0u, (uint32_t)(kind == PK_Z ? t - 1 - q % t : q % t)};
         if (hipMemcpy(ddom, &d, sizeof(Dom), hipMemcpyHostToDevice) != hipSuccess) return false;
         if (hipMemcpy(ditems, hitems.data(), t * reps * sizeof(GItem), hipMemcpyHostToDevice) != hipSuccess) return false;
-        v = variant_of(d, kind, smax);
+        v = variant_of(d, kind);
         a = GArgs{ddom, ditems, (int)(t * reps), 0};
         lds = group_lds(d, kind, prec);
         return true;
@@ -179,14 +179,14 @@ pcx_status autotune_class(const pcx_grid &g, int prec, hipStream_t s, TuneParams
         return grouped ? t / (float)std::max(1L, GFILL / n) : t;
     };
     // launches of pass kinds k1 (and k2) of d, grouped or single-domain
-    auto passes = [&](const Dom &d, int smax, size_t lx, size_t ly, size_t lz, int k1, int k2) {
+    auto passes = [&](const Dom &d, size_t lx, size_t ly, size_t lz, int k1, int k2) {
         std::vector<std::pair<GVariant, std::pair<GArgs, size_t>>> gl;
         if (grouped) {
             // two passes share the item buffer only when they have the same tiles
             for (int k : {k1, k2}) {
                 if (k < 0) continue;
                 GVariant v; GArgs a; size_t lds;
-                if (!prep_group(d, k, smax, v, a, lds)) return std::function<hipError_t()>();
+                if (!prep_group(d, k, v, a, lds)) return std::function<hipError_t()>();
                 gl.push_back({v, {a, lds}});
             }
         }
@@ -205,7 +205,7 @@ pcx_status autotune_class(const pcx_grid &g, int prec, hipStream_t s, TuneParams
                 case PK_XINV_STORE: e = launch_xinv(d, prec, XOUT_STORE, 0, lx, s); break;
                 case PK_YF: e = launch_y(d, prec, false, ly, s); break;
                 case PK_YI: e = launch_y(d, prec, true, ly, s); break;
-                case PK_Z: e = launch_z(d, prec, smax, lz, s); break;
+                case PK_Z: e = launch_z(d, prec, lz, s); break;
                 default: break;
                 }
             }
@@ -213,7 +213,7 @@ pcx_status autotune_class(const pcx_grid &g, int prec, hipStream_t s, TuneParams
         });
     };
 
-    auto make = [&](const TuneParams &tp, const RadixChoice &rc, Dom &d, DomTables &tb, size_t &lx, size_t &ly, size_t &lz, int &smax) {
+    auto make = [&](const TuneParams &tp, const RadixChoice &rc, Dom &d, DomTables &tb, size_t &lx, size_t &ly, size_t &lz) {
         Shapes sh;
         choose_shapes(g, prec, &tp, sh, false);
         pcx_status st = build_domain(g, prec, sh, &rc, tb, d);
@@ -225,7 +225,7 @@ pcx_status autotune_class(const pcx_grid &g, int prec, hipStream_t s, TuneParams
         d.xpart = xpart;
         d.ppart = prec == PREC_F32 ? ppart : nullptr;
         d.pmean = prec == PREC_F32 ? ppart + (size_t)xslots(d) : nullptr;
-        lx = lds_x(d, prec); ly = lds_y(d, prec); lz = lds_z(d, prec); smax = sh.smax;
+        lx = lds_x(d, prec); ly = lds_y(d, prec); lz = lds_z(d, prec);
         return PCX_OK;
     };
     // time fn() (best of 3 after one warm-up)
@@ -260,10 +260,10 @@ pcx_status autotune_class(const pcx_grid &g, int prec, hipStream_t s, TuneParams
                 tp.tj = tj;
                 RadixChoice rc = brc;
                 rc.x = rx;
-                Dom d; DomTables tb; size_t lx, ly, lz; int smax;
-                if (make(tp, rc, d, tb, lx, ly, lz, smax) != PCX_OK) { if (tb.dev) (void)hipFree(tb.dev); continue; }
+                Dom d; DomTables tb; size_t lx, ly, lz;
+                if (make(tp, rc, d, tb, lx, ly, lz) != PCX_OK) { if (tb.dev) (void)hipFree(tb.dev); continue; }
                 // x forward and inverse have the same tiles, so the item list is shared
-                auto fn = passes(d, smax, lx, ly, lz, PK_XFWD_RHS, PK_XINV_STORE);
+                auto fn = passes(d, lx, ly, lz, PK_XFWD_RHS, PK_XINV_STORE);
                 float t = fn ? per_pass(d, PK_XFWD_RHS, timeit(fn)) : 1e30f;
                 (void)hipFree(tb.dev);
                 if (t < bt) { bt = t; best.tj = tj; brc.x = rx; }
@@ -281,9 +281,9 @@ pcx_status autotune_class(const pcx_grid &g, int prec, hipStream_t s, TuneParams
                 tp.tk = tk;
                 RadixChoice rc = brc;
                 rc.y = ry;
-                Dom d; DomTables tb; size_t lx, ly, lz; int smax;
-                if (make(tp, rc, d, tb, lx, ly, lz, smax) != PCX_OK) { if (tb.dev) (void)hipFree(tb.dev); continue; }
-                auto fn = passes(d, smax, lx, ly, lz, PK_YF, PK_YI);
+                Dom d; DomTables tb; size_t lx, ly, lz;
+                if (make(tp, rc, d, tb, lx, ly, lz) != PCX_OK) { if (tb.dev) (void)hipFree(tb.dev); continue; }
+                auto fn = passes(d, lx, ly, lz, PK_YF, PK_YI);
                 float t = fn ? per_pass(d, PK_YF, timeit(fn)) : 1e30f;
                 (void)hipFree(tb.dev);
                 if (t < bt) { bt = t; best.tk = tk; brc.y = ry; }
@@ -297,9 +297,9 @@ pcx_status autotune_class(const pcx_grid &g, int prec, hipStream_t s, TuneParams
             if (G > std::max(1, g.nz / 2) || (g.nz + G - 1) / G > 16) continue;
             TuneParams tp = best;
             tp.zg = G;
-            Dom d; DomTables tb; size_t lx, ly, lz; int smax;
-            if (make(tp, brc, d, tb, lx, ly, lz, smax) != PCX_OK) { if (tb.dev) (void)hipFree(tb.dev); continue; }
-            auto fn = passes(d, smax, lx, ly, lz, PK_Z, -1);
+            Dom d; DomTables tb; size_t lx, ly, lz;
+            if (make(tp, brc, d, tb, lx, ly, lz) != PCX_OK) { if (tb.dev) (void)hipFree(tb.dev); continue; }
+            auto fn = passes(d, lx, ly, lz, PK_Z, -1);
             float t = fn ? per_pass(d, PK_Z, timeit(fn)) : 1e30f;
             (void)hipFree(tb.dev);
             if (t < bt) { bt = t; best.zg = G; }
