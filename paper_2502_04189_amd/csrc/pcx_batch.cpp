@@ -379,7 +379,7 @@ extern "C" pcx_status pcx_batch_create(const pcx_domain *domains, int32_t n, con
                            (size_t)(16 + 7 * NT) * sizeof(double)});
         const size_t nspec = (size_t)B->doms[i].nl * B->grids[i].ny * B->grids[i].nz;
         const size_t ncell = (size_t)B->grids[i].nx * B->grids[i].ny * B->grids[i].nz;
-        off_s1[i] = take(nspec * csz);
+        off_s1[i] = take(nspec / B->grids[i].ny * B->doms[i].ys * csz);
         off_s2[i] = take(nspec / B->grids[i].nz * B->doms[i].zs * csz);
         off_f[i] = take(ncell * 8);
         off_r[i] = B->prec == PREC_F32 ? take(ncell * 8) : 0;

@@ -9,10 +9,11 @@
 //
 // Spectral data live in two workspace layouts, chosen so that every pass
 // reads or writes long contiguous runs and does its corner turn in LDS:
-//   S1 "y-columns": ((k*NL + l)*NY + j)   one (k,l) column contiguous in j/m
+//   S1 "y-columns": ((k*NL + l)*YS + j)   one (k,l) column contiguous in j/m
 //   S2 "z-lines"  : ((l*NY + m)*ZS + k)   one (l,m) line contiguous in k
-// with NL = nx/2 + 1 half-spectrum x modes and ZS = nz rounded up to whole
-// 128-byte lines (so that the y passes' segments of k are aligned).
+// with NL = nx/2 + 1 half-spectrum x modes, and YS, ZS = ny, nz rounded up
+// to whole 128-byte lines, so that the corner turns' segments are aligned
+// (what lies between is neither written nor used).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -79,7 +80,7 @@ struct Dom {
     int tk, ntk;                      // y-pass columns per tile, k tiles
     int zg, zlpw, nzt;                // z lanes per line, lines per WG, z tiles
     int zlev;                         // levels per lane of the z kernel: zg zlev >= nz
-    int zs;                           // stride of the z-lines in S2, >= nz
+    int ys, zs;                       // strides of the columns in S1 (>= ny) and of the z-lines in S2 (>= nz)
     FastDiv dzs;
     MGeo mg[2];                       // marching tiles: [0] RHS and residual, [1] correction
     int mth, yth, xth;                // threads of the marching, y and x workgroups
@@ -113,11 +114,11 @@ constexpr int XMAX_WG = 64;
 constexpr int PMEAN_LEN = 8 + XMAX_WG;
 __host__ __device__ inline int x_tiles(const Dom &d)
 {
-    return d.xlines ? (d.ny * d.nz + d.xlines - 1) / d.xlines : d.ntj * d.nz;
+    return d.xlines ? (d.ys * d.nz + d.xlines - 1) / d.xlines : d.ntj * d.nz;
 }
 __host__ __device__ inline int y_tiles(const Dom &d)
 {
-    return d.ylines ? (int)(((long)d.nl * d.nz + d.ylines - 1) / d.ylines) : d.ntk * d.nl;
+    return d.ylines ? (int)(((long)d.nl * d.zs + d.ylines - 1) / d.ylines) : d.ntk * d.nl;
 }
 __host__ __device__ inline int xslots(const Dom &d) { return x_tiles(d) * (d.xth >> 6); }
 // partial-maximum slots of the fused stencil x passes: one per wave, one

@@ -6,10 +6,11 @@
 // instead of once more for the copy in, the copy out and every pre- and
 // post-step.
 //
-// A tile is LINES consecutive lines: rows (k, j) of the field in memory
-// order (x passes), or columns (l, k) with k fastest (y passes); tiles run
-// over plane and mode boundaries, so domains of short planes fill their
-// tiles.  Butterfly b of a stage is thread b mod the workgroup's threads.
+// A tile is LINES consecutive lines: rows (k, j) with j fastest (x passes)
+// or columns (l, k) with k fastest (y passes), counted with the padded
+// strides of S1 and S2 so that the corner turns' segments start on 128-byte
+// lines (the padding's lines are idle); tiles run over plane and mode
+// boundaries, so domains of short planes fill their tiles.  Butterfly b of a stage is thread b mod the workgroup's threads.
 #pragma once
 
 #include "pcx_fplan.hpp"
@@ -163,6 +164,18 @@ template <int M, typename C> __device__ __forceinline__ C split_root(const C *tw
     return C{-w.x, w.y};
 }
 
+// Row of an x tile: row j of plane k of line q = k ys + j; on: it exists
+// (else a row that does, to read)
+struct XLine {
+    int k, j;
+    bool on;
+};
+__device__ __forceinline__ XLine xline(const Dom &d, int q)
+{
+    const int k = q / d.ys, j = q - k * d.ys;
+    return XLine{min(k, d.nz - 1), min(j, d.ny - 1), k < d.nz && j < d.ny};
+}
+
 // ------------------------------------------------------------- x forward
 // Rows of src (f or r) -> half spectra (or cosine modes) -> S1.  M: half
 // length.  Same transforms as pass_xfwd; the split into X[l] and the cosine
@@ -179,15 +192,18 @@ template <typename T, int M> __device__ __forceinline__ void fft_xfwd(const Dom 
     tws.fetch(d.fx);
     if constexpr (SL) trs.fetch((const C *)d.twr, M / 2 + 1);
     const C *twr = SL ? ltr : (const C *)d.twr;
-    const int nx = d.nx, ny = d.ny, nrow = ny * d.nz;
-    const int q0 = tile * L;
+    const int nx = d.nx, q0 = tile * L;
     const bool wx = d.bcx != BC_PER;
+    auto row_of = [&](int line) {
+        const XLine x = xline(d, q0 + line);
+        return src + ((size_t)x.k * d.ny + x.j) * nx;
+    };
     tws.put(ltw, d.fx);
     if constexpr (SL) trs.put(ltr, (const C *)d.twr, M / 2 + 1);
     const LineFft<T, false, M, L, NTH> F{buf, ltw};
     if (!wx) {
         F.template first<false, false>([&](int line, int n) {
-            const double2 s = ((const double2 *)(src + (size_t)min(q0 + line, nrow - 1) * nx))[n];
+            const double2 s = ((const double2 *)row_of(line))[n];
             return C{(T)s.x, (T)s.y};
         });
     } else {
@@ -196,7 +212,7 @@ template <typename T, int M> __device__ __forceinline__ void fft_xfwd(const Dom 
         // sine transform) from there on
         const double odd = d.bcx == BC_DIR ? -1.0 : 1.0;
         F.template first<false, false>([&](int line, int n) {
-            const double *s = src + (size_t)min(q0 + line, nrow - 1) * nx;
+            const double *s = row_of(line);
             auto pt = [&](int m) {
                 const bool lo = m < M;
                 const double v = s[lo ? 2 * m : 2 * (nx - 1 - m) + 1];
@@ -208,7 +224,8 @@ template <typename T, int M> __device__ __forceinline__ void fft_xfwd(const Dom 
     F.middles();
     F.last();
     // X[l] = E + W^l O of the half-length spectrum, l in [0, M]
-    const int r = threadIdx.x % L, row = q0 + r;
+    const int r = threadIdx.x % L;
+    const XLine x = xline(d, q0 + r);
     const C *z = buf + r * LDC;
     auto mode = [&](int l) {
         if (l == 0 || l == M) {
@@ -220,15 +237,15 @@ template <typename T, int M> __device__ __forceinline__ void fft_xfwd(const Dom 
         const C o = {T(0.5) * (zl.y + zm.y), T(-0.5) * (zl.x - zm.x)};
         return cadd(e, cmul(split_root<M>(twr, l), o));
     };
-    const int k = row / ny, j = row - k * ny, nl = d.nl;
-    C *out = (C *)d.s1 + (size_t)k * nl * ny + j;
-    const bool on = row < nrow;
+    const int ys = d.ys;
+    C *out = (C *)d.s1 + (size_t)x.k * d.nl * ys + x.j;
+    const bool on = x.on;
     if (!wx) {
         constexpr int STEP = NTH / L, K = (M + 1 + STEP - 1) / STEP;
 #pragma unroll
         for (int t = 0; t < K; ++t) {
             const int l = threadIdx.x / L + t * STEP;
-            if (on && l <= M) st_stream(out + (size_t)l * ny, mode(l));
+            if (on && l <= M) st_stream(out + (size_t)l * ys, mode(l));
         }
     } else {
         // A_k = W_{4N}^k X_k: modes Re A_k and, N - k, -Im A_k
@@ -237,7 +254,7 @@ template <typename T, int M> __device__ __forceinline__ void fft_xfwd(const Dom 
         for (int l = threadIdx.x / L; l < nx; l += NTH / L) {
             const int kk = l <= M ? l : nx - l;
             const C a = cmul(wd[kk], mode(kk));
-            if (on) st_stream(out + (size_t)l * ny, C{l <= M ? a.x : -a.y, T(0)});
+            if (on) st_stream(out + (size_t)l * ys, C{l <= M ? a.x : -a.y, T(0)});
         }
     }
 }
@@ -257,18 +274,18 @@ template <typename T, int MODE, int M> __device__ __forceinline__ void fft_xinv(
     tws.fetch(d.fx);
     if constexpr (SL) trs.fetch((const C *)d.twr, M / 2 + 1);
     const C *twr = SL ? ltr : (const C *)d.twr;
-    const int nx = d.nx, ny = d.ny, nl = d.nl, nrow = ny * d.nz;
+    const int nx = d.nx, ys = d.ys;
     const int q0 = tile * L, r = threadIdx.x % L, l0 = threadIdx.x / L;
     const bool wx = d.bcx != BC_PER;
     {
-        const int row = min(q0 + r, nrow - 1), k = row / ny, j = row - k * ny;
-        const C *in = (const C *)d.s1 + (size_t)k * nl * ny + j;
+        const XLine x = xline(d, q0 + r);
+        const C *in = (const C *)d.s1 + (size_t)x.k * d.nl * ys + x.j;
         C *mine = buf + r * LDC;
         if (!wx) {
             constexpr int K = (M + 1 + STEP - 1) / STEP;
             C v[K];
 #pragma unroll
-            for (int t = 0; t < K; ++t) v[t] = in[(size_t)min(l0 + t * STEP, M) * ny];
+            for (int t = 0; t < K; ++t) v[t] = in[(size_t)min(l0 + t * STEP, M) * ys];
 #pragma unroll
             for (int t = 0; t < K; ++t) {
                 // X[0] and X[M] of a real row are real: entry 0 holds both
@@ -286,8 +303,8 @@ template <typename T, int MODE, int M> __device__ __forceinline__ void fft_xinv(
 #pragma unroll
             for (int t = 0; t < K; ++t) {
                 const int l = min(l0 + t * STEP, M - 1);
-                a[t] = in[(size_t)l * ny].x;
-                b[t] = in[(size_t)(l ? nx - l : M) * ny].x;
+                a[t] = in[(size_t)l * ys].x;
+                b[t] = in[(size_t)(l ? nx - l : M) * ys].x;
             }
 #pragma unroll
             for (int t = 0; t < K; ++t) {
@@ -316,20 +333,24 @@ template <typename T, int MODE, int M> __device__ __forceinline__ void fft_xinv(
     const double shift = MODE == XOUT_ACCUM ? d.pmean[0] : 0.0;
     double emax = 0.0, pmax = 0.0, psum = 0.0;
     double2 *po2 = (double2 *)d.po;
-    auto old_p = [&](int row, int h) { return po2[(size_t)min(row, nrow - 1) * M + h]; };
-    auto emit = [&](int row, int h, double2 val, double2 old) {
-        if (row >= nrow) return;
+    auto old_p = [&](int line, int h) {
+        const XLine x = xline(d, q0 + line);
+        return po2[((size_t)x.k * d.ny + x.j) * M + h];
+    };
+    auto emit = [&](int line, int h, double2 val, double2 old) {
+        const XLine x = xline(d, q0 + line);
+        if (!x.on) return;
         const double2 pv = MODE == XOUT_ACCUM ? double2{(old.x - shift) + val.x, (old.y - shift) + val.y} : val;
-        st_stream(po2 + (size_t)row * M + h, pv);
-        if (d.ppart) psum += (pv.x + pv.y) * d.dzf[row / ny];
+        st_stream(po2 + ((size_t)x.k * d.ny + x.j) * M + h, pv);
+        if (d.ppart) psum += (pv.x + pv.y) * d.dzf[x.k];
         emax = amax_nan(amax_nan(emax, val.x), val.y);
         if (MODE == XOUT_ACCUM) pmax = amax_nan(amax_nan(pmax, pv.x), pv.y);
     };
     if (!wx) {
         // accumulate: a round's old p is read ahead of its points
         double2 old[9];
-        auto wr = [&](int line, int n, C v, int r) { emit(q0 + line, n, double2{(double)v.x, (double)v.y}, old[r]); };
-        if constexpr (MODE == XOUT_ACCUM) F.last(wr, [&](int r, int line, int n) { old[r] = old_p(q0 + line, n); });
+        auto wr = [&](int line, int n, C v, int r) { emit(line, n, double2{(double)v.x, (double)v.y}, old[r]); };
+        if constexpr (MODE == XOUT_ACCUM) F.last(wr, [&](int r, int line, int n) { old[r] = old_p(line, n); });
         else F.last(wr, NoPre());
     } else {
         F.last();
@@ -341,7 +362,7 @@ template <typename T, int MODE, int M> __device__ __forceinline__ void fft_xinv(
 #pragma unroll
             for (int t = 0; t < G; ++t) {
                 const int e = min((int)threadIdx.x + (t0 + t) * NTH, L * M - 1);
-                if (MODE == XOUT_ACCUM) old[t] = old_p(q0 + e / M, e % M);
+                if (MODE == XOUT_ACCUM) old[t] = old_p(e / M, e % M);
             }
 #pragma unroll
             for (int t = 0; t < G; ++t) {
@@ -349,7 +370,7 @@ template <typename T, int MODE, int M> __device__ __forceinline__ void fft_xinv(
                 if (e >= L * M) break;
                 const T *z = (const T *)(buf + line * LDC);
                 auto real = [&](int m) { return (double)z[2 * pidx(m >> 1) + (m & 1)]; };
-                emit(q0 + line, h, double2{real(h), odd * real(nx - 1 - h)}, old[t]);
+                emit(line, h, double2{real(h), odd * real(nx - 1 - h)}, old[t]);
             }
         }
     }
@@ -365,14 +386,15 @@ template <typename T, int MODE, int M> __device__ __forceinline__ void fft_xinv(
 }
 
 // ------------------------------------------------------------- y passes
-// Column line of a y tile: mode l and plane k of line q = l nz + k
+// Column of a y tile: mode l and plane k of line q = l zs + k; on: as XLine
 struct YLine {
     int l, k;
+    bool on;
 };
 __device__ __forceinline__ YLine yline(const Dom &d, int q)
 {
-    const int l = q / d.nz;
-    return YLine{l, q - l * d.nz};
+    const int l = q / d.zs, k = q - l * d.zs;
+    return YLine{min(l, d.nl - 1), min(k, d.nz - 1), l < d.nl && k < d.nz};
 }
 
 // S1 -> FFT (cosine transform) in y -> S2
@@ -384,12 +406,12 @@ template <typename T, int N> __device__ __forceinline__ void fft_yfwd(const Dom 
     C *buf = (C *)smem, *ltw = buf + L * LDC;
     TwStage<T, NTH> tws;
     tws.fetch(d.fy);
-    const int nl = d.nl, nz = d.nz, nlin = nl * nz, q0 = tile * L;
+    const int nl = d.nl, q0 = tile * L;
     const bool wy = d.bcy != BC_PER, dy = d.bcy == BC_DIR;
     const C *s1 = (const C *)d.s1;
     auto col = [&](int line) {
-        const YLine y = yline(d, min(q0 + line, nlin - 1));
-        return s1 + ((size_t)y.k * nl + y.l) * N;
+        const YLine y = yline(d, q0 + line);
+        return s1 + ((size_t)y.k * nl + y.l) * d.ys;
     };
     tws.put(ltw, d.fy);
     const LineFft<T, false, N, L, NTH> F{buf, ltw};
@@ -417,13 +439,13 @@ template <typename T, int N> __device__ __forceinline__ void fft_yfwd(const Dom 
     }
     F.middles();
     F.last();
-    const int c = threadIdx.x % L, q = q0 + c;
-    const YLine y = yline(d, min(q, nlin - 1));
+    const int c = threadIdx.x % L;
+    const YLine y = yline(d, q0 + c);
     const int zs = d.zs;
     C *out = (C *)d.s2 + (size_t)y.l * N * zs + y.k;
     const C *z = buf + c * LDC;
     constexpr int K = (N + STEP - 1) / STEP;
-    const bool on = q < nlin;
+    const bool on = y.on;
     if (!wy) {
 #pragma unroll
         for (int t = 0; t < K; ++t) {
@@ -454,11 +476,11 @@ template <typename T, int N> __device__ __forceinline__ void fft_yinv(const Dom 
     C *buf = (C *)smem, *ltw = buf + L * LDC;
     TwStage<T, NTH> tws;
     tws.fetch(d.fy);
-    const int nl = d.nl, nz = d.nz, nlin = nl * nz, q0 = tile * L;
+    const int nl = d.nl, q0 = tile * L;
     const bool wy = d.bcy != BC_PER, dy = d.bcy == BC_DIR;
     C *s1 = (C *)d.s1;
     const int c = threadIdx.x % L;
-    const YLine y = yline(d, min(q0 + c, nlin - 1));
+    const YLine y = yline(d, q0 + c);
     const int zs = d.zs;
     const C *in = (const C *)d.s2 + (size_t)y.l * N * zs + y.k;
     tws.put(ltw, d.fy);
@@ -470,9 +492,8 @@ template <typename T, int N> __device__ __forceinline__ void fft_yinv(const Dom 
         F.middles();
         F.last(
             [&](int line, int n, C v, int) {
-                const int q = q0 + line;
-                const YLine o = yline(d, q);
-                if (q < nlin) st_stream(s1 + ((size_t)o.k * nl + o.l) * N + n, v);
+                const YLine o = yline(d, q0 + line);
+                if (o.on) st_stream(s1 + ((size_t)o.k * nl + o.l) * d.ys + n, v);
             },
             NoPre());
         return;
@@ -502,12 +523,13 @@ template <typename T, int N> __device__ __forceinline__ void fft_yinv(const Dom 
     constexpr int KO = (L * N + NTH - 1) / NTH;
 #pragma unroll 4
     for (int t = 0; t < KO; ++t) {
-        const int e = threadIdx.x + t * NTH, line = e / N, j = e - line * N, q = q0 + line;
-        if (e >= L * N || q >= nlin) break;
-        const YLine o = yline(d, q);
+        const int e = threadIdx.x + t * NTH, line = e / N, j = e - line * N;
+        if (e >= L * N) break;
+        const YLine o = yline(d, q0 + line);
+        if (!o.on) continue;
         C v = buf[line * LDC + pidx((j & 1) ? N - 1 - (j >> 1) : (j >> 1))];
         if (dy && (j & 1)) v = C{-v.x, -v.y};
-        st_stream(s1 + ((size_t)o.k * nl + o.l) * N + j, v);
+        st_stream(s1 + ((size_t)o.k * nl + o.l) * d.ys + j, v);
     }
 }
 
@@ -524,7 +546,10 @@ __device__ __forceinline__ void fft_pass(const Dom &d, const double *src, int ti
     else fft_yinv<T, N>(d, tile, smem);
 }
 
-constexpr int fft_kernel_threads(int n, int csz) { return n ? fft_threads(n, csz) : FSMALL_TH; }
+constexpr int fft_kernel_threads(int n, int csz)
+{
+    return n ? (fft_threads(n, csz) <= 1024 ? fft_threads(n, csz) : throw "more threads than a workgroup has") : FSMALL_TH;
+}
 
 // One kernel for a lone domain (the descriptor in the kernel arguments, a
 // tile per workgroup) and for a batch (an item per workgroup); both read the

@@ -75,14 +75,17 @@ __host__ __device__ constexpr int fft_points(int n, int l, int th)
 __host__ __device__ constexpr int fft_points_max(int csz) { return csz == 16 ? 9 : 16; }
 
 // Lines per tile: about 2048 FP64 or 4096 FP32 points, and at least 128
-// bytes of a corner-turned segment (64 for columns of more than 576: a tile
-// of 128-byte segments would leave room for one workgroup per CU).
+// bytes of a corner-turned segment.  Columns of 648 to 972 take 64-byte
+// segments: a tile of 128-byte ones leaves room for one workgroup per CU, and
+// only at 1024 do the whole lines outweigh that (128 x 1024 x 512 FP64, y
+// forward + inverse: 534 us with 8 lines, 646 with 4; 128 x 768 x 512 with
+// walls 508 and 433; FP32 at 1024 279 either way, with walls 306 with 8, 389 with 16).
 __host__ __device__ constexpr int fft_lines(int n, int csz)
 {
     const int pts = 32768 / csz, least = 128 / csz;
     int l = 128;
     while (l > least && (l * n > pts || (n <= FSMALL && fft_points(n, l, FSMALL_TH) > fft_points_max(csz)))) l >>= 1;
-    if (l * n * csz > 72 * 1024) l >>= 1;
+    if (l * n * csz > 72 * 1024 && (n < 1024 || csz == 8)) l >>= 1;
     return l;
 }
 // Fewest threads (a multiple of 64) that keep within fft_points_max.

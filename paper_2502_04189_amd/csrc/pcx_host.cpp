@@ -232,6 +232,7 @@ void make_domain(const pcx_grid &g, int prec, const Shapes &sh, const RadixChoic
     d.nzt = (int)((nlines + d.zlpw - 1) / d.zlpw);
     d.zlev = sh.smax;
     const int zline = prec == PREC_F64 ? 8 : 16; // 128 bytes of complex values
+    d.ys = (ny + zline - 1) / zline * zline;
     d.zs = (nz + zline - 1) / zline * zline;
     d.dzs = mkdiv(d.zs);
     // marching stencils: TI x TJ cell tiles over chunks of ckc planes
@@ -462,7 +463,7 @@ WsLayout plan_layout(const pcx_plan_s *P)
         off = (off + bytes + 255) & ~(size_t)255;
         return o;
     };
-    L.s1 = put(nspec * csz);
+    L.s1 = put(nspec / P->grid.ny * P->dom.ys * csz);
     L.s2 = put(nspec / P->grid.nz * P->dom.zs * csz);
     L.f = put(ncell * sizeof(double));
     L.r = ref ? put(ncell * sizeof(double)) : 0;
@@ -479,6 +480,7 @@ WsLayout plan_layout_within(pcx_plan_s *P, size_t most)
 {
     WsLayout L = plan_layout(P);
     if (L.total <= most) return L;
+    P->dom.ys = P->grid.ny;
     P->dom.zs = P->grid.nz;
     P->dom.dzs = mkdiv(P->grid.nz);
     return plan_layout(P);

@@ -766,7 +766,7 @@ __device__ __forceinline__ void pass_xfwd(const Dom &d, int tile, char *smem)
         [&](int e, C v) {
             int l = (int)fdiv((uint32_t)e, d.dtj);
             int r = e - l * tj;
-            if (r < rows) st_stream(s1 + ((size_t)k * nl + l) * d.ny + j0 + r, v);
+            if (r < rows) st_stream(s1 + ((size_t)k * nl + l) * d.ys + j0 + r, v);
         });
 }
 
@@ -802,7 +802,7 @@ __device__ __forceinline__ void pass_y(const Dom &d, int tile, char *smem)
             cols * ny,
             [&](int e) {
                 const int c = (int)fdiv((uint32_t)e, d.dnyc), j = e - c * ny;
-                return ld_stream(s1 + ((size_t)(k0 + c) * nl + l) * ny + j);
+                return ld_stream(s1 + ((size_t)(k0 + c) * nl + l) * d.ys + j);
             },
             [&](int e, C v) {
                 const int c = (int)fdiv((uint32_t)e, d.dnyc), j = e - c * ny;
@@ -879,7 +879,7 @@ __device__ __forceinline__ void pass_y(const Dom &d, int tile, char *smem)
             },
             [&](int e, C v) {
                 const int c = (int)fdiv((uint32_t)e, d.dnyc), j = e - c * ny;
-                st_stream(s1 + ((size_t)(k0 + c) * nl + l) * ny + j, v);
+                st_stream(s1 + ((size_t)(k0 + c) * nl + l) * d.ys + j, v);
             });
     }
 }
@@ -1137,7 +1137,7 @@ __device__ __forceinline__ void pass_xinv(const Dom &d, int tile, char *smem, in
         [&](int e) {
             int l = (int)fdiv((uint32_t)e, d.dtj);
             int r = e - l * tj;
-            return s1[((size_t)k * nl + l) * d.ny + j0 + min(r, rows - 1)];
+            return s1[((size_t)k * nl + l) * d.ys + j0 + min(r, rows - 1)];
         },
         [&](int e, C v) {
             int l = (int)fdiv((uint32_t)e, d.dtj);

@@ -80,8 +80,8 @@ namespace pcx {
 pcx_status plan_options(const pcx_options *opts, pcx_options &o);
 pcx_status plan_prepare(pcx_plan_s *P, const pcx_grid *grid, const pcx_options &o, HostTables &ht);
 WsLayout plan_layout(const pcx_plan_s *P);
-// The layout with z-lines rounded up to whole 128-byte lines, or without the
-// rounding where it alone would take the plan beyond `most` bytes.
+// The layout with columns and z-lines rounded up to whole 128-byte lines, or
+// without the rounding where it alone would take the plan beyond `most` bytes.
 WsLayout plan_layout_within(pcx_plan_s *P, size_t most);
 void plan_bind(pcx_plan_s *P, const HostTables &ht, char *tables, char *ws, const WsLayout &L);
 } // namespace pcx

@@ -133,7 +133,7 @@ pcx_status autotune_class(const pcx_grid &g, int prec, hipStream_t s, TuneParams
         if (hipMemcpy(fld[i], ones.data(), ncell * 8, hipMemcpyHostToDevice) != hipSuccess)
             return fail(PCX_ERR_HIP, "autotune scratch copy failed");
     }
-    void *s1 = sc.alloc(nspec * csz), *s2 = sc.alloc((nspec / g.nz) * ((g.nz + 15) & ~15) * csz);
+    void *s1 = sc.alloc((nspec / g.ny) * ((g.ny + 15) & ~15) * csz), *s2 = sc.alloc((nspec / g.nz) * ((g.nz + 15) & ~15) * csz);
     double *f = (double *)sc.alloc(ncell * 8);
     double *rr = (double *)sc.alloc(ncell * 8);
     unsigned long long *stats = (unsigned long long *)sc.alloc(NSTAT * 8);
