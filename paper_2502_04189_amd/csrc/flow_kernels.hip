@@ -236,27 +236,34 @@ __device__ __forceinline__ void mom_put(const FArgs &A, const FTile &t, size_t c
     if (qs) put(qs + c, wallf(A.G, C, s) ? 0.0 : qv + A.Dt * (A.ga * m + A.ze * old));
     put(hc + c, m);
 }
-template <int C>
-__device__ __forceinline__ void mom_store(const FArgs &A, const FTile &t, size_t c, double m, double *hc,
-                                          const double *qc, double *qs)
-{
-    const double old = qs && !A.first ? hc[c] : 0.0;
-    mom_put<C>(A, t, c, m, old, qs ? qc[c] : 0.0, hc, qs);
-}
-
 static_assert(SLX == FTI + 2 && SLY == FTJ + 2, "stage shape follows the tile shape");
+
+// Cell s of direction d of a stage, one outside the tile at most: wrapped
+// across a periodic direction, the adjacent cell across a wall (and, past
+// the end of a partial tile, any valid cell).
+__device__ __forceinline__ int stage_idx(const FGrid &G, int d, int s)
+{
+    const int n = G.n[d];
+    const int t = G.per[d] ? (s < 0 ? s + n : (s >= n ? s - n : s)) : s;
+    return t < 0 ? 0 : (t < n ? t : n - 1);
+}
 
 // Copies u, v, w and phi over the tile of (i0, j0, k) and its one-cell halo
 // into the stage: every load of a thread is issued before its first LDS
-// store.  Interior tiles only: a halo index leaves the grid only across a
-// periodic direction, where it wraps (by one period: the tile plan has no
+// store.  FAST: interior tiles, where a halo index leaves the grid only
+// across a periodic direction and wraps by one period (the tile plan has no
 // interior box when a periodic direction is shorter than the tile and halo).
-__device__ __forceinline__ void stage_fields(const FArgs &A, int i0, int j0, int k, double *st)
+// Otherwise the stage takes the values the wall rules give (face components
+// 0 on and beyond their own walls, minus the adjacent value across another),
+// so the stencils read it as they read an interior tile's.
+template <bool FAST> __device__ __forceinline__ void stage_fields(const FArgs &A, int i0, int j0, int k, double *st)
 {
     constexpr int NR = (SFLD + FT - 1) / FT;
-    const int nx = A.G.n[0], ny = A.G.n[1], nz = A.G.n[2];
+    const FGrid &G = A.G;
+    const int nx = G.n[0], ny = G.n[1], nz = G.n[2];
     const double *src[SNF] = {A.u, A.v, A.w, A.phi};
     size_t g[NR];
+    double sg[3][FAST ? 1 : NR];
 #pragma unroll
     for (int q = 0; q < NR; ++q) {
         int e = threadIdx.x + q * FT;
@@ -264,9 +271,27 @@ __device__ __forceinline__ void stage_fields(const FArgs &A, int i0, int j0, int
         const int kk = e / SPL, r = e - kk * SPL;
         const int jj = r / SLX, ii = r - jj * SLX;
         int gi = i0 - 1 + ii, gj = j0 - 1 + jj, gk = k - 1 + kk;
-        gi = gi < 0 ? gi + nx : (gi >= nx ? gi - nx : gi);
-        gj = gj < 0 ? gj + ny : (gj >= ny ? gj - ny : gj);
-        gk = gk < 0 ? gk + nz : (gk >= nz ? gk - nz : gk);
+        if constexpr (FAST) {
+            gi = gi < 0 ? gi + nx : (gi >= nx ? gi - nx : gi);
+            gj = gj < 0 ? gj + ny : (gj >= ny ? gj - ny : gj);
+            gk = gk < 0 ? gk + nz : (gk >= nz ? gk - nz : gk);
+        } else {
+            const int o[3] = {gi, gj, gk};
+            bool out[3], own[3]; // outside a wall direction; on or beyond the walls of the direction's own faces
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                out[d] = !G.per[d] && (o[d] < 0 || o[d] >= G.n[d]);
+                own[d] = !G.per[d] && (o[d] < 0 || o[d] >= G.n[d] - 1);
+            }
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const bool neg = out[(c + 1) % 3] != out[(c + 2) % 3];
+                sg[c][q] = own[c] ? 0.0 : (neg ? -1.0 : 1.0);
+            }
+            gi = stage_idx(G, 0, gi);
+            gj = stage_idx(G, 1, gj);
+            gk = stage_idx(G, 2, gk);
+        }
         g[q] = ((size_t)gk * ny + gj) * nx + gi;
     }
     double v[SNF][NR];
@@ -279,17 +304,49 @@ __device__ __forceinline__ void stage_fields(const FArgs &A, int i0, int j0, int
 #pragma unroll
         for (int q = 0; q < NR; ++q) {
             const int e = threadIdx.x + q * FT;
+            if constexpr (!FAST) {
+                if (f < 3) v[f][q] = sg[f][q] == 0.0 ? 0.0 : sg[f][q] * v[f][q];
+            }
             if (e < SFLD) st[f * SFLD + e] = v[f][q];
+        }
+}
+
+// The register stage of a tile along the walls: a_x, a_y, a_z (0 beyond
+// their own walls; on them the flux kernel stored 0) and kappa (the adjacent
+// value across a wall) over the thread's 3 x 3 x 3 neighbourhood.
+__device__ __forceinline__ void stage_regs_wall(const FArgs &A, const FTile &t, double (&rg)[SNR][27])
+{
+    const FGrid &G = A.G;
+    const int c[3] = {t.i, t.j, t.k};
+    int ix[3][3];
+    bool low[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        low[d] = !G.per[d] && c[d] == 0;
+#pragma unroll
+        for (int o = 0; o < 3; ++o) ix[d][o] = stage_idx(G, d, c[d] + o - 1);
+    }
+    const double *const src[SNR] = {A.a[0], A.a[1], A.a[2], A.kap};
+#pragma unroll
+    for (int q = 0; q < SNR; ++q)
+#pragma unroll
+        for (int n = 0; n < 27; ++n) {
+            const int o[3] = {n % 3, (n / 3) % 3, n / 9};
+            const double v = src[q][at(G, ix[0][o[0]], ix[1][o[1]], ix[2][o[2]])];
+            rg[q][n] = q < 3 && o[q < 3 ? q : 0] == 0 && low[q < 3 ? q : 0] ? 0.0 : v;
         }
 }
 
 // Momentum right-hand side of the three components (all loads before any
 // store); with u*, the substep's predictor; with p*, the extrapolated
-// pressure.  Interior tiles read u, v, w and phi (about two thirds of the
-// stencil's neighbour values) from a stage in LDS that the workgroup fills
-// with one round of loads: read from memory one by one, in the rounds the
-// compiler's schedule allowed, they left the kernel waiting on memory
-// latency.  (One kernel per component took 13 % longer in all.)  With PH
+// pressure.  Tiles read u, v, w and phi (about two thirds of the stencil's
+// neighbour values) from a stage in LDS that the workgroup fills with one
+// round of loads: read from memory one by one, in the rounds the compiler's
+// schedule allowed, they left the kernel waiting on memory latency.  The
+// tiles along the walls run the same code on a stage that holds what the
+// wall rules give (144 x 54 x 50 in a closed box: 85 us with the rules
+// applied at every access, 26 with the stage).  (One kernel per component
+// took 13 % longer in all.)  With PH
 // the kernel also takes the phase field's right-hand side and update (the
 // substep), whose stencil reads only values the momentum stages already
 // hold: a separate phase pass read phi, u, v, w and a again.
@@ -297,66 +354,50 @@ template <bool FAST, bool PH> __device__ __forceinline__ void momentum_body(cons
 {
     const BoxPick p = box_pick<FAST>(L);
     const FTile t = btile(A.G, p.b, p.w);
-    double m0 = 0.0, m1 = 0.0, m2 = 0.0;
     unsigned long long key = ~0ull;
-    if constexpr (FAST) {
-        // hu, hv, hw (and hphi) are read and written in place: each thread
-        // reads and writes only its own cell
-        __shared__ double st[SNF * SFLD];
-        if (t.valid) { // uniform over the workgroup
-            const int tx = threadIdx.x % FTI, ty = threadIdx.x / FTI;
-            stage_fields(A, t.i - tx, t.j - ty, t.k, st);
-            // register stage: issued with the LDS stage's loads, before the
-            // barrier (threads past the grid read their clamped cell)
-            double rg[SNR][27];
+    // hu, hv, hw (and hphi) are read and written in place: each thread
+    // reads and writes only its own cell
+    __shared__ double st[SNF * SFLD];
+    if (t.valid) { // uniform over the workgroup
+        const int tx = threadIdx.x % FTI, ty = threadIdx.x / FTI;
+        stage_fields<FAST>(A, t.i - tx, t.j - ty, t.k, st);
+        // register stage: issued with the LDS stage's loads, before the
+        // barrier (threads past the grid read their clamped cell)
+        double rg[SNR][27];
+        if constexpr (FAST) {
             const double *const rsrc[SNR] = {A.a[0], A.a[1], A.a[2], A.kap};
             stage_regs<SNR>(A.G, t, rsrc, rg);
-            // the cell's previous right-hand sides and pressures, loaded with
-            // the stages
-            const size_t cc = at(A.G, t.act ? t.i : A.G.n[0] - 1, t.act ? t.j : A.G.n[1] - 1, t.k);
-            double old[3] = {0.0, 0.0, 0.0}, pp1 = 0.0, pp2 = 0.0, oldp = 0.0;
-            if (!A.first) {
-                if (A.us[0]) old[0] = own(A.hu + cc);
-                if (A.us[1]) old[1] = own(A.hv + cc);
-                if (A.us[2]) old[2] = own(A.hw + cc);
-                if (PH) oldp = own(A.hphi + cc);
-            }
-            if (A.pstar) {
-                pp1 = own(A.p1 + cc);
-                pp2 = own(A.p2 + cc);
-            }
-            __syncthreads();
-            if (t.act) {
-                const StageAcc<SNF> x(A.G, t.i, t.j, t.k, st, SPL + (ty + 1) * SLX + tx + 1, rg);
-                const SVel vel;
-                const SVec<4> av;
-                m0 = mom_rhs<0>(A, x, t, vel, SField<3>{}, SField<7>{}, av);
-                m1 = mom_rhs<1>(A, x, t, vel, SField<3>{}, SField<7>{}, av);
-                m2 = mom_rhs<2>(A, x, t, vel, SField<3>{}, SField<7>{}, av);
-                mom_put<0>(A, t, cc, m0, old[0], x.cv(SField<0>{}, 0, 0, 0), A.hu, A.us[0]);
-                mom_put<1>(A, t, cc, m1, old[1], x.cv(SField<1>{}, 0, 0, 0), A.hv, A.us[1]);
-                mom_put<2>(A, t, cc, m2, old[2], x.cv(SField<2>{}, 0, 0, 0), A.hw, A.us[2]);
-                if (A.pstar) put(A.pstar + cc, (1.0 + A.r) * pp1 - A.r * pp2);
-                if constexpr (PH)
-                    phase_put(A, cc, acdi_cell(x, SField<3>{}, vel, av), x.cv(SField<3>{}, 0, 0, 0), oldp, key);
-            }
+        } else {
+            stage_regs_wall(A, t, rg);
         }
-    } else if (t.act) {
-        const PVel vel{A.u, A.v, A.w};
-        const PVec av{A.a[0], A.a[1], A.a[2]};
-        double r = 0.0;
-        with_acc<false>(A.G, t, [&](const auto &x) {
-            m0 = mom_rhs<0>(A, x, t, vel, A.phi, A.kap, av);
-            m1 = mom_rhs<1>(A, x, t, vel, A.phi, A.kap, av);
-            m2 = mom_rhs<2>(A, x, t, vel, A.phi, A.kap, av);
-            if constexpr (PH) r = acdi_cell(x, A.phi, vel, av);
-        });
-        const size_t c = at(A.G, t.i, t.j, t.k);
-        mom_store<0>(A, t, c, m0, A.hu, A.u, A.us[0]);
-        mom_store<1>(A, t, c, m1, A.hv, A.v, A.us[1]);
-        mom_store<2>(A, t, c, m2, A.hw, A.w, A.us[2]);
-        if (A.pstar) put(A.pstar + c, (1.0 + A.r) * A.p1[c] - A.r * A.p2[c]);
-        if constexpr (PH) phase_put(A, c, r, A.phi[c], A.first ? 0.0 : own(A.hphi + c), key);
+        // the cell's previous right-hand sides and pressures, loaded with
+        // the stages
+        const size_t cc = at(A.G, t.act ? t.i : A.G.n[0] - 1, t.act ? t.j : A.G.n[1] - 1, t.k);
+        double old[3] = {0.0, 0.0, 0.0}, pp1 = 0.0, pp2 = 0.0, oldp = 0.0;
+        if (!A.first) {
+            if (A.us[0]) old[0] = own(A.hu + cc);
+            if (A.us[1]) old[1] = own(A.hv + cc);
+            if (A.us[2]) old[2] = own(A.hw + cc);
+            if (PH) oldp = own(A.hphi + cc);
+        }
+        if (A.pstar) {
+            pp1 = own(A.p1 + cc);
+            pp2 = own(A.p2 + cc);
+        }
+        __syncthreads();
+        if (t.act) {
+            const StageAcc<SNF> x(A.G, t.i, t.j, t.k, st, SPL + (ty + 1) * SLX + tx + 1, rg);
+            const SVel vel;
+            const SVec<4> av;
+            const double m0 = mom_rhs<0>(A, x, t, vel, SField<3>{}, SField<7>{}, av);
+            const double m1 = mom_rhs<1>(A, x, t, vel, SField<3>{}, SField<7>{}, av);
+            const double m2 = mom_rhs<2>(A, x, t, vel, SField<3>{}, SField<7>{}, av);
+            mom_put<0>(A, t, cc, m0, old[0], x.cv(SField<0>{}, 0, 0, 0), A.hu, A.us[0]);
+            mom_put<1>(A, t, cc, m1, old[1], x.cv(SField<1>{}, 0, 0, 0), A.hv, A.us[1]);
+            mom_put<2>(A, t, cc, m2, old[2], x.cv(SField<2>{}, 0, 0, 0), A.hw, A.us[2]);
+            if (A.pstar) put(A.pstar + cc, (1.0 + A.r) * pp1 - A.r * pp2);
+            if constexpr (PH) phase_put(A, cc, acdi_cell(x, SField<3>{}, vel, av), x.cv(SField<3>{}, 0, 0, 0), oldp, key);
+        }
     }
     if constexpr (PH) key_to_slot(key, A.rho_part + p.slot);
 }
