@@ -1,9 +1,7 @@
 // flow_kernels.hip -- kernels of the Runge-Kutta substep around the pressure
 // correction: normals, regularization flux and curvature, phase-field
 // update, momentum predictor.  One thread per cell on the plane tiles of
-// flow_tile.hpp: each stencil kernel is instantiated with the interior
-// accessor (FAST) for the interior box and with the general one for the
-// boxes along the walls.
+// flow_tile.hpp, interior tiles on code without wall rules.
 #include "flow_launch.hpp"
 #include "flow_tile.hpp"
 
@@ -29,11 +27,11 @@ __global__ __launch_bounds__(FT) void k_flow_psi(FArgs A)
 // evaluates its own)
 __global__ __launch_bounds__(FT) void k_flow_normals(BoxList L, FArgs A)
 {
-    const BoxPick p = box_pick<false>(L);
+    const BoxPick p = box_pick(L);
     const FTile t = btile(A.G, p.b, p.w);
     if (!t.act) return;
     double nx, ny, nz;
-    with_acc<false>(A.G, t, [&](const auto &x) { normal_cell(x, A.psi, nx, ny, nz); });
+    normal_cell(Gen{A.G, t.i, t.j, t.k}, A.psi, nx, ny, nz);
     const size_t c = at(A.G, t.i, t.j, t.k);
     put(A.n[0] + c, nx);
     put(A.n[1] + c, ny);
@@ -45,10 +43,11 @@ __global__ __launch_bounds__(FT) void k_flow_normals(BoxList L, FArgs A)
 // evaluated here from psi (the cells up to two steps along one axis or one
 // step along two) instead of being stored by a normals pass and read back:
 // 6 GiB less HBM traffic per substep at 512^3.  The box's cells next to a
-// wall box store their own normal, which the wall tiles read.
+// wall box store their own normal, which the wall tiles read: those follow
+// in a launch of their own.
 template <bool FAST> __global__ __launch_bounds__(FT) void k_flow_flux(BoxList L, FArgs A)
 {
-    const BoxPick p = box_pick<FAST>(L);
+    const BoxPick p = box_pick(L);
     const TileBox &b = p.b;
     const FTile t = btile(A.G, b, p.w);
     if (!t.act) return;
@@ -122,12 +121,11 @@ template <bool FAST> __global__ __launch_bounds__(FT) void k_flow_flux(BoxList L
         }
     } else {
         const PVec n{A.n[0], A.n[1], A.n[2]};
-        with_acc<false>(A.G, t, [&](const auto &x) {
-            put(A.a[0] + c, flux_face<0>(x, A.P, A.phi, A.psi, A.n[0]));
-            put(A.a[1] + c, flux_face<1>(x, A.P, A.phi, A.psi, A.n[1]));
-            put(A.a[2] + c, flux_face<2>(x, A.P, A.phi, A.psi, A.n[2]));
-            put(A.kap + c, curvature_cell(x, n));
-        });
+        const Gen x{A.G, t.i, t.j, t.k};
+        put(A.a[0] + c, flux_face<0>(x, A.P, A.phi, A.psi, A.n[0]));
+        put(A.a[1] + c, flux_face<1>(x, A.P, A.phi, A.psi, A.n[1]));
+        put(A.a[2] + c, flux_face<2>(x, A.P, A.phi, A.psi, A.n[2]));
+        put(A.kap + c, curvature_cell(x, n));
     }
 }
 
@@ -174,13 +172,13 @@ __device__ __forceinline__ void key_to_slot(unsigned long long key, unsigned lon
 
 // Phase-field right-hand side only (the phase right-hand side entry point;
 // the substep's update runs in the momentum pass)
-template <bool FAST> __global__ __launch_bounds__(FT) void k_flow_phase(BoxList L, FArgs A)
+__global__ __launch_bounds__(FT) void k_flow_phase(BoxList L, FArgs A)
 {
-    const BoxPick p = box_pick<FAST>(L);
+    const BoxPick p = box_pick(L);
     const FTile t = btile(A.G, p.b, p.w);
     if (!t.act) return;
     double r = 0.0;
-    if constexpr (FAST) {
+    if (p.fast) {
         // phi, u, v, w, a_x, a_y, a_z from registers, loaded up front
         double rg[7][27];
         const double *const src[7] = {A.phi, A.u, A.v, A.w, A.a[0], A.a[1], A.a[2]};
@@ -189,7 +187,7 @@ template <bool FAST> __global__ __launch_bounds__(FT) void k_flow_phase(BoxList 
     } else {
         const PVel vel{A.u, A.v, A.w};
         const PVec av{A.a[0], A.a[1], A.a[2]};
-        with_acc<false>(A.G, t, [&](const auto &x) { r = acdi_cell(x, A.phi, vel, av); });
+        r = acdi_cell(Gen{A.G, t.i, t.j, t.k}, A.phi, vel, av);
     }
     put(A.hphi + at(A.G, t.i, t.j, t.k), r);
 }
@@ -350,24 +348,25 @@ __device__ __forceinline__ void stage_regs_wall(const FArgs &A, const FTile &t, 
 // the kernel also takes the phase field's right-hand side and update (the
 // substep), whose stencil reads only values the momentum stages already
 // hold: a separate phase pass read phi, u, v, w and a again.
-template <bool FAST, bool PH> __device__ __forceinline__ void momentum_body(const BoxList &L, const FArgs &A)
+template <bool PH> __device__ __forceinline__ void momentum_body(const BoxList &L, const FArgs &A)
 {
-    const BoxPick p = box_pick<FAST>(L);
+    __shared__ double st[SNF * SFLD];
+    const BoxPick p = box_pick(L);
     const FTile t = btile(A.G, p.b, p.w);
     unsigned long long key = ~0ull;
     // hu, hv, hw (and hphi) are read and written in place: each thread
     // reads and writes only its own cell
-    __shared__ double st[SNF * SFLD];
-    if (t.valid) { // uniform over the workgroup
+    if (t.valid) { // uniform over the workgroup, as p.fast
         const int tx = threadIdx.x % FTI, ty = threadIdx.x / FTI;
-        stage_fields<FAST>(A, t.i - tx, t.j - ty, t.k, st);
         // register stage: issued with the LDS stage's loads, before the
         // barrier (threads past the grid read their clamped cell)
         double rg[SNR][27];
-        if constexpr (FAST) {
+        if (p.fast) {
+            stage_fields<true>(A, t.i - tx, t.j - ty, t.k, st);
             const double *const rsrc[SNR] = {A.a[0], A.a[1], A.a[2], A.kap};
             stage_regs<SNR>(A.G, t, rsrc, rg);
         } else {
+            stage_fields<false>(A, t.i - tx, t.j - ty, t.k, st);
             stage_regs_wall(A, t, rg);
         }
         // the cell's previous right-hand sides and pressures, loaded with
@@ -402,15 +401,9 @@ template <bool FAST, bool PH> __device__ __forceinline__ void momentum_body(cons
     if constexpr (PH) key_to_slot(key, A.rho_part + p.slot);
 }
 
-template <bool FAST> __global__ __launch_bounds__(FT) void k_flow_momentum(BoxList L, FArgs A)
-{
-    momentum_body<FAST, false>(L, A);
-}
+__global__ __launch_bounds__(FT) void k_flow_momentum(BoxList L, FArgs A) { momentum_body<false>(L, A); }
 // the substep's momentum predictor with the phase update
-template <bool FAST> __global__ __launch_bounds__(FT) void k_flow_mom_phase(BoxList L, FArgs A)
-{
-    momentum_body<FAST, true>(L, A);
-}
+__global__ __launch_bounds__(FT) void k_flow_mom_phase(BoxList L, FArgs A) { momentum_body<true>(L, A); }
 
 __global__ void k_flow_key_reset(unsigned long long *k) { *k = ~0ull; }
 
@@ -425,14 +418,19 @@ hipError_t launch_normals(const FArgs &A, const TilePlan &tp, hipStream_t s)
     if (e != hipSuccess) return e;
     // the tiles along the walls only: the interior box's flux kernel
     // evaluates its normals itself
-    const BoxList out = box_list(tp, false);
+    const BoxList out = box_list(tp, false, true);
     if (out.n) hipLaunchKernelGGL(k_flow_normals, dim3(out.grid), dim3(FT), 0, s, out, A);
     return hipGetLastError();
 }
 hipError_t launch_flux(const FArgs &A, const TilePlan &tp, hipStream_t s)
 {
     if (tp.zlow < 2) return hipErrorInvalidValue;
-    return FLOW_LAUNCH_PLAN(tp, k_flow_flux, s, A);
+    const BoxList in = box_list(tp, true, false), out = box_list(tp, false, true);
+    if (in.n) hipLaunchKernelGGL(k_flow_flux<true>, dim3(in.grid), dim3(FT), 0, s, in, A);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (out.n) hipLaunchKernelGGL(k_flow_flux<false>, dim3(out.grid), dim3(FT), 0, s, out, A);
+    return hipGetLastError();
 }
 hipError_t launch_phase(const FArgs &A, const TilePlan &tp, hipStream_t s)
 {

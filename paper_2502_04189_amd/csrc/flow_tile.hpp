@@ -3,14 +3,11 @@
 // workgroups of 64 x 4 cells of one plane.
 //
 // The tiles of a grid are split into boxes (ranges of x tiles, y tiles and
-// planes): one interior box whose stencils reach no wall, run by a kernel
-// instantiated with the branch-free interior accessor only, and up to six
-// boxes around it, run by the same kernel instantiated with the general
-// accessor.  Kept apart, the interior kernel gets the register budget of its
-// own short code (the general accessor's wall cases raised the register
-// count and cut occupancy for every tile).  Within a launch consecutive
-// workgroups go to different XCDs, so XCD x gets a contiguous range of the
-// box's tiles in the order below.
+// planes): one interior box whose stencils reach no wall, and up to six
+// boxes around it.  A kernel takes all of them in one launch and branches,
+// uniformly over the workgroup, to code on the interior accessor or on the
+// wall rules.  Within a launch consecutive workgroups go to different XCDs,
+// so XCD x gets a contiguous range of a box's tiles in the order below.
 #pragma once
 
 #include <vector>
@@ -148,22 +145,24 @@ __host__ __device__ inline void box_tile(const TileBox &b, long t, int &it, int 
 // The boxes of one launch: workgroup first[q] + w is workgroup w of box q
 // and owns partial-result slot slot0[q] + w (every box's workgroups are a
 // multiple of 8, so w & 7 is the workgroup's XCD as well).
-constexpr int MAXBOX = 6;
+constexpr int MAXBOX = 7;
 struct BoxList {
     int n, grid;
+    int fast; // box 0 is the interior box
     TileBox box[MAXBOX];
     int slot0[MAXBOX], first[MAXBOX];
 };
 
-// The interior box (fast) or the boxes along the walls of a plan, as one
+// The interior box and / or the boxes along the walls of a plan, as one
 // launch: run one after another, the wall boxes of a small grid each took
 // the time of one workgroup (45-60 us for the momentum at 144 x 54 x 50) and
 // left the device idle.
-inline BoxList box_list(const TilePlan &p, bool fast)
+inline BoxList box_list(const TilePlan &p, bool interior, bool walls)
 {
     BoxList L{};
-    for (int b = 0; b < p.n; ++b) {
-        if (p.fast[b] != fast) continue;
+    for (int b = 0; b < p.n; ++b) { // the interior box, if any, is the plan's first
+        if (!(p.fast[b] ? interior : walls)) continue;
+        if (p.fast[b]) L.fast = 1;
         L.box[L.n] = p.box[b];
         L.slot0[L.n] = p.slot0[b];
         L.first[L.n] = L.grid;
@@ -178,16 +177,15 @@ struct BoxPick {
     TileBox b;
     unsigned w;
     int slot;
+    bool fast;
 };
-template <bool FAST> __device__ __forceinline__ BoxPick box_pick(const BoxList &L)
+__device__ __forceinline__ BoxPick box_pick(const BoxList &L)
 {
-    BoxPick p{L.box[0], blockIdx.x, L.slot0[0] + (int)blockIdx.x};
-    if constexpr (!FAST) { // the interior is one box
+    BoxPick p{L.box[0], blockIdx.x, L.slot0[0] + (int)blockIdx.x, L.fast != 0};
 #pragma unroll
-        for (int q = 1; q < MAXBOX; ++q)
-            if (q < L.n && (int)blockIdx.x >= L.first[q])
-                p = BoxPick{L.box[q], blockIdx.x - L.first[q], L.slot0[q] + (int)blockIdx.x - L.first[q]};
-    }
+    for (int q = 1; q < MAXBOX; ++q)
+        if (q < L.n && (int)blockIdx.x >= L.first[q])
+            p = BoxPick{L.box[q], blockIdx.x - L.first[q], L.slot0[q] + (int)blockIdx.x - L.first[q], false};
     return p;
 }
 
@@ -210,14 +208,6 @@ __device__ __forceinline__ FTile btile(const FGrid &G, const TileBox &b, unsigne
     return c;
 }
 
-// runs body(accessor): the interior accessor in the FAST instantiation, the
-// general one otherwise
-template <bool FAST, class Body> __device__ __forceinline__ void with_acc(const FGrid &G, const FTile &t, Body body)
-{
-    if constexpr (FAST) body(Fast(G, t.i, t.j, t.k));
-    else body(Gen{G, t.i, t.j, t.k});
-}
-
 // register stage of the listed fields: each thread's 3 x 3 x 3 neighbourhood
 // (loads whose values no stencil reads are removed by the compiler), all
 // issued before the first use; threads past the grid read a clamped cell
@@ -232,15 +222,11 @@ __device__ __forceinline__ void stage_regs(const FGrid &G, const FTile &t, const
         for (int n = 0; n < 27; ++n) rg[q][n] = src[q][f.idx(n % 3 - 1, (n / 3) % 3 - 1, n / 9 - 1)];
 }
 
-// Launches kernel<true> on the interior box and kernel<false> on the others
-// together; every kernel takes (box list, args...).
+// Launches a kernel, which takes (box list, args...), on every box of a plan.
 #define FLOW_LAUNCH_PLAN(TP, KERNEL, STREAM, ...)                                                          \
     ([&]() -> hipError_t {                                                                                \
-        const BoxList in_ = box_list((TP), true), out_ = box_list((TP), false);                           \
-        if (in_.n) hipLaunchKernelGGL(KERNEL<true>, dim3(in_.grid), dim3(FT), 0, (STREAM), in_, __VA_ARGS__); \
-        hipError_t e_ = hipGetLastError();                                                                \
-        if (e_ != hipSuccess) return e_;                                                                  \
-        if (out_.n) hipLaunchKernelGGL(KERNEL<false>, dim3(out_.grid), dim3(FT), 0, (STREAM), out_, __VA_ARGS__); \
+        const BoxList l_ = box_list((TP), true, true);                                                    \
+        hipLaunchKernelGGL(KERNEL, dim3(l_.grid), dim3(FT), 0, (STREAM), l_, __VA_ARGS__);                \
         return hipGetLastError();                                                                         \
     }())
 

@@ -3,7 +3,7 @@
 // (the preconditioner is the constant-coefficient solve of the plan, run by
 // the host between these kernels).  Stencil and vector kernels run one
 // thread per cell on the plane tiles of flow_tile.hpp (the stencils with the
-// interior accessor on the interior box, the general one elsewhere); the inner
+// interior accessor on interior tiles, the general one elsewhere); the inner
 // products are volume-weighted (the dzf factor; dx dy is common to all cells
 // and cancels in every ratio the iteration takes) and are reduced in a fixed
 // order, so a run is deterministic.  The iteration's scalars stay in device
@@ -78,23 +78,22 @@ __device__ __forceinline__ double div_cell(const X &x, const double *u, const do
 }
 
 // out = sign D((1/rho_f) G p); with R, partial sums of dzf p out
-template <bool FAST>
 __global__ __launch_bounds__(FT) void k_vc_apply(BoxList L, FGrid G, const double *rho, const double *p, double *out,
                                                  double sign, VRed R, int want)
 {
-    const BoxPick pk = box_pick<FAST>(L);
+    const BoxPick pk = box_pick(L);
     const FTile t = btile(G, pk.b, pk.w);
     double a = 0.0;
     if (t.act) {
         double q = 0.0;
-        if constexpr (FAST) {
+        if (pk.fast) {
             // rho and p from registers, loaded up front
             double rg[2][27];
             const double *const src[2] = {rho, p};
             stage_regs<2>(G, t, src, rg);
             q = sign * vdiv_cell(StageAcc<0>(G, t.i, t.j, t.k, nullptr, 0, rg), SField<0>{}, SField<1>{});
         } else {
-            with_acc<false>(G, t, [&](const auto &x) { q = sign * vdiv_cell(x, rho, p); });
+            q = sign * vdiv_cell(Gen{G, t.i, t.j, t.k}, rho, p);
         }
         const size_t c = at(G, t.i, t.j, t.k);
         out[c] = q;
@@ -104,16 +103,16 @@ __global__ __launch_bounds__(FT) void k_vc_apply(BoxList L, FGrid G, const doubl
 }
 
 // r = -(D u) / dt; partial sum of dzf r
-template <bool FAST>
 __global__ __launch_bounds__(FT) void k_vc_rhs(BoxList L, FGrid G, const double *u, const double *v, const double *w,
                                                double idt, double *r, VRed R)
 {
-    const BoxPick pk = box_pick<FAST>(L);
+    const BoxPick pk = box_pick(L);
     const FTile t = btile(G, pk.b, pk.w);
     double a = 0.0;
     if (t.act) {
         double q = 0.0;
-        with_acc<FAST>(G, t, [&](const auto &x) { q = -div_cell(x, u, v, w) * idt; });
+        if (pk.fast) q = -div_cell(Fast(G, t.i, t.j, t.k), u, v, w) * idt;
+        else q = -div_cell(Gen{G, t.i, t.j, t.k}, u, v, w) * idt;
         r[at(G, t.i, t.j, t.k)] = q;
         a = G.dzf[t.k] * q;
     }
@@ -219,21 +218,22 @@ __global__ __launch_bounds__(FT) void k_vc_pshift(FGrid G, double *p, VRed R)
 }
 
 // u_out = u - dt (1/rho_f) G p on the +face of each direction, 0 on a wall face
-template <bool FAST>
 __global__ __launch_bounds__(FT) void k_vc_correct(BoxList L, FGrid G, const double *rho, const double *p, const double *u,
                                                    const double *v, const double *w, double dt, double *uo,
                                                    double *vo, double *wo)
 {
-    const BoxPick pk = box_pick<FAST>(L);
+    const BoxPick pk = box_pick(L);
     const FTile t = btile(G, pk.b, pk.w);
     if (!t.act) return;
     const size_t c = at(G, t.i, t.j, t.k);
     double gx = 0.0, gy = 0.0, gz = 0.0;
-    with_acc<FAST>(G, t, [&](const auto &x) {
+    auto flux = [&](const auto &x) {
         gx = bflux<0>(x, rho, p, 0);
         gy = bflux<1>(x, rho, p, 0);
         gz = bflux<2>(x, rho, p, 0);
-    });
+    };
+    if (pk.fast) flux(Fast(G, t.i, t.j, t.k));
+    else flux(Gen{G, t.i, t.j, t.k});
     uo[c] = wallf(G, 0, t.i) ? 0.0 : u[c] - dt * gx;
     vo[c] = wallf(G, 1, t.j) ? 0.0 : v[c] - dt * gy;
     wo[c] = wallf(G, 2, t.k) ? 0.0 : w[c] - dt * gz;
