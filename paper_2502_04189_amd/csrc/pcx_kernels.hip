@@ -196,6 +196,17 @@ hipError_t launch_resid(const Dom &d, hipStream_t s)
 }
 
 // A fixed-plan or z pass of a lone domain: one workgroup per tile.
+// The fixed-plan and z kernels are compiled in files of their own.  The
+// references are weak, so the host code (this file, plans, batches, tuner)
+// also links and runs without them; a launch is then refused.
+extern __attribute__((weak)) const void *fft_xfwd_kernel(int prec, int n);
+extern __attribute__((weak)) const void *fft_xinv_store_kernel(int prec, int n);
+extern __attribute__((weak)) const void *fft_xinv_accum_kernel(int prec, int n);
+extern __attribute__((weak)) const void *fft_yfwd_kernel(int prec, int n);
+extern __attribute__((weak)) const void *fft_yinv_kernel(int prec, int n);
+extern __attribute__((weak)) const void *z_kernel(int prec, int levels);
+static const void *kernel_of(const void *(*table)(int, int), int prec, int n) { return table ? table(prec, n) : nullptr; }
+
 static hipError_t launch_fft(const void *fn, const Dom &d, int tiles, int threads, size_t lds, hipStream_t s, int resid = 0)
 {
     if (!fn) return hipErrorInvalidValue;
@@ -219,7 +230,7 @@ template <int NTH> static hipError_t launch_xfwd_t(const Dom &d, int prec, int s
 
 hipError_t launch_xfwd(const Dom &d, int prec, int src, size_t lds, hipStream_t s)
 {
-    if (d.xlines) return launch_fft(fft_xfwd_kernel(prec, d.M), d, x_tiles(d), d.xth, lds, s, src == SRC_RESID);
+    if (d.xlines) return launch_fft(kernel_of(fft_xfwd_kernel, prec, d.M), d, x_tiles(d), d.xth, lds, s, src == SRC_RESID);
     return d.xth == 512 ? launch_xfwd_t<512>(d, prec, src, lds, s) : launch_xfwd_t<NT>(d, prec, src, lds, s);
 }
 
@@ -259,7 +270,7 @@ hipError_t launch_smax(const Dom &d, hipStream_t s)
 hipError_t launch_y(const Dom &d, int prec, bool inv, size_t lds, hipStream_t s)
 {
     if (d.ylines)
-        return launch_fft(inv ? fft_yinv_kernel(prec, d.ny) : fft_yfwd_kernel(prec, d.ny), d, y_tiles(d), d.yth, lds, s);
+        return launch_fft(inv ? kernel_of(fft_yinv_kernel, prec, d.ny) : kernel_of(fft_yfwd_kernel, prec, d.ny), d, y_tiles(d), d.yth, lds, s);
     const int grid = d.ntk * d.nl;
     if (d.yth == 512) {
         if (prec == PREC_F64) {
@@ -279,7 +290,7 @@ hipError_t launch_y(const Dom &d, int prec, bool inv, size_t lds, hipStream_t s)
 
 hipError_t launch_z(const Dom &d, int prec, size_t lds, hipStream_t s)
 {
-    return launch_fft(z_kernel(prec, d.zlev), d, d.nzt, NT, lds, s);
+    return launch_fft(kernel_of(z_kernel, prec, d.zlev), d, d.nzt, NT, lds, s);
 }
 
 template <int NTH> static hipError_t launch_xinv_t(const Dom &d, int prec, int mode, int solve, size_t lds, hipStream_t s)
@@ -296,7 +307,7 @@ template <int NTH> static hipError_t launch_xinv_t(const Dom &d, int prec, int m
 hipError_t launch_xinv(const Dom &d, int prec, int mode, int solve, size_t lds, hipStream_t s)
 {
     if (d.xlines)
-        return launch_fft(mode == XOUT_STORE ? fft_xinv_store_kernel(prec, d.M) : fft_xinv_accum_kernel(prec, d.M), d,
+        return launch_fft(mode == XOUT_STORE ? kernel_of(fft_xinv_store_kernel, prec, d.M) : kernel_of(fft_xinv_accum_kernel, prec, d.M), d,
                           x_tiles(d), d.xth, lds, s);
     return d.xth == 512 ? launch_xinv_t<512>(d, prec, mode, solve, lds, s)
                         : launch_xinv_t<NT>(d, prec, mode, solve, lds, s);
@@ -494,13 +505,13 @@ static const void *group_fft_fn(const GVariant &v, int prec)
 {
     const int n = v.n == 1 ? FSMALL : v.n;
     switch (v.kind) {
-    case PK_Z: return z_kernel(prec, v.smax);
+    case PK_Z: return kernel_of(z_kernel, prec, v.smax);
     case PK_XFWD_RHS:
-    case PK_XFWD_RESID: return fft_xfwd_kernel(prec, n);
-    case PK_XINV_STORE: return fft_xinv_store_kernel(prec, n);
-    case PK_XINV_ACCUM: return fft_xinv_accum_kernel(prec, n);
-    case PK_YF: return fft_yfwd_kernel(prec, n);
-    case PK_YI: return fft_yinv_kernel(prec, n);
+    case PK_XFWD_RESID: return kernel_of(fft_xfwd_kernel, prec, n);
+    case PK_XINV_STORE: return kernel_of(fft_xinv_store_kernel, prec, n);
+    case PK_XINV_ACCUM: return kernel_of(fft_xinv_accum_kernel, prec, n);
+    case PK_YF: return kernel_of(fft_yfwd_kernel, prec, n);
+    case PK_YI: return kernel_of(fft_yinv_kernel, prec, n);
     }
     return nullptr;
 }
