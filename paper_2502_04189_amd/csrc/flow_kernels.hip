@@ -2,6 +2,8 @@
 // correction: normals, regularization flux and curvature, phase-field
 // update, momentum predictor.  One thread per cell on the plane tiles of
 // flow_tile.hpp, interior tiles on code without wall rules.
+#include <algorithm>
+
 #include "flow_launch.hpp"
 #include "flow_tile.hpp"
 
@@ -38,94 +40,196 @@ __global__ __launch_bounds__(FT) void k_flow_normals(BoxList L, FArgs A)
     put(A.n[2] + c, nz);
 }
 
-// Regularization flux and curvature.  On the interior box (planes from 2 on
-// with walls in z) the normals of the cell and its six neighbours are
-// evaluated here from psi (the cells up to two steps along one axis or one
-// step along two) instead of being stored by a normals pass and read back:
-// 6 GiB less HBM traffic per substep at 512^3.  The box's cells next to a
-// wall box store their own normal, which the wall tiles read: those follow
-// in a launch of their own.
-template <bool FAST> __global__ __launch_bounds__(FT) void k_flow_flux(BoxList L, FArgs A)
+// Regularization flux and curvature on the tiles along the walls, from the
+// stored normals (their own tiles' by k_flow_normals, an interior
+// neighbour's by k_flow_flux_in)
+__global__ __launch_bounds__(FT) void k_flow_flux_wall(BoxList L, FArgs A)
 {
     const BoxPick p = box_pick(L);
-    const TileBox &b = p.b;
-    const FTile t = btile(A.G, b, p.w);
+    const FTile t = btile(A.G, p.b, p.w);
     if (!t.act) return;
     const size_t c = at(A.G, t.i, t.j, t.k);
-    if constexpr (FAST) {
-        const FGrid &G = A.G;
-        const int nx = G.n[0], ny = G.n[1], nz = G.n[2];
-        const size_t sz = (size_t)nx * ny;
-        // offsets of the cells -2 .. 2 steps along each axis (wrapped once
-        // across a periodic direction; a wall is at least two cells away)
-        size_t ox[5], oy[5], oz[5];
-        int kw[5];
+    const PVec n{A.n[0], A.n[1], A.n[2]};
+    const Gen x{A.G, t.i, t.j, t.k};
+    put(A.a[0] + c, flux_face<0>(x, A.P, A.phi, A.psi, A.n[0]));
+    put(A.a[1] + c, flux_face<1>(x, A.P, A.phi, A.psi, A.n[1]));
+    put(A.a[2] + c, flux_face<2>(x, A.P, A.phi, A.psi, A.n[2]));
+    put(A.kap + c, curvature_cell(x, n));
+}
+
+// The flux and curvature on the interior box (planes from 2 on with walls in
+// z), marching in z: a workgroup takes MFI x MFJ columns over a chunk of
+// planes, keeps four planes of psi and three of phi in LDS (tile and halo)
+// and evaluates each normal once, one plane ahead of the flux that uses it:
+// n of the own cell stays in registers, its x and y components go through
+// LDS for the in-plane neighbours, and the cells just outside the tile (144
+// of them for 512 threads) are evaluated by the first waves.  Evaluating the
+// seven normals a cell reads at every cell took 481 VALU instructions per
+// cell and 3.1 ms at 512^3; here 1.61 ms, of which the six fields it moves
+// take 1.24 ms at copy rate.  One barrier per plane: a plane of LDS is
+// written no earlier than a barrier after its last read.
+constexpr int MFI = 64, MFJ = 8, MFT = MFI * MFJ;
+constexpr int PSX = MFI + 4, PSY = MFJ + 4, PSN = PSX * PSY; // psi plane: two cells of halo
+constexpr int PHX = MFI + 1, PHY = MFJ + 1, PHN = PHX * PHY; // phi plane: one cell up in x and y
+constexpr int NXX = MFI + 2, NXN = NXX * MFJ;                // n_x: one cell of halo in x
+constexpr int NYN = MFI * (MFJ + 2);                         // n_y: one in y
+constexpr int MFR = 2 * (MFI + MFJ);                         // halo cells whose normal is evaluated
+static_assert(PSN <= 2 * MFT && PHN <= 2 * MFT && MFR <= MFT, "two items per thread");
+
+// uniform entry of a table no kernel writes, by a scalar load
+__device__ __forceinline__ double utab(const double *p, int k)
+{
+    return ((const __attribute__((address_space(4))) double *)p)[__builtin_amdgcn_readfirstlane(k)];
+}
+
+__global__ __launch_bounds__(MFT) void k_flow_flux_in(TileBox b, int ckc, FArgs A)
+{
+    __shared__ double sps[4][PSN], sph[3][PHN], snx[2][NXN], sny[2][NYN];
+    const FGrid &G = A.G;
+    const int nx = G.n[0], ny = G.n[1], nz = G.n[2];
+    const size_t sz = (size_t)nx * ny;
+    // tile of this workgroup, an XCD's workgroups a contiguous range
+    const int i1 = min((b.it0 + b.nit) * FTI, nx), j1 = min((b.jt0 + b.njt) * FTJ, ny);
+    const int ntj = (j1 - b.jt0 * FTJ + MFJ - 1) / MFJ, nch = (b.nk + ckc - 1) / ckc;
+    const int ntile = b.nit * ntj * nch, per = (ntile + 7) >> 3;
+    const int tile = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per || tile >= ntile) return;
+    const int ch = tile / (b.nit * ntj), rem = tile - ch * (b.nit * ntj), jt = rem / b.nit;
+    const int i0 = (b.it0 + rem - jt * b.nit) * FTI, j0 = b.jt0 * FTJ + jt * MFJ;
+    const int kb = b.k0 + ch * ckc, ke = min(b.k0 + b.nk, kb + ckc);
+    const int tid = threadIdx.x, tx = tid & (MFI - 1), ty = tid / MFI;
+    const int i = i0 + tx, j = j0 + ty;
+    const bool act = i < i1 && j < j1;
+    // in-plane offset of cell (i0 + a, j0 + c): wrapped once across a
+    // periodic direction; past a partial tile any valid cell
+    auto off = [&](int a, int c) {
+        int x = i0 + a, y = j0 + c;
+        x = x < 0 ? x + nx : (x >= nx ? x - nx : x);
+        y = y < 0 ? y + ny : (y >= ny ? y - ny : y);
+        return (size_t)min(max(y, 0), ny - 1) * nx + min(max(x, 0), nx - 1);
+    };
+    auto wrapk = [&](int k) { return k < 0 ? k + nz : (k >= nz ? k - nz : k); };
+    // the thread's items of a psi and of a phi plane
+    const int q1 = min(tid + MFT, PSN - 1), r1 = min(tid + MFT, PHN - 1);
+    const size_t o0 = off(tid % PSX - 2, tid / PSX - 2), o1 = off(q1 % PSX - 2, q1 / PSX - 2);
+    const int r0 = min(tid, PHN - 1);
+    const size_t h0 = off(r0 % PHX, r0 / PHX), h1 = off(r1 % PHX, r1 / PHX);
+    const double hx = 0.5 * G.ih[0], hy = 0.5 * G.ih[1];
+    const int me = (ty + 2) * PSX + tx + 2; // own cell in a psi plane
+    // the halo cell whose normal this thread evaluates: rows j0 - 1 and j0 +
+    // MFJ (its y component), then columns i0 - 1 and i0 + MFI (its x component)
+    const bool ring = tid < MFR, ry = tid < 2 * MFI;
+    const int rq = tid - 2 * MFI;
+    const int rj = ry ? (tid < MFI ? -1 : MFJ) : (rq & (MFJ - 1)), ri = ry ? tx : (rq < MFJ ? -1 : MFI);
+    const int rme = ring ? (rj + 2) * PSX + ri + 2 : me;
+    const int rdst = ry ? (rj + 1) * MFI + ri : rj * NXX + ri + 1;
+    // normal at place c of the plane k (psi planes k - 1, k, k + 1 in LDS)
+    auto normal = [&](int c, int k, double iz, double &ux, double &uy, double &uz) {
+        const double *p = sps[k & 3];
+        unit_normal((p[c + 1] - p[c - 1]) * hx, (p[c + PSX] - p[c - PSX]) * hy,
+                    (sps[(k + 1) & 3][c] - sps[(k - 1) & 3][c]) * iz, ux, uy, uz);
+    };
+    auto halo_normal = [&](int k, double iz) {
+        if (!ring) return;
+        double ux, uy, uz;
+        normal(rme, k, iz, ux, uy, uz);
+        if (ry) sny[k & 1][rdst] = uy;
+        else snx[k & 1][rdst] = ux;
+    };
+    auto iz2 = [&](int k) { return utab(G.rz, 6 * wrapk(k) + 4); };
+    // prologue: psi of planes kb - 2 .. kb + 1, phi of kb
+    {
+        double p[4][2];
 #pragma unroll
-        for (int d = 0; d < 5; ++d) {
-            int v = t.i + d - 2;
-            ox[d] = (size_t)(v < 0 ? v + nx : (v >= nx ? v - nx : v));
-            v = t.j + d - 2;
-            oy[d] = (size_t)(v < 0 ? v + ny : (v >= ny ? v - ny : v)) * nx;
-            v = t.k + d - 2;
-            kw[d] = v < 0 ? v + nz : (v >= nz ? v - nz : v);
-            oz[d] = (size_t)kw[d] * sz;
+        for (int q = 0; q < 4; ++q) {
+            const double *s = A.psi + (size_t)wrapk(kb - 2 + q) * sz;
+            p[q][0] = s[o0];
+            p[q][1] = s[o1];
         }
-        // psi [c][b][a] at offset (a, b, c) - 2 and phi over the 3 x 3 x 3
-        // neighbourhood, all loaded up front (loads no stencil reads are
-        // removed by the compiler)
-        double ps[5][5][5];
+        const double *f = A.phi + (size_t)wrapk(kb) * sz;
+        const double f0 = f[h0], f1 = f[h1];
 #pragma unroll
-        for (int cc = 0; cc < 5; ++cc)
-#pragma unroll
-            for (int bb = 0; bb < 5; ++bb)
-#pragma unroll
-                for (int aa = 0; aa < 5; ++aa) ps[cc][bb][aa] = A.psi[oz[cc] + oy[bb] + ox[aa]];
-        double rg[5][27];
-#pragma unroll
-        for (int n = 0; n < 27; ++n) {
-            const int aa = n % 3 + 1, bb = (n / 3) % 3 + 1, cc = n / 9 + 1;
-            rg[0][n] = A.phi[oz[cc] + oy[bb] + ox[aa]];
-            rg[1][n] = ps[cc][bb][aa];
-            rg[2][n] = rg[3][n] = rg[4][n] = 0.0;
+        for (int q = 0; q < 4; ++q) {
+            sps[(kb - 2 + q) & 3][tid] = p[q][0];
+            if (tid + MFT < PSN) sps[(kb - 2 + q) & 3][tid + MFT] = p[q][1];
         }
-        // the normal at offset (a, b, c) as the normals pass computes it
-        const double hx = 0.5 * G.ih[0], hy = 0.5 * G.ih[1];
-        auto normal_at = [&](int a, int bo, int co) {
-            const double iz = G.rz[6 * (size_t)kw[co + 2] + 4];
-            const double gx = (ps[co + 2][bo + 2][a + 3] - ps[co + 2][bo + 2][a + 1]) * hx;
-            const double gy = (ps[co + 2][bo + 3][a + 2] - ps[co + 2][bo + 1][a + 2]) * hy;
-            const double gz = (ps[co + 3][bo + 2][a + 2] - ps[co + 1][bo + 2][a + 2]) * iz;
-            const int n = 9 * (co + 1) + 3 * (bo + 1) + a + 1;
-            unit_normal(gx, gy, gz, rg[2][n], rg[3][n], rg[4][n]);
+        sph[kb % 3][r0] = f0;
+        if (tid + MFT < PHN) sph[kb % 3][tid + MFT] = f1;
+    }
+    __syncthreads();
+    double nxc, nyc, nzc, nzm, t0, t1;
+    normal(me, kb - 1, iz2(kb - 1), t0, t1, nzm);
+    normal(me, kb, iz2(kb), nxc, nyc, nzc);
+    halo_normal(kb, iz2(kb));
+    snx[kb & 1][ty * NXX + tx + 1] = nxc;
+    sny[kb & 1][(ty + 1) * MFI + tx] = nyc;
+    // width of planes and the z face below plane kb
+    const double dzm = utab(G.dzf, wrapk(kb - 1));
+    double dz0 = utab(G.dzf, kb);
+    double nfb = (nzm * dz0 + nzc * dzm) * (0.5 * utab(G.rz, 6 * kb + 2));
+    __syncthreads(); // plane kb - 2 was read above, its place takes kb + 2
+    // planes in flight: psi of k + 2, phi of k + 1
+    const double *sp = A.psi + (size_t)wrapk(kb + 2) * sz, *sf = A.phi + (size_t)wrapk(kb + 1) * sz;
+    double p0 = sp[o0], p1 = sp[o1], f0 = sf[h0], f1 = sf[h1];
+    int phs = kb % 3; // phi plane of k
+    for (int k = kb; k < ke; ++k) {
+        const int phn = phs == 2 ? 0 : phs + 1;
+        sps[(k + 2) & 3][tid] = p0;
+        if (tid + MFT < PSN) sps[(k + 2) & 3][tid + MFT] = p1;
+        sph[phn][r0] = f0;
+        if (tid + MFT < PHN) sph[phn][tid + MFT] = f1;
+        // the next planes (the last ones of the chunk are read, not used)
+        sp = A.psi + (size_t)wrapk(min(k + 3, ke + 1)) * sz;
+        sf = A.phi + (size_t)wrapk(min(k + 2, ke)) * sz;
+        p0 = sp[o0];
+        p1 = sp[o1];
+        f0 = sf[h0];
+        f1 = sf[h1];
+        __syncthreads();
+        double nxp, nyp, nzp;
+        normal(me, k + 1, iz2(k + 1), nxp, nyp, nzp);
+        halo_normal(k + 1, iz2(k + 1));
+        snx[(k + 1) & 1][ty * NXX + tx + 1] = nxp;
+        sny[(k + 1) & 1][(ty + 1) * MFI + tx] = nyp;
+        const double dzp = utab(G.dzf, wrapk(k + 1)), izc = utab(G.rz, 6 * k + 3), izf = utab(G.rz, 6 * k);
+        const double *ps = sps[k & 3] + me;
+        const double *ph = sph[phs] + ty * PHX + tx;
+        const double *px = snx[k & 1] + ty * NXX + tx + 1, *py = sny[k & 1] + (ty + 1) * MFI + tx;
+        const double nfe = 0.5 * (nxc + px[1]), nfw = 0.5 * (px[-1] + nxc);
+        const double nfn = 0.5 * (nyc + py[MFI]), nfs = 0.5 * (py[-MFI] + nyc);
+        const double nft = (nzc * dzp + nzp * dz0) * (0.5 * izc);
+        const double P0 = ps[0], F0 = ph[0];
+        auto flux = [&](double psf, double gphi, double nf) {
+            // (1 - tanh^2 z) / 4 as in flux_face
+            const double y = exp(-2.0 * fabs(psf * A.P.ihe));
+            const double w = y / ((1.0 + y) * (1.0 + y));
+            return A.P.gamma * (A.P.eps * gphi - w * nf);
         };
-        normal_at(0, 0, 0);
-        normal_at(-1, 0, 0);
-        normal_at(1, 0, 0);
-        normal_at(0, -1, 0);
-        normal_at(0, 1, 0);
-        normal_at(0, 0, -1);
-        normal_at(0, 0, 1);
-        const StageAcc<0> x(G, t.i, t.j, t.k, nullptr, 0, rg);
-        const SVec<2> n;
-        put(A.a[0] + c, flux_face<0>(x, A.P, SField<0>{}, SField<1>{}, SField<2>{}));
-        put(A.a[1] + c, flux_face<1>(x, A.P, SField<0>{}, SField<1>{}, SField<3>{}));
-        put(A.a[2] + c, flux_face<2>(x, A.P, SField<0>{}, SField<1>{}, SField<4>{}));
-        put(A.kap + c, curvature_cell(x, n));
-        const bool edge = (!G.per[0] && (t.i == b.it0 * FTI || t.i == (b.it0 + b.nit) * FTI - 1)) ||
-                          (!G.per[1] && (t.j == b.jt0 * FTJ || t.j == (b.jt0 + b.njt) * FTJ - 1)) ||
-                          (!G.per[2] && (t.k == b.k0 || t.k == b.k0 + b.nk - 1));
-        if (edge) {
-            put(A.n[0] + c, rg[2][13]);
-            put(A.n[1] + c, rg[3][13]);
-            put(A.n[2] + c, rg[4][13]);
+        const double ax = flux(0.5 * (P0 + ps[1]), (ph[1] - F0) * G.ih[0], nfe);
+        const double ay = flux(0.5 * (P0 + ps[PSX]), (ph[PHX] - F0) * G.ih[1], nfn);
+        const double az = flux((P0 * dzp + sps[(k + 1) & 3][me] * dz0) * (0.5 * izc),
+                               (sph[phn][ty * PHX + tx] - F0) * izc, nft);
+        const double kap = -((nfe - nfw) * G.ih[0] + (nfn - nfs) * G.ih[1] + (nft - nfb) * izf);
+        if (act) {
+            const size_t c = (size_t)k * sz + (size_t)j * nx + i;
+            put(A.a[0] + c, ax);
+            put(A.a[1] + c, ay);
+            put(A.a[2] + c, az);
+            put(A.kap + c, kap);
+            // the box's cells next to a wall box: their normal is read there
+            if ((!G.per[0] && (i == b.it0 * FTI || i == i1 - 1)) || (!G.per[1] && (j == b.jt0 * FTJ || j == j1 - 1)) ||
+                (!G.per[2] && (k == b.k0 || k == b.k0 + b.nk - 1))) {
+                put(A.n[0] + c, nxc);
+                put(A.n[1] + c, nyc);
+                put(A.n[2] + c, nzc);
+            }
         }
-    } else {
-        const PVec n{A.n[0], A.n[1], A.n[2]};
-        const Gen x{A.G, t.i, t.j, t.k};
-        put(A.a[0] + c, flux_face<0>(x, A.P, A.phi, A.psi, A.n[0]));
-        put(A.a[1] + c, flux_face<1>(x, A.P, A.phi, A.psi, A.n[1]));
-        put(A.a[2] + c, flux_face<2>(x, A.P, A.phi, A.psi, A.n[2]));
-        put(A.kap + c, curvature_cell(x, n));
+        nxc = nxp;
+        nyc = nyp;
+        nzc = nzp;
+        nfb = nft;
+        dz0 = dzp;
+        phs = phn;
     }
 }
 
@@ -422,14 +526,36 @@ hipError_t launch_normals(const FArgs &A, const TilePlan &tp, hipStream_t s)
     if (out.n) hipLaunchKernelGGL(k_flow_normals, dim3(out.grid), dim3(FT), 0, s, out, A);
     return hipGetLastError();
 }
+// Planes per chunk of the marching flux (txy tiles per plane, two workgroups
+// per CU): rounds of workgroups times the planes each takes, four of them to
+// start, is least.
+static int flux_chunk(int nk, int txy)
+{
+    int best = nk;
+    long cost = -1;
+    for (int n = 1; n <= nk; ++n) {
+        const int c = (nk + n - 1) / n;
+        const long wgs = (long)txy * ((nk + c - 1) / c), t = (wgs + 511) / 512 * (c + 4);
+        if (cost < 0 || t < cost) { cost = t; best = c; }
+    }
+    return best;
+}
 hipError_t launch_flux(const FArgs &A, const TilePlan &tp, hipStream_t s)
 {
     if (tp.zlow < 2) return hipErrorInvalidValue;
-    const BoxList in = box_list(tp, true, false), out = box_list(tp, false, true);
-    if (in.n) hipLaunchKernelGGL(k_flow_flux<true>, dim3(in.grid), dim3(FT), 0, s, in, A);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (out.n) hipLaunchKernelGGL(k_flow_flux<false>, dim3(out.grid), dim3(FT), 0, s, out, A);
+    const BoxList out = box_list(tp, false, true);
+    for (int q = 0; q < tp.n; ++q) {
+        if (!tp.fast[q]) continue;
+        const TileBox &b = tp.box[q];
+        const int j0 = b.jt0 * FTJ, j1 = std::min((b.jt0 + b.njt) * FTJ, A.G.n[1]);
+        const int txy = b.nit * ((j1 - j0 + MFJ - 1) / MFJ);
+        const int ckc = flux_chunk(b.nk, txy);
+        const int tiles = txy * ((b.nk + ckc - 1) / ckc);
+        hipLaunchKernelGGL(k_flow_flux_in, dim3((tiles + 7) / 8 * 8), dim3(MFT), 0, s, b, ckc, A);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    if (out.n) hipLaunchKernelGGL(k_flow_flux_wall, dim3(out.grid), dim3(FT), 0, s, out, A);
     return hipGetLastError();
 }
 hipError_t launch_phase(const FArgs &A, const TilePlan &tp, hipStream_t s)
