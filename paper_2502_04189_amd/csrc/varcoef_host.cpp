@@ -23,10 +23,12 @@ struct pcx_varcoef_s {
     pcx_plan plan = nullptr;
     double *tab = nullptr; // z metric tables (metric_tables)
     double *ws = nullptr;  // r, z, d, q
-    double *red = nullptr; // partials, first level, scalars
+    double *red = nullptr; // partials (operator, update, dot), scalars
+    double *hres = nullptr, *dres = nullptr; // the residual in host memory, host and device address
     size_t ncell = 0;
     double *r, *z, *d, *q;
-    VRed R;
+    ATiles T;
+    VRed RA, R, RD;
 };
 
 static void vc_free(pcx_varcoef V)
@@ -36,6 +38,7 @@ static void vc_free(pcx_varcoef V)
     if (V->tab) (void)hipFree(V->tab);
     if (V->ws) (void)hipFree(V->ws);
     if (V->red) (void)hipFree(V->red);
+    if (V->hres) (void)hipHostFree(V->hres);
     delete V;
 }
 
@@ -80,16 +83,13 @@ extern "C" pcx_status pcx_varcoef_create(const pcx_grid *grid, const pcx_options
     G.ih[1] = 1.0 / G.h[1];
     V->ncell = (size_t)nx * ny * nz;
     V->tp = flow::tile_plan(G);
-    const int nb = V->tp.nslots;
-    // the vector kernels run nb workgroups of one cell per thread
-    if ((size_t)nb * flow::FT < V->ncell) {
-        vc_free(V);
-        return fail(PCX_ERR_INVALID, "reduction slots do not cover the grid");
-    }
-    const size_t nred = 2 * (size_t)nb + 2 * RED_WG + NSC;
+    V->T = apply_tiles(G);
+    const size_t nred = 3 * 2 * (size_t)RED_MAX + NSC;
     if (hipMalloc(&V->tab, t.size() * sizeof(double)) != hipSuccess ||
         hipMalloc(&V->ws, 4 * V->ncell * sizeof(double)) != hipSuccess ||
-        hipMalloc(&V->red, nred * sizeof(double)) != hipSuccess) {
+        hipMalloc(&V->red, nred * sizeof(double)) != hipSuccess ||
+        hipHostMalloc((void **)&V->hres, sizeof(double), hipHostMallocDefault) != hipSuccess ||
+        hipHostGetDevicePointer((void **)&V->dres, V->hres, 0) != hipSuccess) {
         vc_free(V);
         return fail(PCX_ERR_NOMEM, "projection workspace allocation failed");
     }
@@ -100,10 +100,11 @@ extern "C" pcx_status pcx_varcoef_create(const pcx_grid *grid, const pcx_options
     V->z = V->ws + V->ncell;
     V->d = V->ws + 2 * V->ncell;
     V->q = V->ws + 3 * V->ncell;
-    V->R.part = V->red;
-    V->R.lvl = V->red + 2 * (size_t)nb;
-    V->R.sc = V->R.lvl + 2 * RED_WG;
-    V->R.nb = nb;
+    double *sc0 = V->red + 3 * 2 * (size_t)RED_MAX;
+    const int nv = vec_wgs(V->ncell);
+    V->RA = VRed{V->red, sc0, V->T.wgs};
+    V->R = VRed{V->red + 2 * RED_MAX, sc0, nv};
+    V->RD = VRed{V->red + 4 * RED_MAX, sc0, nv};
     // the scalar slots start at zero but for the total weight nx ny sum(dzf)
     std::vector<double> sc(NSC, 0.0);
     sc[S_WTOT] = (double)nx * (double)ny * zsum;
@@ -127,7 +128,7 @@ extern "C" pcx_status pcx_varcoef_apply(pcx_varcoef V, const double *rho, const 
 {
     if (!V || !rho || !p || !out) return fail(PCX_ERR_INVALID, "NULL argument");
     if (out == rho || out == p) return fail(PCX_ERR_INVALID, "out aliases an input");
-    VCHK(launch_apply(V->G, V->tp, rho, p, out, 1.0, nullptr, (hipStream_t)stream));
+    VCHK(launch_apply(V->G, V->T, rho, p, out, 1.0, nullptr, (hipStream_t)stream));
     return PCX_OK;
 }
 
@@ -163,9 +164,9 @@ extern "C" pcx_status pcx_varcoef_project(pcx_varcoef V, double dt, double rho0,
     const VRed &R = V->R;
     double *p = p_out;
     // r = -(D u*)/dt minus its mean; bnorm = its norm
-    VCHK(launch_rhs(G, V->tp, u, v, w, 1.0 / dt, V->r, R, s));
+    VCHK(launch_rhs(G, u, v, w, 1.0 / dt, V->r, R, s));
     VCHK(red_scal(R, MODE_MEAN, s));
-    VCHK(launch_center(G, V->tp, V->r, R, s));
+    VCHK(launch_center(G, V->r, R, s));
     VCHK(red_scal(R, MODE_BNORM, s));
     VCHK(hipMemsetAsync(p, 0, V->ncell * sizeof(double), s));
     double res = 0.0;
@@ -176,16 +177,15 @@ extern "C" pcx_status pcx_varcoef_project(pcx_varcoef V, double dt, double rho0,
         // z = -rho0 L^-1 r (the solve; the factor is folded into the kernels)
         st = pcx_poisson_solve(V->plan, V->r, V->z, stream);
         if (st != PCX_OK) return st;
-        VCHK(launch_dinit(G, V->tp, V->r, V->z, V->d, rho0, R, s));
+        VCHK(launch_dinit(G, V->r, V->z, V->d, rho0, R, s));
         VCHK(red_scal(R, MODE_RZ, s));
         while (it < maxit) {
-            VCHK(launch_apply(G, V->tp, rho, V->d, V->q, -1.0, &R, s));
-            VCHK(red_scal(R, MODE_ALPHA, s));
-            VCHK(launch_update(G, V->tp, p, V->d, V->r, V->q, R, s));
-            VCHK(red_scal(R, MODE_RES, s));
+            VCHK(launch_apply(G, V->T, rho, V->d, V->q, -1.0, &V->RA, s));
+            VCHK(launch_update(G, p, V->d, V->r, V->q, V->RA, R, s));
+            VCHK(red_scal(R, MODE_RES, s, V->dres));
             ++it;
-            st = read_sc(V, S_RES, s, &res);
-            if (st != PCX_OK) return st;
+            VCHK(hipStreamSynchronize(s));
+            res = *(volatile double *)V->hres;
             if (!std::isfinite(res)) {
                 if (iters) *iters = it;
                 if (relres) *relres = res;
@@ -193,19 +193,18 @@ extern "C" pcx_status pcx_varcoef_project(pcx_varcoef V, double dt, double rho0,
             }
             if (res <= tol) break;
             // the solve ignores the residual's mean (it removes the singular
-            // mode); the dot pass removes it from r itself
+            // mode); the dot pass and the update take it off r
             st = pcx_poisson_solve(V->plan, V->r, V->z, stream);
             if (st != PCX_OK) return st;
-            VCHK(launch_dot(G, V->tp, V->r, V->z, rho0, R, s));
-            VCHK(red_scal(R, MODE_BETA, s));
-            VCHK(launch_dupd(G, V->tp, V->z, V->d, rho0, R, s));
+            VCHK(launch_dot(G, V->r, V->z, rho0, V->RD, s));
+            VCHK(launch_dupd(G, V->z, V->d, rho0, V->RD, s));
         }
     }
     // correction with p (its gradient does not see the mean), then the gauge
-    VCHK(launch_pmean(G, V->tp, p, R, s));
+    VCHK(launch_pmean(G, p, R, s));
     VCHK(red_scal(R, MODE_PMEAN, s));
     VCHK(launch_correct(G, V->tp, rho, p, u, v, w, dt, u_out, v_out, w_out, s));
-    VCHK(launch_pshift(G, V->tp, p, R, s));
+    VCHK(launch_pshift(G, p, R, s));
     if (iters) *iters = it;
     if (relres) *relres = res;
     if (res > tol) return fail(PCX_ERR_NOT_CONVERGED, "maxit reached before tol");

@@ -10,57 +10,85 @@ namespace pcx {
 namespace vc {
 
 // device scalar slots of the conjugate-gradient iteration
-enum { S_RZ, S_DQ, S_ALPHA, S_BETA, S_M, S_RES, S_BNORM, S_WTOT, S_PMEAN, NSC };
+// (S_RZN: rz of the direction in use, S_RZ: of the one before it, so that
+// the kernel that forms beta reads the one and stores the other)
+enum { S_RZ, S_RZN, S_M, S_DRIFT, S_RES, S_BNORM, S_WTOT, S_PMEAN, NSC };
 
-// what the scalar kernel makes of the two reduced sums (S0, S1)
+// what red_scal makes of the two reduced sums (S0, S1)
 enum {
     MODE_MEAN,  // m = S0 / wtot
-    MODE_BNORM, // bnorm = sqrt(S0); res = 1 (0 when S0 = 0)
+    MODE_BNORM, // bnorm = sqrt(S0); res = 1 (0 when S0 = 0); drift = 0
     MODE_RZ,    // rz = S0
-    MODE_ALPHA, // dq = S0; alpha = rz / dq
-    MODE_RES,   // m = S0 / wtot; res = sqrt(S1 - m S0) / bnorm
-    MODE_BETA,  // beta = S0 / rz; rz = S0
+    MODE_RES,   // drift = S0 / wtot; res = sqrt(S1 - drift S0) / bnorm
     MODE_PMEAN  // pmean = S0 / wtot
 };
 
-// workgroups of the first reduction level (partials -> lvl)
-constexpr int RED_WG = 256;
-
-// Reductions: every partial-writing kernel stores the two sums of its
-// workgroup b (numbered over the launches of the tile plan) at part[b] and
-// part[nb + b] (nb = TilePlan::nslots); red_scal sums them in a fixed order
-// into the scalar slots.
+// Reductions: a partial-writing kernel stores the two sums of its workgroup
+// b at part[b] and part[nb + b], nb <= RED_MAX workgroups in all, and what
+// needs the total sums them in a fixed order: red_scal (one workgroup) into
+// the scalar slots, or every workgroup of the next kernel for itself, which
+// costs it about a microsecond and spares two launches in the chain.
+constexpr int RED_MAX = 1024;
 struct VRed {
     double *part; // 2 nb
-    double *lvl;  // 2 RED_WG
     double *sc;   // NSC
     int nb;
 };
+
+// Workgroups of the vector kernels (256 cells each and round, RED_MAX at most)
+inline int vec_wgs(size_t cells)
+{
+    const size_t n = (cells + flow::FT - 1) / flow::FT;
+    return n < (size_t)RED_MAX ? (int)n : RED_MAX;
+}
+
+// Tiles of the operator: MAI x MAJ columns over chunks of ckc planes, each
+// workgroup a plane in LDS.  A chunk starts with two extra planes, and 512
+// workgroups (two per CU) run at once: the chunk length with the fewest
+// planes marched in a row.
+constexpr int MAI = 64, MAJ = 8, MAT = MAI * MAJ;
+struct ATiles {
+    int nti, ntj, ckc, n, wgs; // tiles, workgroups (a multiple of 8)
+};
+inline ATiles apply_tiles(const flow::FGrid &G)
+{
+    ATiles t{(G.n[0] + MAI - 1) / MAI, (G.n[1] + MAJ - 1) / MAJ, G.n[2], 0, 0};
+    const long txy = (long)t.nti * t.ntj;
+    long best = -1;
+    for (int n = 1; n <= G.n[2]; ++n) {
+        const int c = (G.n[2] + n - 1) / n;
+        const long wgs = txy * ((G.n[2] + c - 1) / c), cost = (wgs + 511) / 512 * (c + 2);
+        if (best < 0 || cost < best) { best = cost; t.ckc = c; }
+    }
+    t.n = (int)(txy * ((G.n[2] + t.ckc - 1) / t.ckc));
+    t.wgs = t.n < RED_MAX ? (t.n + 7) / 8 * 8 : RED_MAX;
+    return t;
+}
 
 using flow::FGrid;
 
 using flow::TilePlan;
 
-hipError_t launch_apply(const FGrid &G, const TilePlan &tp, const double *rho, const double *p, double *out,
-                        double sign, const VRed *R, hipStream_t s);
-hipError_t launch_rhs(const FGrid &G, const TilePlan &tp, const double *u, const double *v, const double *w,
-                      double idt, double *r, const VRed &R, hipStream_t s);
-hipError_t launch_center(const FGrid &G, const TilePlan &tp, double *r, const VRed &R, hipStream_t s);
-hipError_t launch_dinit(const FGrid &G, const TilePlan &tp, const double *r, const double *z, double *d, double rho0,
+// out = sign D((1/rho_f) G p); with R (nb = T.wgs) partial sums of dzf p out
+hipError_t launch_apply(const FGrid &G, const ATiles &T, const double *rho, const double *p, double *out, double sign,
+                        const VRed *R, hipStream_t s);
+hipError_t launch_rhs(const FGrid &G, const double *u, const double *v, const double *w, double idt, double *r, const VRed &R, hipStream_t s);
+hipError_t launch_center(const FGrid &G, double *r, const VRed &R, hipStream_t s);
+hipError_t launch_dinit(const FGrid &G, const double *r, const double *z, double *d, double rho0,
                         const VRed &R, hipStream_t s);
-hipError_t launch_update(const FGrid &G, const TilePlan &tp, double *p, const double *d, double *r, const double *q,
+// IN: partials whose sum the kernel takes, R: the ones it writes
+hipError_t launch_update(const FGrid &G, double *p, const double *d, double *r, const double *q, const VRed &IN,
                          const VRed &R, hipStream_t s);
-hipError_t launch_dot(const FGrid &G, const TilePlan &tp, double *r, const double *z, double rho0, const VRed &R,
-                      hipStream_t s);
-hipError_t launch_dupd(const FGrid &G, const TilePlan &tp, const double *z, double *d, double rho0, const VRed &R,
-                       hipStream_t s);
-hipError_t launch_pmean(const FGrid &G, const TilePlan &tp, const double *p, const VRed &R, hipStream_t s);
+hipError_t launch_dot(const FGrid &G, const double *r, const double *z, double rho0, const VRed &R, hipStream_t s);
+hipError_t launch_dupd(const FGrid &G, const double *z, double *d, double rho0, const VRed &IN, hipStream_t s);
+hipError_t launch_pmean(const FGrid &G, const double *p, const VRed &R, hipStream_t s);
 hipError_t launch_correct(const FGrid &G, const TilePlan &tp, const double *rho, const double *p, const double *u,
                           const double *v, const double *w, double dt, double *uo, double *vo, double *wo,
                           hipStream_t s);
-hipError_t launch_pshift(const FGrid &G, const TilePlan &tp, double *p, const VRed &R, hipStream_t s);
-// the two-level reduction of the partials and the scalar step `mode`
-hipError_t red_scal(const VRed &R, int mode, hipStream_t s);
+hipError_t launch_pshift(const FGrid &G, double *p, const VRed &R, hipStream_t s);
+// the sums of the partials and the scalar step `mode`; MODE_RES also stores
+// the residual at *host (host memory the device can write)
+hipError_t red_scal(const VRed &R, int mode, hipStream_t s, double *host = nullptr);
 
 } // namespace vc
 } // namespace pcx
