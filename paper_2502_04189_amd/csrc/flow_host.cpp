@@ -28,7 +28,7 @@ struct pcx_flow_s {
     pcx_plan plan = nullptr;
     double *tab = nullptr;           // z metric tables (metric_tables)
     double *ws = nullptr;            // NWS fields
-    unsigned long long *key = nullptr;
+    unsigned long long *key = nullptr, *dkey = nullptr; // minimum density key in host memory, host and device address
     unsigned long long *part = nullptr; // per-workgroup minimum keys
     size_t ncell = 0;
     double *psi, *n[3], *a[3], *kap, *rho_new, *pstar, *us[3];
@@ -40,7 +40,7 @@ static void flow_free(pcx_flow F)
     if (F->plan) pcx_plan_destroy(F->plan);
     if (F->tab) (void)hipFree(F->tab);
     if (F->ws) (void)hipFree(F->ws);
-    if (F->key) (void)hipFree(F->key);
+    if (F->key) (void)hipHostFree(F->key);
     if (F->part) (void)hipFree(F->part);
     delete F;
 }
@@ -78,7 +78,8 @@ extern "C" pcx_status pcx_flow_create(const pcx_grid *grid, const pcx_flow_param
     F->ncell = (size_t)nx * ny * nz;
     if (hipMalloc(&F->tab, t.size() * sizeof(double)) != hipSuccess ||
         hipMalloc(&F->ws, NWS * F->ncell * sizeof(double)) != hipSuccess ||
-        hipMalloc(&F->key, sizeof(unsigned long long)) != hipSuccess) {
+        hipHostMalloc((void **)&F->key, sizeof(unsigned long long), hipHostMallocDefault) != hipSuccess ||
+        hipHostGetDevicePointer((void **)&F->dkey, F->key, 0) != hipSuccess) {
         flow_free(F);
         return fail(PCX_ERR_NOMEM, "flow workspace allocation failed");
     }
@@ -101,7 +102,7 @@ extern "C" pcx_status pcx_flow_create(const pcx_grid *grid, const pcx_flow_param
     F->P = FParams{q.rho1, q.rho2, q.mu1, q.mu2, q.sigma, {q.gx, q.gy, q.gz}, q.gamma, q.eps, q.eps_s, 0.5 / q.eps};
     F->tp = tile_plan(G);
     F->tpn = tile_plan(G, 2);
-    if (hipMalloc(&F->part, (size_t)F->tp.nslots * sizeof(unsigned long long)) != hipSuccess) {
+    if (hipMalloc(&F->part, ((size_t)F->tp.nslots + MINWG) * sizeof(unsigned long long)) != hipSuccess) {
         flow_free(F);
         return fail(PCX_ERR_NOMEM, "flow workspace allocation failed");
     }
@@ -142,7 +143,7 @@ static FArgs base_args(pcx_flow F, const double *phi, const double *u, const dou
     }
     A.kap = F->kap;
     A.first = 1;
-    A.rho_min_key = F->key;
+    A.rho_min_key = F->dkey;
     A.rho_part = F->part;
     return A;
 }
@@ -192,7 +193,7 @@ extern "C" pcx_status pcx_flow_momentum_rhs(pcx_flow F, const double *phi, const
 
 // The substep up to the correction: normals, flux and curvature, momentum
 // predictor, phase update; u*, the new density and p* into the given
-// buffers; rho0 read back (one 8-byte copy: synchronizes the stream).
+// buffers; rho0 read back (synchronizes the stream).
 static pcx_status predictor(pcx_flow F, int32_t sub, double Dt, const double *phi, const double *u, const double *v,
                             const double *w, const double *p1, const double *p2, double r, double *hphi, double *hu,
                             double *hv, double *hw, double *phi_out, double *const us[3], double *rho_new,
@@ -216,10 +217,8 @@ static pcx_status predictor(pcx_flow F, int32_t sub, double Dt, const double *ph
     // one pass: the momentum predictor and the phase update read the state at
     // the start of the substep only
     FCHK(launch_momentum_phase(A, F->tp, s));
-    unsigned long long key = 0;
-    FCHK(hipMemcpyAsync(&key, F->key, sizeof(key), hipMemcpyDeviceToHost, s));
     FCHK(hipStreamSynchronize(s));
-    *rho0 = key_to_double(key);
+    *rho0 = key_to_double(*(volatile unsigned long long *)F->key);
     if (!(*rho0 > 0.0) || !std::isfinite(*rho0)) return fail(PCX_ERR_NONFINITE, "minimum density is not positive and finite");
     *dt = (GA[sub - 1] + ZE[sub - 1]) * Dt;
     return PCX_OK;

@@ -296,13 +296,13 @@ __global__ __launch_bounds__(FT) void k_flow_phase(BoxList L, FArgs A)
     put(A.hphi + at(A.G, t.i, t.j, t.k), r);
 }
 
-// minimum of the n workgroup keys into *rho_min_key (a few workgroups, one
-// atomic each)
-__global__ __launch_bounds__(FT) void k_flow_min(const unsigned long long *part, int n, unsigned long long *key_out)
+// minimum of n workgroup keys: each workgroup's own into out[its number]
+constexpr int MINT = 1024;
+__global__ __launch_bounds__(MINT) void k_flow_min(const unsigned long long *part, int n, unsigned long long *out)
 {
-    __shared__ unsigned long long red[FT / 64];
+    __shared__ unsigned long long red[MINT / 64];
     unsigned long long key = ~0ull;
-    for (int i = blockIdx.x * FT + threadIdx.x; i < n; i += gridDim.x * FT) key = part[i] < key ? part[i] : key;
+    for (int i = blockIdx.x * MINT + threadIdx.x; i < n; i += gridDim.x * MINT) key = part[i] < key ? part[i] : key;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         const unsigned long long x = __shfl_xor(key, o, 64);
@@ -311,9 +311,8 @@ __global__ __launch_bounds__(FT) void k_flow_min(const unsigned long long *part,
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = key;
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int i = 1; i < FT / 64; ++i) key = red[i] < key ? red[i] : key;
-        key = red[0] < key ? red[0] : key;
-        atomicMin(key_out, key);
+        for (int i = 0; i < MINT / 64; ++i) key = red[i] < key ? red[i] : key;
+        __hip_atomic_store(out + blockIdx.x, key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
@@ -509,8 +508,6 @@ __global__ __launch_bounds__(FT) void k_flow_momentum(BoxList L, FArgs A) { mome
 // the substep's momentum predictor with the phase update
 __global__ __launch_bounds__(FT) void k_flow_mom_phase(BoxList L, FArgs A) { momentum_body<true>(L, A); }
 
-__global__ void k_flow_key_reset(unsigned long long *k) { *k = ~0ull; }
-
 // The normals and the flux take a plan made with zlow = 2 (the flux kernel's
 // interior form reads psi two cells away).
 hipError_t launch_normals(const FArgs &A, const TilePlan &tp, hipStream_t s)
@@ -569,13 +566,22 @@ hipError_t launch_momentum(const FArgs &A, const TilePlan &tp, hipStream_t s)
 hipError_t launch_momentum_phase(const FArgs &A, const TilePlan &tp, hipStream_t s)
 {
     if (!A.phi_out || !A.hphi || !A.rho_new) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_flow_key_reset, dim3(1), dim3(1), 0, s, A.rho_min_key);
-    hipError_t e = hipGetLastError();
+    hipError_t e = FLOW_LAUNCH_PLAN(tp, k_flow_mom_phase, s, A);
     if (e != hipSuccess) return e;
-    e = FLOW_LAUNCH_PLAN(tp, k_flow_mom_phase, s, A);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_flow_min, dim3(64), dim3(FT), 0, s, (const unsigned long long *)A.rho_part, tp.nslots,
-                       A.rho_min_key);
+    // Up to 16 keys per thread one workgroup takes them all; more (4 million
+    // cells and up) in two levels.  The result goes to host memory: clearing
+    // a key, minima by atomics and a copy of it took two more steps of the
+    // stream's chain and the copy's wait.
+    const unsigned long long *part = A.rho_part;
+    int n = tp.nslots;
+    if (n > 16 * MINT) {
+        hipLaunchKernelGGL(k_flow_min, dim3(MINWG), dim3(MINT), 0, s, part, n, A.rho_part + n);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        part += n;
+        n = MINWG;
+    }
+    hipLaunchKernelGGL(k_flow_min, dim3(1), dim3(MINT), 0, s, part, n, A.rho_min_key);
     return hipGetLastError();
 }
 

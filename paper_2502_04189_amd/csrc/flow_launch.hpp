@@ -18,13 +18,14 @@ struct FArgs {
     int first;                       // first substep: no previous right-hand side
     double *hphi, *hu, *hv, *hw;     // previous right-hand sides in, this substep's out
     double *phi_out, *us[3], *rho_new; // NULL: right-hand sides only
-    unsigned long long *rho_min_key;
-    unsigned long long *rho_part;    // one key per workgroup of the phase pass (TilePlan::nslots)
+    unsigned long long *rho_min_key; // host memory the device can write
+    unsigned long long *rho_part;    // one key per workgroup of the phase pass (TilePlan::nslots), then MINWG more
     const double *p1, *p2;           // pressures of the two previous substeps
     double r;
     double *pstar;                   // NULL: no extrapolation
 };
 
+constexpr int MINWG = 64; // workgroups of a first level of the minimum
 hipError_t launch_normals(const FArgs &A, const TilePlan &tp, hipStream_t s);
 hipError_t launch_flux(const FArgs &A, const TilePlan &tp, hipStream_t s);
 hipError_t launch_phase(const FArgs &A, const TilePlan &tp, hipStream_t s);

@@ -405,6 +405,7 @@ static pcx_status plan_free(pcx_plan P)
     if (!P) return PCX_OK;
     if (P->tables.dev) (void)hipFree(P->tables.dev);
     if (P->ws) (void)hipFree(P->ws);
+    if (P->hrep) (void)hipHostFree(P->hrep);
     for (auto e : P->ev) (void)hipEventDestroy(e);
     delete P;
     return PCX_OK;
@@ -563,6 +564,11 @@ extern "C" pcx_status pcx_plan_create(const pcx_grid *grid, const pcx_options *o
         return fail(PCX_ERR_NOMEM, "workspace allocation failed");
     }
     plan_bind(P, ht, (char *)P->tables.dev, (char *)P->ws, L);
+    if (hipHostMalloc((void **)&P->hrep, (NSTAT + (size_t)P->grid.nz) * 8, hipHostMallocDefault) != hipSuccess ||
+        hipHostGetDevicePointer((void **)&P->drep, P->hrep, 0) != hipSuccess) {
+        P->drep = nullptr;
+        (void)hipGetLastError();
+    }
     *out = P;
     return PCX_OK;
 }
@@ -777,12 +783,34 @@ extern "C" pcx_status pcx_step(pcx_plan P, double dt, double rho0, const double 
     // where no extra solve can be taken after the first correction).
     pcx_status st = PCX_OK;
     std::vector<unsigned long long> h(NSTAT);
+    std::vector<double> ps(P->grid.nz);
     if (!report) return correct();
+    // the statistics, with sums also the plane sums of p, once the stream is done
+    auto fetch = [&](bool sums) -> pcx_status {
+        const double *q = sums ? p_out : nullptr;
+        const int nxy = P->grid.nx * P->grid.ny;
+        if (P->drep) {
+            HIPCHK(launch_report(P->stats, q, nxy, P->grid.nz, P->drep, s));
+        } else {
+            if (sums) HIPCHK(launch_plane_sums(q, nxy, P->grid.nz, P->psum, s));
+            HIPCHK(hipMemcpyAsync(h.data(), P->stats, NSTAT * 8, hipMemcpyDeviceToHost, s));
+            if (sums) HIPCHK(hipMemcpyAsync(ps.data(), P->psum, ps.size() * 8, hipMemcpyDeviceToHost, s));
+        }
+        HIPCHK(hipStreamSynchronize(s));
+        if (P->drep) {
+            std::memcpy(h.data(), P->hrep, NSTAT * 8);
+            if (sums) std::memcpy(ps.data(), P->hrep + NSTAT, ps.size() * 8);
+        }
+        return PCX_OK;
+    };
+    bool sums = false;
     while (true) {
         st = correct();
         if (st != PCX_OK) return st;
-        HIPCHK(hipMemcpyAsync(h.data(), P->stats, NSTAT * 8, hipMemcpyDeviceToHost, s));
-        HIPCHK(hipStreamSynchronize(s));
+        // no further solve can follow: the plane sums in the same go
+        sums = P->prec == PREC_F64 || solves >= P->opt.max_iters || inplace;
+        st = fetch(sums);
+        if (st != PCX_OK) return st;
         double finf = stat_d(h, ST_FINF), dv = stat_d(h, ST_DIV);
         double rel = dv / ((dt / rho0) * finf);
         double einf = stat_d(h, ST_SOLVE0 + 4 * (solves - 1) + 1);
@@ -796,10 +824,10 @@ extern "C" pcx_status pcx_step(pcx_plan P, double dt, double rho0, const double 
         ++solves;
     }
     // report
-    HIPCHK(launch_plane_sums(p_out, P->grid.nx * P->grid.ny, P->grid.nz, P->psum, s));
-    std::vector<double> ps(P->grid.nz);
-    HIPCHK(hipMemcpyAsync(ps.data(), P->psum, ps.size() * 8, hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
+    if (!sums) {
+        st = fetch(true);
+        if (st != PCX_OK) return st;
+    }
     double num = 0.0, lz = P->zf[P->grid.nz] - P->zf[0];
     for (int k = 0; k < P->grid.nz; ++k) num += (P->zf[k + 1] - P->zf[k]) * ps[k];
     pcx_report r;

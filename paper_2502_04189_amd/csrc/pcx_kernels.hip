@@ -136,9 +136,12 @@ __global__ void k_zero(unsigned long long *p, int n)
 }
 
 // Per-plane sums of p in a fixed order (deterministic), one workgroup per k.
-__global__ __launch_bounds__(NT) void k_plane_sums(const double *p, int nxy, double *out)
+__global__ __launch_bounds__(NT) void k_plane_sums(const double *p, int nxy, double *out,
+                                                   const unsigned long long *stats, unsigned long long *stats_out)
 {
     __shared__ double part[NT];
+    if (stats && blockIdx.x == 0 && (int)threadIdx.x < NSTAT) stats_out[threadIdx.x] = stats[threadIdx.x];
+    if (!p) return;
     const double *pl = p + (size_t)blockIdx.x * nxy;
     double s = 0.0;
     for (int i = threadIdx.x; i < nxy; i += NT) s += pl[i];
@@ -339,7 +342,13 @@ hipError_t launch_div(const Dom &d, hipStream_t s)
 
 hipError_t launch_plane_sums(const double *p, int nxy, int nz, double *out, hipStream_t s)
 {
-    PCX_LAUNCH(k_plane_sums, nz, 0, s, p, nxy, out);
+    PCX_LAUNCH(k_plane_sums, nz, 0, s, p, nxy, out, (const unsigned long long *)nullptr, (unsigned long long *)nullptr);
+}
+
+hipError_t launch_report(const unsigned long long *stats, const double *p, int nxy, int nz, unsigned long long *out,
+                         hipStream_t s)
+{
+    PCX_LAUNCH(k_plane_sums, p ? nz : 1, 0, s, p, nxy, (double *)(out + NSTAT), stats, out);
 }
 
 // The 8-byte key of pcx_rho_min: a file-scope device variable (one per

@@ -24,6 +24,11 @@ hipError_t launch_div(const Dom &d, hipStream_t s);
 hipError_t launch_pmean(const Dom &d, hipStream_t s);
 hipError_t launch_xmax(const Dom &d, int solve, hipStream_t s);
 hipError_t launch_plane_sums(const double *p, int nxy, int nz, double *out, hipStream_t s);
+// The statistics and, with p, the plane sums of p into out[NSTAT + nz], host
+// memory the device can write: a report then takes one synchronisation and
+// no copy (two of each took 50 us more of a 32^3 step's 127).
+hipError_t launch_report(const unsigned long long *stats, const double *p, int nxy, int nz, unsigned long long *out,
+                         hipStream_t s);
 // min over n doubles into *out (host); synchronises s
 hipError_t min_to_host(const double *a, long long n, hipStream_t s, double *out);
 

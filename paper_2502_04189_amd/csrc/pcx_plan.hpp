@@ -100,6 +100,9 @@ struct pcx_plan_s {
     double *f = nullptr;
     double *r = nullptr;
     double *psum = nullptr;
+    // statistics and plane sums of a report in host memory, host and device
+    // address (NULL: no such memory, a report copies them)
+    unsigned long long *hrep = nullptr, *drep = nullptr;
     double *ppart = nullptr;
     double *xpart = nullptr;
     double *spart = nullptr;
