@@ -155,15 +155,6 @@ template <typename T, bool INV, int N, int LINES, int NTH> struct LineFft {
     __device__ __forceinline__ void last() const { middle<P.r[P.n - 1], N / P.r[P.n - 1]>(); }
 };
 
-// W_nx^l for l in [0, M] from the table of the first M / 2 + 1 (W^(M-l) =
-// -conj W^l), in LDS or in memory
-template <int M, typename C> __device__ __forceinline__ C split_root(const C *twr, int l)
-{
-    if (2 * l <= M) return twr[l];
-    const C w = twr[M - l];
-    return C{-w.x, w.y};
-}
-
 // Row of an x tile: row j of plane k of line q = k ys + j; on: it exists
 // (else a row that does, to read)
 struct XLine {
@@ -184,14 +175,11 @@ template <typename T, int M> __device__ __forceinline__ void fft_xfwd(const Dom 
 {
     using C = c2<T>;
     constexpr int L = fft_lines(M, sizeof(C)), NTH = fft_threads(M, sizeof(C)), LDC = lds_line(M);
+    constexpr int STEP = NTH / L, K = (M / 2 + 1 + STEP - 1) / STEP;
     static_assert(NTH % L == 0, "a thread keeps its row in the corner turn");
-    C *buf = (C *)smem, *ltw = buf + L * LDC, *ltr = ltw + tw_half(M);
-    constexpr bool SL = fft_split_lds(M, sizeof(C));
+    C *buf = (C *)smem, *ltw = buf + L * LDC;
     TwStage<T, NTH> tws;
-    TabStage<T, NTH> trs;
     tws.fetch(d.fx);
-    if constexpr (SL) trs.fetch((const C *)d.twr, M / 2 + 1);
-    const C *twr = SL ? ltr : (const C *)d.twr;
     const int nx = d.nx, q0 = tile * L;
     const bool wx = d.bcx != BC_PER;
     auto row_of = [&](int line) {
@@ -199,7 +187,6 @@ template <typename T, int M> __device__ __forceinline__ void fft_xfwd(const Dom 
         return src + ((size_t)x.k * d.ny + x.j) * nx;
     };
     tws.put(ltw, d.fx);
-    if constexpr (SL) trs.put(ltr, (const C *)d.twr, M / 2 + 1);
     const LineFft<T, false, M, L, NTH> F{buf, ltw};
     if (!wx) {
         F.template first<false, false>([&](int line, int n) {
@@ -222,39 +209,53 @@ template <typename T, int M> __device__ __forceinline__ void fft_xfwd(const Dom 
         });
     }
     F.middles();
+    // X[l] = E + W^l O and X[M-l] = conj(E - W^l O) of the half-length
+    // spectrum, l in [0, M/2], by one thread: a root and two LDS reads for two
+    // modes, the roots from memory ahead of the last stage (in LDS they cost
+    // a tile per CU at some lengths)
+    const int r = threadIdx.x % L, l0 = threadIdx.x / L;
+    const C *twr = (const C *)d.twr;
+    C w[K];
+#pragma unroll
+    for (int t = 0; t < K; ++t) w[t] = twr[min(l0 + t * STEP, M / 2)];
     F.last();
-    // X[l] = E + W^l O of the half-length spectrum, l in [0, M]
-    const int r = threadIdx.x % L;
     const XLine x = xline(d, q0 + r);
     const C *z = buf + r * LDC;
-    auto mode = [&](int l) {
-        if (l == 0 || l == M) {
+    auto pair = [&](int l, C root, C &xl, C &xm) {
+        if (l == 0) {
             const C a = z[0];
-            return C{l == 0 ? a.x + a.y : a.x - a.y, T(0)};
+            xl = C{a.x + a.y, T(0)};
+            xm = C{a.x - a.y, T(0)};
+            return;
         }
         const C zl = z[pidx(l)], zm = z[pidx(M - l)];
         const C e = {T(0.5) * (zl.x + zm.x), T(0.5) * (zl.y - zm.y)};
-        const C o = {T(0.5) * (zl.y + zm.y), T(-0.5) * (zl.x - zm.x)};
-        return cadd(e, cmul(split_root<M>(twr, l), o));
+        const C o = cmul(root, C{T(0.5) * (zl.y + zm.y), T(-0.5) * (zl.x - zm.x)});
+        xl = cadd(e, o);
+        xm = C{e.x - o.x, o.y - e.y};
     };
     const int ys = d.ys;
     C *out = (C *)d.s1 + (size_t)x.k * d.nl * ys + x.j;
     const bool on = x.on;
-    if (!wx) {
-        constexpr int STEP = NTH / L, K = (M + 1 + STEP - 1) / STEP;
+    // A_k = W_{4N}^k X_k: with walls modes Re A_k and, N - k, -Im A_k
+    const C *wd = (const C *)d.dctx;
 #pragma unroll
-        for (int t = 0; t < K; ++t) {
-            const int l = threadIdx.x / L + t * STEP;
-            if (on && l <= M) st_stream(out + (size_t)l * ys, mode(l));
-        }
-    } else {
-        // A_k = W_{4N}^k X_k: modes Re A_k and, N - k, -Im A_k
-        const C *wd = (const C *)d.dctx;
-#pragma unroll 4
-        for (int l = threadIdx.x / L; l < nx; l += NTH / L) {
-            const int kk = l <= M ? l : nx - l;
-            const C a = cmul(wd[kk], mode(kk));
-            if (on) st_stream(out + (size_t)l * ys, C{l <= M ? a.x : -a.y, T(0)});
+    for (int t = 0; t < K; ++t) {
+        const int l = l0 + t * STEP, m = M - l;
+        if (!on || l > M / 2) continue;
+        C xl, xm;
+        pair(l, w[t], xl, xm);
+        if (!wx) {
+            st_stream(out + (size_t)l * ys, xl);
+            if (l != m) st_stream(out + (size_t)m * ys, xm);
+        } else {
+            const C al = cmul(wd[l], xl);
+            st_stream(out + (size_t)l * ys, C{al.x, T(0)});
+            if (l) st_stream(out + (size_t)(nx - l) * ys, C{-al.y, T(0)});
+            if (l == m) continue;
+            const C am = cmul(wd[m], xm);
+            st_stream(out + (size_t)m * ys, C{am.x, T(0)});
+            if (l) st_stream(out + (size_t)(nx - m) * ys, C{-am.y, T(0)});
         }
     }
 }
@@ -267,67 +268,74 @@ template <typename T, int MODE, int M> __device__ __forceinline__ void fft_xinv(
     using C = c2<T>;
     constexpr int L = fft_lines(M, sizeof(C)), NTH = fft_threads(M, sizeof(C)), LDC = lds_line(M), STEP = NTH / L;
     static_assert(NTH % L == 0, "a thread keeps its row in the corner turn");
-    C *buf = (C *)smem, *ltw = buf + L * LDC, *ltr = ltw + tw_half(M);
-    constexpr bool SL = fft_split_lds(M, sizeof(C));
+    C *buf = (C *)smem, *ltw = buf + L * LDC;
     TwStage<T, NTH> tws;
-    TabStage<T, NTH> trs;
     tws.fetch(d.fx);
-    if constexpr (SL) trs.fetch((const C *)d.twr, M / 2 + 1);
-    const C *twr = SL ? ltr : (const C *)d.twr;
     const int nx = d.nx, ys = d.ys;
     const int q0 = tile * L, r = threadIdx.x % L, l0 = threadIdx.x / L;
     const bool wx = d.bcx != BC_PER;
     {
+        // Z[l] = E + i O, E = X[l] + conj(X[M-l]), O = (X[l] - conj(X[M-l]))
+        // conj(W^l); Z[M-l] = conj(E) + i conj(O): the thread that loads both
+        // modes forms both points on their way into LDS.  (Formed by the
+        // first stage's butterflies, they took 2 LDS reads and a root a
+        // point and up to 128 registers, a tile less per CU at many
+        // lengths: nx = 576, 34 M cells, 141 us against 102; 972, 167 and 114)
         const XLine x = xline(d, q0 + r);
-        const C *in = (const C *)d.s1 + (size_t)x.k * d.nl * ys + x.j;
+        const C *in = (const C *)d.s1 + (size_t)x.k * d.nl * ys + x.j, *twr = (const C *)d.twr;
         C *mine = buf + r * LDC;
-        if (!wx) {
-            constexpr int K = (M + 1 + STEP - 1) / STEP;
-            C v[K];
+        constexpr int K = (M / 2 + 1 + STEP - 1) / STEP;
+        auto pair = [&](int l, C xl, C xm, C w) {
+            if (l == 0) {
+                // X[0] and X[M] of a real row are real
+                mine[0] = C{xl.x + xm.x, xl.x - xm.x};
+                return;
+            }
+            const C e = {xl.x + xm.x, xl.y - xm.y}, df = {xl.x - xm.x, xl.y + xm.y};
+            const C o = cmul(df, cconj(w));
+            mine[pidx(l)] = C{e.x - o.y, e.y + o.x};
+            if (2 * l != M) mine[pidx(M - l)] = C{e.x + o.y, o.x - e.y};
+        };
+        C w[K];
 #pragma unroll
-            for (int t = 0; t < K; ++t) v[t] = in[(size_t)min(l0 + t * STEP, M) * ys];
+        for (int t = 0; t < K; ++t) w[t] = twr[min(l0 + t * STEP, M / 2)];
+        if (!wx) {
+            C a[K], b[K];
 #pragma unroll
             for (int t = 0; t < K; ++t) {
-                // X[0] and X[M] of a real row are real: entry 0 holds both
-                const int l = l0 + t * STEP;
-                if (l == 0) mine[0].x = v[t].x;
-                else if (l < M) mine[pidx(l)] = v[t];
-                else if (l == M) mine[0].y = v[t].x;
+                const int l = min(l0 + t * STEP, M / 2);
+                a[t] = in[(size_t)l * ys];
+                b[t] = in[(size_t)(M - l) * ys];
             }
+#pragma unroll
+            for (int t = 0; t < K; ++t)
+                if (l0 + t * STEP <= M / 2) pair(l0 + t * STEP, a[t], b[t], w[t]);
         } else {
             // real modes X: V_k = conj(W_{4N}^k) (X_k - i X_{N-k}), k in [1, M),
-            // and in entry 0 V_0 = X_0 and V_M, both real
+            // V_0 = X_0 and V_M = conj(w_M) (1 - i) X_M, both real
             const C *wd = (const C *)d.dctx;
-            constexpr int K = (M + STEP - 1) / STEP;
-            T a[K], b[K];
+            T a[K][2], b[K][2]; // X_l, X_{N-l}; X_{M-l}, X_{M+l}
 #pragma unroll
             for (int t = 0; t < K; ++t) {
-                const int l = min(l0 + t * STEP, M - 1);
-                a[t] = in[(size_t)l * ys].x;
-                b[t] = in[(size_t)(l ? nx - l : M) * ys].x;
+                const int l = min(l0 + t * STEP, M / 2);
+                a[t][0] = in[(size_t)l * ys].x;
+                a[t][1] = in[(size_t)(nx - max(l, 1)) * ys].x;
+                b[t][0] = in[(size_t)(M - l) * ys].x;
+                b[t][1] = in[(size_t)(M + l) * ys].x;
             }
 #pragma unroll
             for (int t = 0; t < K; ++t) {
                 const int l = l0 + t * STEP;
-                if (l >= M) continue;
-                const C v = cmul(cconj(wd[l]), C{a[t], -b[t]});
-                // V_M = conj(w_M) (1 - i) X_M
-                mine[pidx(l)] = l ? v : C{a[t], cmul(cconj(wd[M]), C{b[t], -b[t]}).x};
+                if (l > M / 2) continue;
+                const C vl = l ? cmul(cconj(wd[l]), C{a[t][0], -a[t][1]}) : C{a[t][0], T(0)};
+                pair(l, vl, cmul(cconj(wd[M - l]), C{b[t][0], -b[t][1]}), w[t]);
             }
         }
     }
     tws.put(ltw, d.fx);
-    if constexpr (SL) trs.put(ltr, (const C *)d.twr, M / 2 + 1);
     __syncthreads();
-    // Z[n] = E + i O,  E = X[n] + conj(X[M-n]),  O = (X[n] - conj(X[M-n])) conj(W^n)
     const LineFft<T, true, M, L, NTH> F{buf, ltw};
-    F.template first<false, true>([&](int line, int n) {
-        const C *z = buf + line * LDC;
-        const C xl = z[pidx(n)], xm = z[pidx(n ? M - n : 0)];
-        const C e = {xl.x + xm.x, xl.y - xm.y}, df = {xl.x - xm.x, xl.y + xm.y};
-        const C o = cmul(df, cconj(split_root<M>(twr, n)));
-        return n ? C{e.x - o.y, e.y + o.x} : C{xl.x + xl.y, xl.x - xl.y};
-    });
+    F.template first<false, true>([&](int line, int n) { return buf[line * LDC + pidx(n)]; });
     F.middles();
     // accumulation also removes the FP64 volume mean of the previous p
     const double shift = MODE == XOUT_ACCUM ? d.pmean[0] : 0.0;
@@ -438,8 +446,12 @@ template <typename T, int N> __device__ __forceinline__ void fft_yfwd(const Dom 
         F.template first<false, true>([&](int line, int n) { return buf[line * LDC + pidx(n)]; });
     }
     F.middles();
+    const int c = threadIdx.x % L, m0 = threadIdx.x / L;
+    // walls: X_m = (w_m V_m + conj(w_m) V_{N-m}) / 2, X_0 = V_0, and with
+    // w_{N-m} = -i conj(w_m) the other point of the pair by the same thread
+    const C *wd = (const C *)d.dcty;
+    constexpr int KW = (N / 2 + 1 + STEP - 1) / STEP;
     F.last();
-    const int c = threadIdx.x % L;
     const YLine y = yline(d, q0 + c);
     const int zs = d.zs;
     C *out = (C *)d.s2 + (size_t)y.l * N * zs + y.k;
@@ -449,21 +461,22 @@ template <typename T, int N> __device__ __forceinline__ void fft_yfwd(const Dom 
     if (!wy) {
 #pragma unroll
         for (int t = 0; t < K; ++t) {
-            const int m = threadIdx.x / L + t * STEP;
+            const int m = m0 + t * STEP;
             if (on && (N % STEP == 0 || m < N)) st_stream(out + (size_t)m * zs, z[pidx(m)]);
         }
-    } else {
-        // X_m = (w_m V_m + conj(w_m) V_{N-m}) / 2, X_0 = V_0
-        const C *wd = (const C *)d.dcty;
-#pragma unroll 4
-        for (int m = threadIdx.x / L; m < N; m += STEP) {
-            C v = z[pidx(m)];
-            if (m) {
-                const C w = wd[m], p = cmul(w, v), g = cmul(cconj(w), z[pidx(N - m)]);
-                v = C{T(0.5) * (p.x + g.x), T(0.5) * (p.y + g.y)};
-            }
-            if (on) st_stream(out + (size_t)m * zs, v);
+        return;
+    }
+#pragma unroll
+    for (int t = 0; t < KW; ++t) {
+        const int m = m0 + t * STEP;
+        if (!on || m > N / 2) continue;
+        if (m == 0) {
+            st_stream(out, z[0]);
+            continue;
         }
+        const C w = wd[m], pv = cmul(w, z[pidx(m)]), g = cmul(cconj(w), z[pidx(N - m)]);
+        st_stream(out + (size_t)m * zs, C{T(0.5) * (pv.x + g.x), T(0.5) * (pv.y + g.y)});
+        if (2 * m != N) st_stream(out + (size_t)(N - m) * zs, C{T(0.5) * (g.y - pv.y), T(0.5) * (pv.x - g.x)});
     }
 }
 
@@ -498,26 +511,37 @@ template <typename T, int N> __device__ __forceinline__ void fft_yinv(const Dom 
             NoPre());
         return;
     }
-    constexpr int K = (N + STEP - 1) / STEP;
+    // V_m = conj(w_m) (X_m - i X_{N-m}), X_N = 0, and with conj(w_{N-m}) = i
+    // w_m the other point of the pair, formed by the thread that loads both
+    // (as in the x inverse)
+    constexpr int K = (N / 2 + 1 + STEP - 1) / STEP;
     {
-        C v[K];
-#pragma unroll
-        for (int t = 0; t < K; ++t) v[t] = ld_stream(in + (size_t)min((int)threadIdx.x / L + t * STEP, N - 1) * zs);
+        const C *wd = (const C *)d.dcty;
+        const int m0 = threadIdx.x / L;
+        C *mine = buf + c * LDC;
+        C xa[K], xb[K], w[K];
 #pragma unroll
         for (int t = 0; t < K; ++t) {
-            const int m = threadIdx.x / L + t * STEP;
-            if (N % STEP == 0 || m < N) buf[c * LDC + pidx(m)] = v[t];
+            const int m = min(m0 + t * STEP, N / 2);
+            xa[t] = ld_stream(in + (size_t)m * zs);
+            xb[t] = ld_stream(in + (size_t)(N - max(m, 1)) * zs);
+            w[t] = wd[m];
+        }
+#pragma unroll
+        for (int t = 0; t < K; ++t) {
+            const int m = m0 + t * STEP;
+            if (m > N / 2) continue;
+            if (m == 0) {
+                mine[0] = xa[t];
+                continue;
+            }
+            mine[pidx(m)] = cmul(cconj(w[t]), C{xa[t].x + xb[t].y, xa[t].y - xb[t].x});
+            const C g = cmul(w[t], C{xb[t].x + xa[t].y, xb[t].y - xa[t].x});
+            if (2 * m != N) mine[pidx(N - m)] = C{-g.y, g.x};
         }
     }
     __syncthreads();
-    // V_k = conj(w_k) (X_k - i X_{N-k}), X_N = 0
-    const C *wd = (const C *)d.dcty;
-    F.template first<false, true>([&](int line, int n) {
-        const C *z = buf + line * LDC;
-        const C xk = z[pidx(n)], xn = z[pidx(n ? N - n : 0)];
-        const C v = cmul(cconj(wd[n]), C{xk.x + xn.y, xk.y - xn.x});
-        return n ? v : xk;
-    });
+    F.template first<false, true>([&](int line, int n) { return buf[line * LDC + pidx(n)]; });
     F.middles();
     F.last();
     constexpr int KO = (L * N + NTH - 1) / NTH;
@@ -551,6 +575,8 @@ constexpr int fft_kernel_threads(int n, int csz)
     return n ? (fft_threads(n, csz) <= 1024 ? fft_threads(n, csz) : throw "more threads than a workgroup has") : FSMALL_TH;
 }
 
+constexpr int fft_kernel_waves(int n, int csz) { return n ? fft_waves(n, csz) : 4; }
+
 // One kernel for a lone domain (the descriptor in the kernel arguments, a
 // tile per workgroup) and for a batch (an item per workgroup); both read the
 // descriptor through the constant address space.  There is no loop over
@@ -559,7 +585,8 @@ constexpr int fft_kernel_threads(int n, int csz)
 // 216 VGPRs with one and 80 without).  N = 0: every length up to FSMALL, by
 // the domain's own.
 template <typename T, int KIND, int N>
-__global__ __launch_bounds__(fft_kernel_threads(N, 2 * sizeof(T))) __attribute__((amdgpu_waves_per_eu(4))) void k_fft(FftArgs unused)
+__global__ __launch_bounds__(fft_kernel_threads(N, 2 * sizeof(T))) __attribute__((amdgpu_waves_per_eu(fft_kernel_waves(N, 2 * sizeof(T))))) void
+k_fft(FftArgs unused)
 {
     extern __shared__ __align__(16) char smem[];
     typedef const __attribute__((address_space(4))) FftArgs *Arg;

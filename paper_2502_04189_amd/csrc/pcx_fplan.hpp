@@ -96,16 +96,21 @@ __host__ __device__ constexpr int fft_threads(int n, int csz)
     while (fft_points(n, fft_lines(n, csz), th) > fft_points_max(csz)) th += 64;
     return th;
 }
-// The split twiddles of an x pass are in LDS unless two workgroups would not
-// fit a CU's 160 KB with them.
-__host__ __device__ constexpr bool fft_split_lds(int n, int csz)
-{
-    return ((size_t)fft_lines(n, csz) * lds_line(n) + tw_half(n) + n / 2 + 1) * csz <= 79 * 1024;
-}
 // LDS bytes of an x or y tile
-__host__ __device__ constexpr size_t fft_lds(int n, int csz, bool x)
+__host__ __device__ constexpr size_t fft_lds(int n, int csz)
 {
-    return ((size_t)fft_lines(n, csz) * lds_line(n) + tw_half(n) + (x && fft_split_lds(n, csz) ? n / 2 + 1 : 0)) * csz;
+    return ((size_t)fft_lines(n, csz) * lds_line(n) + tw_half(n)) * csz;
+}
+
+// Waves per SIMD that as many tiles as LDS has room for make up, between 4
+// (128 registers) and 7 (72): a few lengths take some registers more than
+// that leaves, and with them a tile per CU less (972 points forward in x:
+// 84 instead of 80, one tile instead of two, 142 us instead of 103).
+__host__ __device__ constexpr int fft_waves(int n, int csz)
+{
+    const int w = fft_threads(n, csz) / 64, t = (int)(160 * 1024 / fft_lds(n, csz));
+    const int e = (t * w + 3) / 4;
+    return n <= FSMALL || e < 4 ? 4 : (e > 7 ? 7 : e);
 }
 
 // longest half length of an x pass (columns: 1024)

@@ -380,12 +380,12 @@ size_t lds_x_general(const Dom &d, int prec)
 }
 size_t lds_x(const Dom &d, int prec)
 {
-    if (d.xlines) return fft_lds(d.M, prec == PREC_F64 ? 16 : 8, true);
+    if (d.xlines) return fft_lds(d.M, prec == PREC_F64 ? 16 : 8);
     return lds_x_general(d, prec);
 }
 size_t lds_y(const Dom &d, int prec)
 {
-    if (d.ylines) return fft_lds(d.ny, prec == PREC_F64 ? 16 : 8, false);
+    if (d.ylines) return fft_lds(d.ny, prec == PREC_F64 ? 16 : 8);
     return ((size_t)d.tk * lds_line(d.ny) + tw_half(d.ny)) * (prec == PREC_F64 ? 16 : 8) + 64;
 }
 size_t lds_z(const Dom &d, int prec)
