@@ -251,23 +251,23 @@ using SVel = SVec<0>;
 constexpr int SLX = 64 + 2, SLY = 4 + 2, SPL = SLX * SLY, SFLD = 3 * SPL, SNF = 4, SNR = 4;
 
 // Interior accessor whose staged fields come from the stages and all others
-// from memory (as Fast): fields F < NL from the LDS stage (l0: the thread's
-// cell in its middle plane), the others from the register stage rg[F - NL]
+// from memory (as Fast): fields F < NL from the LDS stage (lz: the thread's
+// cell in the planes below, of and above it), the others from the register stage rg[F - NL]
 // (rg[f][n]: offset (a, b, c) at n = 9 (c + 1) + 3 (b + 1) + a + 1).
 template <int NL> struct StageAcc : Fast {
     const double *st;
-    int l0;
+    int lz[3];
     const double (*rg)[27];
-    __device__ __forceinline__ StageAcc(const FGrid &G, int i, int j, int k, const double *stage, int l,
+    __device__ __forceinline__ StageAcc(const FGrid &G, int i, int j, int k, const double *stage, int lm, int l0, int lp,
                                         const double (*regs)[27])
-        : Fast(G, i, j, k), st(stage), l0(l), rg(regs)
+        : Fast(G, i, j, k), st(stage), lz{lm, l0, lp}, rg(regs)
     {
     }
     using Fast::cv;
     using Fast::fv;
     template <int F> __device__ __forceinline__ double cv(SField<F>, int a, int b, int c) const
     {
-        if constexpr (F < NL) return st[F * SFLD + l0 + c * SPL + b * SLX + a];
+        if constexpr (F < NL) return st[F * SFLD + lz[c + 1] + b * SLX + a];
         else return rg[F - NL][9 * (c + 1) + 3 * (b + 1) + a + 1];
     }
     template <int C, int F> __device__ __forceinline__ double fv(SField<F> q, int a, int b, int c) const

@@ -287,7 +287,7 @@ __global__ __launch_bounds__(FT) void k_flow_phase(BoxList L, FArgs A)
         double rg[7][27];
         const double *const src[7] = {A.phi, A.u, A.v, A.w, A.a[0], A.a[1], A.a[2]};
         stage_regs<7>(A.G, t, src, rg);
-        r = acdi_cell(StageAcc<0>(A.G, t.i, t.j, t.k, nullptr, 0, rg), SField<0>{}, SVec<1>{}, SVec<4>{});
+        r = acdi_cell(StageAcc<0>(A.G, t.i, t.j, t.k, nullptr, 0, 0, 0, rg), SField<0>{}, SVec<1>{}, SVec<4>{});
     } else {
         const PVel vel{A.u, A.v, A.w};
         const PVec av{A.a[0], A.a[1], A.a[2]};
@@ -321,8 +321,8 @@ __device__ __forceinline__ double mom_rhs(const FArgs &A, const X &x, const FTil
                                           const AV &a)
 {
     const int s = C == 0 ? t.i : (C == 1 ? t.j : t.k);
-    // a branch, not a select: it keeps the three components apart (merged,
-    // the interior kernel takes 160 VGPRs, 3 waves per SIMD instead of 4)
+    // a branch, not a select: it keeps the three components apart (merged, one
+    // workgroup per tile took 160 registers instead of 126)
     return wallf(A.G, C, s) ? 0.0 : mom_face<C>(x, A.P, phi, kap, vel, a);
 }
 
@@ -349,68 +349,75 @@ __device__ __forceinline__ int stage_idx(const FGrid &G, int d, int s)
     return t < 0 ? 0 : (t < n ? t : n - 1);
 }
 
-// Copies u, v, w and phi over the tile of (i0, j0, k) and its one-cell halo
-// into the stage: every load of a thread is issued before its first LDS
-// store.  FAST: interior tiles, where a halo index leaves the grid only
-// across a periodic direction and wraps by one period (the tile plan has no
-// interior box when a periodic direction is shorter than the tile and halo).
-// Otherwise the stage takes the values the wall rules give (face components
-// 0 on and beyond their own walls, minus the adjacent value across another),
-// so the stencils read it as they read an interior tile's.
-template <bool FAST> __device__ __forceinline__ void stage_fields(const FArgs &A, int i0, int j0, int k, double *st)
-{
-    constexpr int NR = (SFLD + FT - 1) / FT;
-    const FGrid &G = A.G;
-    const int nx = G.n[0], ny = G.n[1], nz = G.n[2];
-    const double *src[SNF] = {A.u, A.v, A.w, A.phi};
-    size_t g[NR];
-    double sg[3][FAST ? 1 : NR];
+// The thread's cells of a stage plane: u, v, w and phi over the tile of (i0,
+// j0) and its one-cell halo.  FAST: interior tiles, where a halo index leaves
+// the grid only across a periodic direction and wraps by one period (the tile
+// plan has no interior box when a periodic direction is shorter than the tile
+// and halo).  Otherwise the stage takes the values the wall rules give (face
+// components 0 on and beyond their own walls, minus the adjacent value across
+// another), so the stencils read it as they read an interior tile's.  A
+// plane's address is uniform over the workgroup and the offsets in it (32
+// bits, in bytes) are the same for every plane and field.
+constexpr int SNR2 = (SPL + FT - 1) / FT;
+template <bool FAST> struct StagePlane {
+    uint32_t off[SNR2];
+    bool out[2][SNR2], own[2][SNR2]; // outside a wall direction; on or beyond the walls of the direction's own faces
+    __device__ __forceinline__ StagePlane(const FGrid &G, int i0, int j0)
+    {
+        const int nx = G.n[0], ny = G.n[1];
 #pragma unroll
-    for (int q = 0; q < NR; ++q) {
-        int e = threadIdx.x + q * FT;
-        e = e < SFLD ? e : SFLD - 1;
-        const int kk = e / SPL, r = e - kk * SPL;
-        const int jj = r / SLX, ii = r - jj * SLX;
-        int gi = i0 - 1 + ii, gj = j0 - 1 + jj, gk = k - 1 + kk;
-        if constexpr (FAST) {
-            gi = gi < 0 ? gi + nx : (gi >= nx ? gi - nx : gi);
-            gj = gj < 0 ? gj + ny : (gj >= ny ? gj - ny : gj);
-            gk = gk < 0 ? gk + nz : (gk >= nz ? gk - nz : gk);
-        } else {
-            const int o[3] = {gi, gj, gk};
-            bool out[3], own[3]; // outside a wall direction; on or beyond the walls of the direction's own faces
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                out[d] = !G.per[d] && (o[d] < 0 || o[d] >= G.n[d]);
-                own[d] = !G.per[d] && (o[d] < 0 || o[d] >= G.n[d] - 1);
+        for (int q = 0; q < SNR2; ++q) {
+            int e = threadIdx.x + q * FT;
+            e = e < SPL ? e : SPL - 1;
+            const int jj = e / SLX, ii = e - jj * SLX;
+            int gi = i0 - 1 + ii, gj = j0 - 1 + jj;
+            if constexpr (FAST) {
+                gi = gi < 0 ? gi + nx : (gi >= nx ? gi - nx : gi);
+                gj = gj < 0 ? gj + ny : (gj >= ny ? gj - ny : gj);
+            } else {
+                out[0][q] = !G.per[0] && (gi < 0 || gi >= nx);
+                own[0][q] = !G.per[0] && (gi < 0 || gi >= nx - 1);
+                out[1][q] = !G.per[1] && (gj < 0 || gj >= ny);
+                own[1][q] = !G.per[1] && (gj < 0 || gj >= ny - 1);
+                gi = stage_idx(G, 0, gi);
+                gj = stage_idx(G, 1, gj);
             }
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const bool neg = out[(c + 1) % 3] != out[(c + 2) % 3];
-                sg[c][q] = own[c] ? 0.0 : (neg ? -1.0 : 1.0);
-            }
-            gi = stage_idx(G, 0, gi);
-            gj = stage_idx(G, 1, gj);
-            gk = stage_idx(G, 2, gk);
+            off[q] = ((uint32_t)gj * nx + gi) * 8u;
         }
-        g[q] = ((size_t)gk * ny + gj) * nx + gi;
     }
-    double v[SNF][NR];
+    // plane k from memory, into the registers v
+    __device__ __forceinline__ void load(const FArgs &A, int k, double (&v)[SNF][SNR2]) const
+    {
+        const FGrid &G = A.G;
+        const double *const src[SNF] = {A.u, A.v, A.w, A.phi};
+        const size_t o = (size_t)stage_idx(G, 2, k) * ((size_t)G.n[0] * G.n[1]);
 #pragma unroll
-    for (int f = 0; f < SNF; ++f)
+        for (int f = 0; f < SNF; ++f)
 #pragma unroll
-        for (int q = 0; q < NR; ++q) v[f][q] = src[f][g[q]];
+            for (int q = 0; q < SNR2; ++q) v[f][q] = ldo(src[f] + o, off[q]);
+    }
+    // and from there into the stage plane at st
+    __device__ __forceinline__ void store(const FGrid &G, int k, const double (&v)[SNF][SNR2], double *st) const
+    {
+        const bool outz = !FAST && !G.per[2] && (k < 0 || k >= G.n[2]);
+        const bool ownz = !FAST && !G.per[2] && (k < 0 || k >= G.n[2] - 1);
 #pragma unroll
-    for (int f = 0; f < SNF; ++f)
+        for (int f = 0; f < SNF; ++f)
 #pragma unroll
-        for (int q = 0; q < NR; ++q) {
-            const int e = threadIdx.x + q * FT;
-            if constexpr (!FAST) {
-                if (f < 3) v[f][q] = sg[f][q] == 0.0 ? 0.0 : sg[f][q] * v[f][q];
+            for (int q = 0; q < SNR2; ++q) {
+                const int e = threadIdx.x + q * FT;
+                double x = v[f][q];
+                if constexpr (!FAST) {
+                    if (f < 3) {
+                        const bool zero = f == 0 ? own[0][q] : (f == 1 ? own[1][q] : ownz);
+                        const bool neg = f == 0 ? out[1][q] != outz : (f == 1 ? outz != out[0][q] : out[0][q] != out[1][q]);
+                        x = zero ? 0.0 : (neg ? -x : x);
+                    }
+                }
+                if (e < SPL) st[f * SFLD + e] = x;
             }
-            if (e < SFLD) st[f * SFLD + e] = v[f][q];
-        }
-}
+    }
+};
 
 // The register stage of a tile along the walls: a_x, a_y, a_z (0 beyond
 // their own walls; on them the flux kernel stored 0) and kappa (the adjacent
@@ -438,42 +445,49 @@ __device__ __forceinline__ void stage_regs_wall(const FArgs &A, const FTile &t, 
         }
 }
 
-// Momentum right-hand side of the three components (all loads before any
-// store); with u*, the substep's predictor; with p*, the extrapolated
-// pressure.  Tiles read u, v, w and phi (about two thirds of the stencil's
-// neighbour values) from a stage in LDS that the workgroup fills with one
-// round of loads: read from memory one by one, in the rounds the compiler's
-// schedule allowed, they left the kernel waiting on memory latency.  The
-// tiles along the walls run the same code on a stage that holds what the
-// wall rules give (144 x 54 x 50 in a closed box: 85 us with the rules
-// applied at every access, 26 with the stage).  (One kernel per component
-// took 13 % longer in all.)  With PH
-// the kernel also takes the phase field's right-hand side and update (the
-// substep), whose stencil reads only values the momentum stages already
-// hold: a separate phase pass read phi, u, v, w and a again.
-template <bool PH> __device__ __forceinline__ void momentum_body(const BoxList &L, const FArgs &A)
+// Momentum right-hand side of the three components (all loads of a plane
+// before any store); with u*, the substep's predictor; with p*, the
+// extrapolated pressure.  With PH also the phase field's right-hand side and
+// update (the substep), whose stencil reads only values the stages already
+// hold.
+// A workgroup marches its tile through a chunk of planes with three planes of
+// u, v, w and phi (tile and halo) in LDS, so a plane is fetched once per
+// chunk and not by the three tiles that read it: with one workgroup per tile
+// and plane a wave issued 62 vector memory instructions and the substep's
+// pass took 7.2 ms at 512^3; 5.9 here, of which the 24 fields it moves take
+// 5.0 at copy rate (taking a fifth of the arithmetic out of the former
+// changed nothing).  At 144 x 54 x 50 in a closed box 33 us either way.
+// The tiles along the walls run the same code on a stage that holds what the
+// wall rules give (26 us against 85 with the rules applied at every access).
+template <bool PH, bool FAST>
+__device__ __forceinline__ void momentum_march(const FArgs &A, FTile t, int ke, double *st, unsigned long long &key)
 {
-    __shared__ double st[SNF * SFLD];
-    const BoxPick p = box_pick(L);
-    const FTile t = btile(A.G, p.b, p.w);
-    unsigned long long key = ~0ull;
-    // hu, hv, hw (and hphi) are read and written in place: each thread
-    // reads and writes only its own cell
-    if (t.valid) { // uniform over the workgroup, as p.fast
-        const int tx = threadIdx.x % FTI, ty = threadIdx.x / FTI;
-        // register stage: issued with the LDS stage's loads, before the
-        // barrier (threads past the grid read their clamped cell)
-        double rg[SNR][27];
-        if (p.fast) {
-            stage_fields<true>(A, t.i - tx, t.j - ty, t.k, st);
+    const int tx = threadIdx.x % FTI, ty = threadIdx.x / FTI, l = (ty + 1) * SLX + tx + 1;
+    const StagePlane<FAST> sp(A.G, t.i - tx, t.j - ty);
+    int s0 = 1; // slot of plane k; the planes below and above in the ones before and after it
+    {
+        double v0[SNF][SNR2], v1[SNF][SNR2];
+        sp.load(A, t.k - 1, v0);
+        sp.load(A, t.k, v1);
+        sp.store(A.G, t.k - 1, v0, st);
+        sp.store(A.G, t.k, v1, st + SPL);
+    }
+#pragma unroll 1
+    for (; t.k < ke; ++t.k) {
+        // nothing computed from the column is kept from plane to plane (220
+        // registers otherwise, two waves per SIMD; 164 so, three)
+        asm volatile("" : "+v"(t.i), "+v"(t.j));
+        const int sm = s0 == 0 ? 2 : s0 - 1, su = s0 == 2 ? 0 : s0 + 1;
+        double v[SNF][SNR2], rg[SNR][27];
+        sp.load(A, t.k + 1, v);
+        if constexpr (FAST) {
             const double *const rsrc[SNR] = {A.a[0], A.a[1], A.a[2], A.kap};
             stage_regs<SNR>(A.G, t, rsrc, rg);
         } else {
-            stage_fields<false>(A, t.i - tx, t.j - ty, t.k, st);
             stage_regs_wall(A, t, rg);
         }
         // the cell's previous right-hand sides and pressures, loaded with
-        // the stages
+        // the stages (threads past the grid read a clamped cell)
         const size_t cc = at(A.G, t.act ? t.i : A.G.n[0] - 1, t.act ? t.j : A.G.n[1] - 1, t.k);
         double old[3] = {0.0, 0.0, 0.0}, pp1 = 0.0, pp2 = 0.0, oldp = 0.0;
         if (!A.first) {
@@ -486,9 +500,10 @@ template <bool PH> __device__ __forceinline__ void momentum_body(const BoxList &
             pp1 = own(A.p1 + cc);
             pp2 = own(A.p2 + cc);
         }
+        sp.store(A.G, t.k + 1, v, st + su * SPL);
         __syncthreads();
         if (t.act) {
-            const StageAcc<SNF> x(A.G, t.i, t.j, t.k, st, SPL + (ty + 1) * SLX + tx + 1, rg);
+            const StageAcc<SNF> x(A.G, t.i, t.j, t.k, st, sm * SPL + l, s0 * SPL + l, su * SPL + l, rg);
             const SVel vel;
             const SVec<4> av;
             const double m0 = mom_rhs<0>(A, x, t, vel, SField<3>{}, SField<7>{}, av);
@@ -498,8 +513,29 @@ template <bool PH> __device__ __forceinline__ void momentum_body(const BoxList &
             mom_put<1>(A, t, cc, m1, old[1], x.cv(SField<1>{}, 0, 0, 0), A.hv, A.us[1]);
             mom_put<2>(A, t, cc, m2, old[2], x.cv(SField<2>{}, 0, 0, 0), A.hw, A.us[2]);
             if (A.pstar) put(A.pstar + cc, (1.0 + A.r) * pp1 - A.r * pp2);
-            if constexpr (PH) phase_put(A, cc, acdi_cell(x, SField<3>{}, vel, av), x.cv(SField<3>{}, 0, 0, 0), oldp, key);
+            if constexpr (PH) {
+                unsigned long long q;
+                phase_put(A, cc, acdi_cell(x, SField<3>{}, vel, av), x.cv(SField<3>{}, 0, 0, 0), oldp, q);
+                key = q < key ? q : key;
+            }
         }
+        __syncthreads(); // the plane below gives its place to the one after next
+        s0 = su;
+    }
+}
+
+template <bool PH> __device__ __forceinline__ void momentum_body(const BoxList &L, const FArgs &A)
+{
+    __shared__ double st[SNF * SFLD];
+    const BoxPick p = box_pick(L);
+    int ke;
+    const FTile t = bchunk(A.G, L, p, ke);
+    unsigned long long key = ~0ull;
+    // hu, hv, hw (and hphi) are read and written in place: each thread
+    // reads and writes only its own cells
+    if (t.valid) { // uniform over the workgroup, as p.fast
+        if (p.fast) momentum_march<PH, true>(A, t, ke, st, key);
+        else momentum_march<PH, false>(A, t, ke, st, key);
     }
     if constexpr (PH) key_to_slot(key, A.rho_part + p.slot);
 }
@@ -559,21 +595,40 @@ hipError_t launch_phase(const FArgs &A, const TilePlan &tp, hipStream_t s)
 {
     return FLOW_LAUNCH_PLAN(tp, k_flow_phase, s, A);
 }
+// The momentum launch: chunks of planes of every box.  Rounds of workgroups
+// (four per CU) times the planes each takes, two to start, is least; 32
+// planes at most (512^3: 6.04, 5.96, 5.85, 5.91 and 6.13 ms with 8, 16, 32,
+// 64 and 128; 144 x 54 x 50: 39, 37, 34 and 41 us with 1, 2, 3 and 4).
+static BoxList momentum_list(const TilePlan &tp)
+{
+    const BoxList L = box_list(tp, true, true);
+    int best = 1;
+    long cost = -1;
+    for (int c = 1; c <= 32; ++c) {
+        const long t = (box_chunks(L, c).grid + 1023L) / 1024 * (c + 2);
+        if (cost < 0 || t < cost) { cost = t; best = c; }
+    }
+    return box_chunks(L, best);
+}
 hipError_t launch_momentum(const FArgs &A, const TilePlan &tp, hipStream_t s)
 {
-    return FLOW_LAUNCH_PLAN(tp, k_flow_momentum, s, A);
+    const BoxList L = momentum_list(tp);
+    hipLaunchKernelGGL(k_flow_momentum, dim3(L.grid), dim3(FT), 0, s, L, A);
+    return hipGetLastError();
 }
 hipError_t launch_momentum_phase(const FArgs &A, const TilePlan &tp, hipStream_t s)
 {
     if (!A.phi_out || !A.hphi || !A.rho_new) return hipErrorInvalidValue;
-    hipError_t e = FLOW_LAUNCH_PLAN(tp, k_flow_mom_phase, s, A);
+    const BoxList L = momentum_list(tp);
+    hipLaunchKernelGGL(k_flow_mom_phase, dim3(L.grid), dim3(FT), 0, s, L, A);
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // Up to 16 keys per thread one workgroup takes them all; more (4 million
     // cells and up) in two levels.  The result goes to host memory: clearing
     // a key, minima by atomics and a copy of it took two more steps of the
     // stream's chain and the copy's wait.
     const unsigned long long *part = A.rho_part;
-    int n = tp.nslots;
+    int n = L.grid; // at most tp.nslots
     if (n > 16 * MINT) {
         hipLaunchKernelGGL(k_flow_min, dim3(MINWG), dim3(MINT), 0, s, part, n, A.rho_part + n);
         e = hipGetLastError();

@@ -151,6 +151,7 @@ struct BoxList {
     int fast; // box 0 is the interior box
     TileBox box[MAXBOX];
     int slot0[MAXBOX], first[MAXBOX];
+    int ck, kend[MAXBOX]; // a list in chunks of ck planes: box[q].nk counts chunks, kend[q] is the box's last plane + 1
 };
 
 // The interior box and / or the boxes along the walls of a plan, as one
@@ -172,21 +173,58 @@ inline BoxList box_list(const TilePlan &p, bool interior, bool walls)
     return L;
 }
 
+// The list with a workgroup per chunk of ck planes of a tile, for kernels
+// that march in z; slots in the order of the workgroups (no more than before).
+inline BoxList box_chunks(BoxList L, int ck)
+{
+    L.ck = ck;
+    L.grid = 0;
+    for (int q = 0; q < L.n; ++q) {
+        L.kend[q] = L.box[q].k0 + L.box[q].nk;
+        L.box[q].nk = (L.box[q].nk + ck - 1) / ck;
+        L.slot0[q] = L.first[q] = L.grid;
+        L.grid += box_grid(L.box[q]);
+    }
+    return L;
+}
+
 // the box of this workgroup, its number in the box and its slot
 struct BoxPick {
     TileBox b;
     unsigned w;
     int slot;
     bool fast;
+    int kend;
 };
 __device__ __forceinline__ BoxPick box_pick(const BoxList &L)
 {
-    BoxPick p{L.box[0], blockIdx.x, L.slot0[0] + (int)blockIdx.x, L.fast != 0};
+    BoxPick p{L.box[0], blockIdx.x, L.slot0[0] + (int)blockIdx.x, L.fast != 0, L.kend[0]};
 #pragma unroll
     for (int q = 1; q < MAXBOX; ++q)
         if (q < L.n && (int)blockIdx.x >= L.first[q])
-            p = BoxPick{L.box[q], blockIdx.x - L.first[q], L.slot0[q] + (int)blockIdx.x - L.first[q], false};
+            p = BoxPick{L.box[q], blockIdx.x - L.first[q], L.slot0[q] + (int)blockIdx.x - L.first[q], false, L.kend[q]};
     return p;
+}
+
+// The thread's column in a list in chunks and its planes [k, ke): x tiles
+// fastest, then y tiles, then chunks, so the tiles an XCD runs at once are
+// neighbours in x and y on the same planes.
+__device__ __forceinline__ FTile bchunk(const FGrid &G, const BoxList &L, const BoxPick &p, int &ke)
+{
+    const int nxy = p.b.nit * p.b.njt, n = nxy * p.b.nk, per = (n + 7) >> 3;
+    const int t = (int)(p.w & 7) * per + (int)(p.w >> 3);
+    FTile c;
+    c.act = false;
+    c.valid = t < n && (int)(p.w >> 3) < per;
+    c.i = c.j = c.k = ke = 0;
+    if (!c.valid) return c;
+    const int ch = t / nxy, rem = t - ch * nxy, jt = rem / p.b.nit;
+    c.k = p.b.k0 + ch * L.ck;
+    ke = c.k + L.ck < p.kend ? c.k + L.ck : p.kend;
+    c.i = (p.b.it0 + rem - jt * p.b.nit) * FTI + (threadIdx.x % FTI);
+    c.j = (p.b.jt0 + jt) * FTJ + (threadIdx.x / FTI);
+    c.act = c.i < G.n[0] && c.j < G.n[1];
+    return c;
 }
 
 // the thread's cell in workgroup w of box b (act false past the box or the grid)
@@ -208,18 +246,31 @@ __device__ __forceinline__ FTile btile(const FGrid &G, const TileBox &b, unsigne
     return c;
 }
 
+// the value `off` bytes into a plane whose address is uniform over the wave
+__device__ __forceinline__ double ldo(const double *plane, uint32_t off)
+{
+    return *(const double *)((const char *)plane + off);
+}
+
 // register stage of the listed fields: each thread's 3 x 3 x 3 neighbourhood
 // (loads whose values no stencil reads are removed by the compiler), all
-// issued before the first use; threads past the grid read a clamped cell
+// issued before the first use; threads past the grid read a clamped cell.
+// Plane bases are uniform, offsets in a plane 32 bits.
 template <int N>
 __device__ __forceinline__ void stage_regs(const FGrid &G, const FTile &t, const double *const (&src)[N],
                                            double (&rg)[N][27])
 {
-    const Fast f(G, t.act ? t.i : G.n[0] - 1, t.act ? t.j : G.n[1] - 1, t.k);
+    const int nx = G.n[0], ny = G.n[1], nz = G.n[2];
+    const int i = t.act ? t.i : nx - 1, j = t.act ? t.j : ny - 1, k = t.k;
+    const int x[3] = {i == 0 ? nx - 1 : i - 1, i, i == nx - 1 ? 0 : i + 1};
+    const int y[3] = {j == 0 ? ny - 1 : j - 1, j, j == ny - 1 ? 0 : j + 1};
+    const int z[3] = {k == 0 ? nz - 1 : k - 1, k, k == nz - 1 ? 0 : k + 1};
 #pragma unroll
     for (int q = 0; q < N; ++q)
 #pragma unroll
-        for (int n = 0; n < 27; ++n) rg[q][n] = src[q][f.idx(n % 3 - 1, (n / 3) % 3 - 1, n / 9 - 1)];
+        for (int n = 0; n < 27; ++n)
+            rg[q][n] = ldo(src[q] + (size_t)z[n / 9] * ((size_t)nx * ny),
+                           ((uint32_t)y[(n / 3) % 3] * nx + x[n % 3]) * 8u);
 }
 
 // Launches a kernel, which takes (box list, args...), on every box of a plan.
