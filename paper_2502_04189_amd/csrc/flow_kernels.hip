@@ -1,7 +1,8 @@
 // flow_kernels.hip -- kernels of the Runge-Kutta substep around the pressure
 // correction: normals, regularization flux and curvature, phase-field
-// update, momentum predictor.  One thread per cell on the plane tiles of
-// flow_tile.hpp, interior tiles on code without wall rules.
+// update, momentum predictor, on the tiles of flow_tile.hpp: the flux of the
+// interior box and the momentum pass march in z, the others take one thread
+// per cell; interior tiles on code without wall rules.
 #include <algorithm>
 
 #include "flow_launch.hpp"

@@ -4,7 +4,8 @@
 //
 // The tiles of a grid are split into boxes (ranges of x tiles, y tiles and
 // planes): one interior box whose stencils reach no wall, and up to six
-// boxes around it.  A kernel takes all of them in one launch and branches,
+// boxes around it.  A kernel takes all of them in one launch (the flux two:
+// its wall tiles read normals the interior ones store) and branches,
 // uniformly over the workgroup, to code on the interior accessor or on the
 // wall rules.  Within a launch consecutive workgroups go to different XCDs,
 // so XCD x gets a contiguous range of a box's tiles in the order below.
