@@ -12,8 +12,10 @@
 //   S1 "y-columns": ((k*NL + l)*YS + j)   one (k,l) column contiguous in j/m
 //   S2 "z-lines"  : ((l*NY + m)*ZS + k)   one (l,m) line contiguous in k
 // with NL = nx/2 + 1 half-spectrum x modes, and YS, ZS = ny, nz rounded up
-// to whole 128-byte lines, so that the corner turns' segments are aligned
-// (what lies between is neither written nor used).
+// to whole 128-byte lines, so that the corner turns' segments are aligned.
+// What lies between never enters a result: in S1 it is neither written nor
+// read, in S2 the z solve carries it along (it reads whole lines and stores
+// copies of a line's last level there).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -131,6 +133,17 @@ __host__ __device__ inline int div_wgs(const Dom &d)
     const int v = (d.ny * d.nz + NT / 64 - 1) / (NT / 64);
     return v > 1024 ? 1024 : v;
 }
+// LDS slot of level k of line `line` of a z tile (line stride ls, one spare
+// slot per 16 elements)
+__host__ __device__ inline int z_slot(int line, int k, int ls)
+{
+    const int e = line * ls + k;
+    return e + (e >> 4);
+}
+// The slot that element k of a z-line in S2 (k < zs) is stored from: the
+// padding past nz takes the line's last level.  The waves of a z workgroup
+// are not synchronized, so a wave touches the slots of its own lines only.
+__host__ __device__ inline int z_out_slot(int line, int k, int ls, int nz) { return z_slot(line, k < nz ? k : nz - 1, ls); }
 // workgroups of the reduction of those slots (pass_xmax), at most XMAX_WG
 __host__ __device__ inline int xmax_wgs(const Dom &d)
 {

@@ -918,17 +918,18 @@ __device__ __forceinline__ void pass_z(const Dom &d, int tile, char *smem)
     const int wlines = min(lpw, nlin - wl0);
     if (wlines <= 0) return;
     const int wb = wl0 * zs, wn = wlines * zs;   // element range of the wave in S2
-    // padded LDS index: one spare slot per 16 elements
-#define ZP(e) ((e) + ((e) >> 4))
-    // element e of the wave's lines -> its place in LDS (-1: beyond the line)
-    auto place = [&](int e) {
-        const int line = (int)fdiv((uint32_t)e, d.dzs), k = e - line * zs;
-        return k < nz ? ZP((wl0 + line) * LS + k) : -1;
+    // element e of the wave's lines: line of the workgroup, level (from nz on
+    // padding, not staged)
+    auto line_of = [&](int e, int &k) {
+        const int line = (int)fdiv((uint32_t)e, d.dzs);
+        k = e - line * zs;
+        return wl0 + line;
     };
     staged_copy_t<64, 8, C>(lane, wn, [&](int e) { return s2[gbase + wb + e]; },
                             [&](int e, C v) {
-                                const int q = place(e);
-                                if (q >= 0) buf[q] = v;
+                                int k;
+                                const int line = line_of(e, k);
+                                if (k < nz) buf[z_slot(line, k, LS)] = v;
                             });
     wave_sync();
 
@@ -963,7 +964,7 @@ __device__ __forceinline__ void pass_z(const Dom &d, int tile, char *smem)
 #pragma unroll
         for (int s = 0; s < SMAX; ++s) {
             if (s < S) {
-                C v = buf[ZP(gls * LS + k0 + s)];
+                C v = buf[z_slot(gls, k0 + s, LS)];
                 y[s] = C{v.x * scale, v.y * scale};
                 if (FULL && CY == 2 && k0 + s >= nz) y[s] = C{T(0), T(0)};
             }
@@ -1095,7 +1096,7 @@ __device__ __forceinline__ void pass_z(const Dom &d, int tile, char *smem)
         if (active) {
 #pragma unroll
             for (int s = 0; s < SMAX; ++s)
-                if (s < S) buf[ZP(gl * LS + k0 + s)] = y[s];
+                if (s < S) buf[z_slot(gl, k0 + s, LS)] = y[s];
         }
     };
     using std::integral_constant;
@@ -1104,9 +1105,13 @@ __device__ __forceinline__ void pass_z(const Dom &d, int tile, char *smem)
     else if (full) solve(integral_constant<bool, true>{}, integral_constant<int, 2>{});
     else solve(integral_constant<bool, false>{}, integral_constant<int, 0>{});
     wave_sync();
-    staged_copy_t<64, 8, C>(lane, wn, [&](int e) { return buf[max(place(e), 0)]; },
-                            [&](int e, C v) { st_stream(s2 + gbase + wb + e, v); }); // past nz: any value
-#undef ZP
+    staged_copy_t<64, 8, C>(lane, wn,
+                            [&](int e) {
+                                int k;
+                                const int line = line_of(e, k);
+                                return buf[z_out_slot(line, k, LS, nz)];
+                            },
+                            [&](int e, C v) { st_stream(s2 + gbase + wb + e, v); });
 }
 
 // ------------------------------------------------------------------ xinv
