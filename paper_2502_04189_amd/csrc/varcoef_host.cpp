@@ -163,16 +163,22 @@ extern "C" pcx_status pcx_varcoef_project(pcx_varcoef V, double dt, double rho0,
     const flow::FGrid &G = V->G;
     const VRed &R = V->R;
     double *p = p_out;
+    int it = 0;
+    double res = 0.0;
+    auto nonfinite = [&]() {
+        if (iters) *iters = it;
+        if (relres) *relres = res;
+        return fail(PCX_ERR_NONFINITE, "residual norm is not finite");
+    };
     // r = -(D u*)/dt minus its mean; bnorm = its norm
     VCHK(launch_rhs(G, u, v, w, 1.0 / dt, V->r, R, s));
     VCHK(red_scal(R, MODE_MEAN, s));
     VCHK(launch_center(G, V->r, R, s));
     VCHK(red_scal(R, MODE_BNORM, s));
     VCHK(hipMemsetAsync(p, 0, V->ncell * sizeof(double), s));
-    double res = 0.0;
     pcx_status st = read_sc(V, S_RES, s, &res);
     if (st != PCX_OK) return st;
-    int it = 0;
+    if (!std::isfinite(res)) return nonfinite();
     if (res > 0.0) {
         // z = -rho0 L^-1 r (the solve; the factor is folded into the kernels)
         st = pcx_poisson_solve(V->plan, V->r, V->z, stream);
@@ -186,11 +192,7 @@ extern "C" pcx_status pcx_varcoef_project(pcx_varcoef V, double dt, double rho0,
             ++it;
             VCHK(hipStreamSynchronize(s));
             res = *(volatile double *)V->hres;
-            if (!std::isfinite(res)) {
-                if (iters) *iters = it;
-                if (relres) *relres = res;
-                return fail(PCX_ERR_NONFINITE, "residual norm is not finite");
-            }
+            if (!std::isfinite(res)) return nonfinite();
             if (res <= tol) break;
             // the solve ignores the residual's mean (it removes the singular
             // mode); the dot pass and the update take it off r

@@ -422,15 +422,17 @@ __global__ __launch_bounds__(RED_MAX) void k_vc_scal(VRed R, int mode, double *h
     case MODE_MEAN: sc[S_M] = a / sc[S_WTOT]; break;
     case MODE_BNORM:
         sc[S_BNORM] = sqrt(a);
-        sc[S_RES] = a > 0.0 ? 1.0 : 0.0;
+        sc[S_RES] = a > 0.0 && a < INFINITY ? 1.0 : a; // 0, or a norm that is not finite
         sc[S_DRIFT] = 0.0;
         break;
     case MODE_RZ: sc[S_RZN] = a; break;
     case MODE_RES: {
         const double m = a / sc[S_WTOT];
         sc[S_DRIFT] = m;
-        // sum dzf (r - m)^2 = sum dzf r^2 - m sum dzf r
-        const double res = sqrt(fmax(b - m * a, 0.0)) / sc[S_BNORM];
+        // sum dzf (r - m)^2 = sum dzf r^2 - m sum dzf r, below 0 by rounding
+        // only; NaN goes through (the host's stop test sees nothing else)
+        const double t = b - m * a;
+        const double res = sqrt(t < 0.0 ? 0.0 : t) / sc[S_BNORM];
         sc[S_RES] = res;
         if (host) __hip_atomic_store(host, res, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         break;

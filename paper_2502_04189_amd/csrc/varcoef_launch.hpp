@@ -17,7 +17,7 @@ enum { S_RZ, S_RZN, S_M, S_DRIFT, S_RES, S_BNORM, S_WTOT, S_PMEAN, NSC };
 // what red_scal makes of the two reduced sums (S0, S1)
 enum {
     MODE_MEAN,  // m = S0 / wtot
-    MODE_BNORM, // bnorm = sqrt(S0); res = 1 (0 when S0 = 0); drift = 0
+    MODE_BNORM, // bnorm = sqrt(S0); res = 1 (S0 itself when it is 0 or not finite); drift = 0
     MODE_RZ,    // rz = S0
     MODE_RES,   // drift = S0 / wtot; res = sqrt(S1 - drift S0) / bnorm
     MODE_PMEAN  // pmean = S0 / wtot
