@@ -12,7 +12,7 @@
 //   S1 "y-columns": ((k*NL + l)*YS + j)   one (k,l) column contiguous in j/m
 //   S2 "z-lines"  : ((l*NY + m)*ZS + k)   one (l,m) line contiguous in k
 // with NL = nx/2 + 1 half-spectrum x modes, and YS, ZS = ny, nz rounded up
-// to whole 128-byte lines, so that the corner turns' segments are aligned.
+// to whole 128-byte lines (ZS by the rule of z_stride), so that the corner turns' segments are aligned.
 // What lies between never enters a result: in S1 it is neither written nor
 // read, in S2 the z solve carries it along (it reads whole lines and stores
 // copies of a line's last level there).
@@ -132,6 +132,18 @@ __host__ __device__ inline int div_wgs(const Dom &d)
 {
     const int v = (d.ny * d.nz + NT / 64 - 1) / (NT / 64);
     return v > 1024 ? 1024 : v;
+}
+// Stride of the z-lines in S2 (zline: elements of 128 bytes): whole 128-byte
+// lines, but nz itself where they would be more than 1.5 nz, since the y
+// passes take the padding's columns along idle.  Steps of 512 x 512 x nz,
+// padded against not, FP64 with walls: nz = 2 103 and 83 us, 5 129 and 125,
+// 10 196 and 194, 12 208 and 203, 13 232 and 249, 17 (1.41 nz) 287 and 317,
+// 33 487 and 557; refined: 2 296 and 238, 5 322 and 279, 10 388 and 379, 17
+// (1.88 nz) 572 and 590 (periodic 426 and 423), 25 685 and 768.
+inline int z_stride(int nz, int zline)
+{
+    const int zs = (nz + zline - 1) / zline * zline;
+    return 2 * zs <= 3 * nz ? zs : nz;
 }
 // LDS slot of level k of line `line` of a z tile (line stride ls, one spare
 // slot per 16 elements)

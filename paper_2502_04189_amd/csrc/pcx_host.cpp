@@ -233,7 +233,7 @@ void make_domain(const pcx_grid &g, int prec, const Shapes &sh, const RadixChoic
     d.zlev = sh.smax;
     const int zline = prec == PREC_F64 ? 8 : 16; // 128 bytes of complex values
     d.ys = (ny + zline - 1) / zline * zline;
-    d.zs = (nz + zline - 1) / zline * zline;
+    d.zs = z_stride(nz, zline);
     d.dzs = mkdiv(d.zs);
     // marching stencils: TI x TJ cell tiles over chunks of ckc planes
     d.mth = sh.mth;
