@@ -143,7 +143,7 @@ static int pow2_floor(long v)
 // size), z lanes per line, marching workgroup size.  Corner-turn segments are
 // kept at 128 bytes (8 FP64 or 16 FP32 complex values).  The batched form runs
 // every pass in 256-thread workgroups.
-void choose_shapes(const pcx_grid &g, int prec, const TuneParams *tp, Shapes &sh, bool batch)
+void choose_shapes(const pcx_grid &g, int prec, const TuneParams *tp, Shapes &sh, bool batch, bool lone)
 {
     const int M = g.nx / 2;
     const size_t csz = prec == PREC_F64 ? 16 : 8;
@@ -188,6 +188,24 @@ void choose_shapes(const pcx_grid &g, int prec, const TuneParams *tp, Shapes &sh
     // general passes only)
     sh.xfix = !batch && M <= FXMAX && fplan(M).n ? fft_lines(M, (int)csz) : 0;
     sh.yfix = !batch && fplan(g.ny).n ? fft_lines(g.ny, (int)csz) : 0;
+    if (lone && prec == PREC_F32) {
+        // FP32 wall transforms of a grid that leaves most of the device idle
+        // take the general passes: their tiles are an eighth and less of the
+        // fixed plans' 4096 points, and a tile's own chain is all that counts.
+        // x forward and accumulate of a refined step with walls, fixed
+        // against general: 64 x 64 x 24 (12 tiles) 12.8 + 18.6 and 10.2 + 11.1
+        // us, 256 x 256 x 16 (128) 14.8 + 20.9 and 15.1 + 17.5, but the y
+        // passes of that (128) 26 and 42; y of 64 x 64 x 3 (3) 24 and 19.
+        // Periodic transforms and FP64 ones (half the points) are as fast or
+        // faster fixed, as are lengths whose general plan has several stages
+        // more (81 points: 25 %).
+        const int zline = 16, ys = (g.ny + zline - 1) / zline * zline, zs = z_stride(g.nz, zline);
+        auto few = [&](int n, long lines, int per_tile, int most) {
+            return (lines + per_tile - 1) / per_tile <= most && (int)default_radices(n).size() <= fplan(n).n + 1;
+        };
+        if (sh.xfix && g.bc_x != PCX_BC_PERIODIC && few(M, (long)ys * g.nz, sh.xfix, 64)) sh.xfix = 0;
+        if (sh.yfix && g.bc_y != PCX_BC_PERIODIC && few(g.ny, (long)nlx * zs, sh.yfix, 16)) sh.yfix = 0;
+    }
     if (sh.xfix) sh.xth = fft_threads(M, (int)csz);
     if (sh.yfix) sh.yth = fft_threads(g.ny, (int)csz);
 }
@@ -452,7 +470,7 @@ pcx_status plan_prepare(pcx_plan_s *P, const pcx_grid *grid, const pcx_options &
             cache.save(o.tune_cache);
         }
     }
-    choose_shapes(P->grid, P->prec, have ? &tp : nullptr, P->sh, false);
+    choose_shapes(P->grid, P->prec, have ? &tp : nullptr, P->sh, false, true);
     make_domain(P->grid, P->prec, P->sh, have ? &rc : nullptr, ht, P->dom);
     return PCX_OK;
 }

@@ -53,7 +53,8 @@ FastDiv mkdiv(uint32_t d);
 std::vector<int> default_radices(int n);
 void fill_fft(FftDesc &fd, int n, const std::vector<int> &rad);
 pcx_status validate_grid(const pcx_grid *g);
-void choose_shapes(const pcx_grid &g, int prec, const TuneParams *tp, Shapes &sh, bool batch);
+// lone: of a domain that has the device to itself
+void choose_shapes(const pcx_grid &g, int prec, const TuneParams *tp, Shapes &sh, bool batch, bool lone = false);
 void make_domain(const pcx_grid &g, int prec, const Shapes &sh, const RadixChoice *rc, HostTables &ht, Dom &d);
 void bind_tables(Dom &d, const HostTables &ht, char *base);
 pcx_status build_domain(const pcx_grid &g, int prec, const Shapes &sh, const RadixChoice *rc, DomTables &tb, Dom &d);

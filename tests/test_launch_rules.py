@@ -1,6 +1,7 @@
 """Host-side checks of the rules that choose strides, tiles and chunks of
 planes, by compiling and running tests/hostcheck/*_check.cpp against the
-library's own headers (host code only: no device call).  CPU only."""
+library's own headers and, where a rule is not in one, the library itself
+(host code only: no device call).  CPU only."""
 import os
 import subprocess
 
@@ -8,15 +9,17 @@ import pytest
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
+PKG = os.path.join(ROOT, "paper_2502_04189_amd")
+LINK = {"shapes": ["-L" + PKG, "-l:libpcx.so", "-Wl,-rpath," + PKG]}
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not available")
-@pytest.mark.parametrize("rule", ["z_stride"])
+@pytest.mark.parametrize("rule", ["z_stride", "shapes"])
 def test_rule(tmp_path, rule):
     exe = tmp_path / rule
     subprocess.check_call([HIPCC, "-O1", "-std=c++17", "-x", "hip", "--offload-arch=gfx950", "-I",
                            os.path.join(ROOT, "paper_2502_04189_amd", "csrc"), "-I", os.path.join(ROOT, "include"),
-                           os.path.join(HERE, "hostcheck", rule + "_check.cpp"), "-o", str(exe)])
+                           os.path.join(HERE, "hostcheck", rule + "_check.cpp"), "-o", str(exe)] + LINK.get(rule, []))
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and r.stdout.startswith("ok"), r.stdout + r.stderr
