@@ -28,8 +28,9 @@ struct pcx_flow_s {
     pcx_plan plan = nullptr;
     double *tab = nullptr;           // z metric tables (metric_tables)
     double *ws = nullptr;            // NWS fields
-    unsigned long long *key = nullptr, *dkey = nullptr; // minimum density key in host memory, host and device address
-    unsigned long long *part = nullptr; // per-workgroup minimum keys
+    // per-workgroup minimum keys, first-level ones, the minimum's where the
+    // plan has no host memory for it
+    unsigned long long *part = nullptr;
     size_t ncell = 0;
     double *psi, *n[3], *a[3], *kap, *rho_new, *pstar, *us[3];
 };
@@ -40,7 +41,6 @@ static void flow_free(pcx_flow F)
     if (F->plan) pcx_plan_destroy(F->plan);
     if (F->tab) (void)hipFree(F->tab);
     if (F->ws) (void)hipFree(F->ws);
-    if (F->key) (void)hipHostFree(F->key);
     if (F->part) (void)hipFree(F->part);
     delete F;
 }
@@ -77,9 +77,7 @@ extern "C" pcx_status pcx_flow_create(const pcx_grid *grid, const pcx_flow_param
     const std::vector<double> t = metric_tables(F->zf.data(), nz, grid->bc_z == PCX_BC_PERIODIC);
     F->ncell = (size_t)nx * ny * nz;
     if (hipMalloc(&F->tab, t.size() * sizeof(double)) != hipSuccess ||
-        hipMalloc(&F->ws, NWS * F->ncell * sizeof(double)) != hipSuccess ||
-        hipHostMalloc((void **)&F->key, sizeof(unsigned long long), hipHostMallocDefault) != hipSuccess ||
-        hipHostGetDevicePointer((void **)&F->dkey, F->key, 0) != hipSuccess) {
+        hipMalloc(&F->ws, NWS * F->ncell * sizeof(double)) != hipSuccess) {
         flow_free(F);
         return fail(PCX_ERR_NOMEM, "flow workspace allocation failed");
     }
@@ -102,7 +100,7 @@ extern "C" pcx_status pcx_flow_create(const pcx_grid *grid, const pcx_flow_param
     F->P = FParams{q.rho1, q.rho2, q.mu1, q.mu2, q.sigma, {q.gx, q.gy, q.gz}, q.gamma, q.eps, q.eps_s, 0.5 / q.eps};
     F->tp = tile_plan(G);
     F->tpn = tile_plan(G, 2);
-    if (hipMalloc(&F->part, ((size_t)F->tp.nslots + MINWG) * sizeof(unsigned long long)) != hipSuccess) {
+    if (hipMalloc(&F->part, ((size_t)F->tp.nslots + MINWG + 1) * sizeof(unsigned long long)) != hipSuccess) {
         flow_free(F);
         return fail(PCX_ERR_NOMEM, "flow workspace allocation failed");
     }
@@ -143,7 +141,6 @@ static FArgs base_args(pcx_flow F, const double *phi, const double *u, const dou
     }
     A.kap = F->kap;
     A.first = 1;
-    A.rho_min_key = F->dkey;
     A.rho_part = F->part;
     return A;
 }
@@ -216,9 +213,14 @@ static pcx_status predictor(pcx_flow F, int32_t sub, double Dt, const double *ph
     FCHK(launch_flux(A, F->tpn, s));
     // one pass: the momentum predictor and the phase update read the state at
     // the start of the substep only
+    unsigned long long *const words = plan_host_words(F->plan);
+    A.rho_min_key = words ? words + F->plan->owner_word() : F->part + F->tp.nslots + MINWG;
     FCHK(launch_momentum_phase(A, F->tp, s));
+    unsigned long long key = 0;
+    if (!words) FCHK(hipMemcpyAsync(&key, A.rho_min_key, sizeof(key), hipMemcpyDeviceToHost, s));
     FCHK(hipStreamSynchronize(s));
-    *rho0 = key_to_double(*(volatile unsigned long long *)F->key);
+    if (words) key = *(const volatile unsigned long long *)(F->plan->hrep + F->plan->owner_word());
+    *rho0 = key_to_double(key);
     if (!(*rho0 > 0.0) || !std::isfinite(*rho0)) return fail(PCX_ERR_NONFINITE, "minimum density is not positive and finite");
     *dt = (GA[sub - 1] + ZE[sub - 1]) * Dt;
     return PCX_OK;

@@ -18,7 +18,7 @@ struct FArgs {
     int first;                       // first substep: no previous right-hand side
     double *hphi, *hu, *hv, *hw;     // previous right-hand sides in, this substep's out
     double *phi_out, *us[3], *rho_new; // NULL: right-hand sides only
-    unsigned long long *rho_min_key; // host memory the device can write
+    unsigned long long *rho_min_key; // the minimum's key (in host memory the device can write, or the device's)
     unsigned long long *rho_part;    // one key per workgroup of the phase pass (TilePlan::nslots), then MINWG more
     const double *p1, *p2;           // pressures of the two previous substeps
     double r;

@@ -550,6 +550,20 @@ void plan_bind(pcx_plan_s *P, const HostTables &ht, char *tables, char *ws, cons
     P->lzs = lds_z(P->dom, P->prec);
 }
 
+unsigned long long *plan_host_words(pcx_plan_s *P)
+{
+    if (P->hrep_tried) return P->drep;
+    P->hrep_tried = true;
+    if (hipHostMalloc((void **)&P->hrep, (P->owner_word() + 1) * 8, hipHostMallocDefault) != hipSuccess) {
+        P->hrep = nullptr;
+        (void)hipGetLastError();
+    } else if (hipHostGetDevicePointer((void **)&P->drep, P->hrep, 0) != hipSuccess) {
+        P->drep = nullptr;
+        (void)hipGetLastError();
+    }
+    return P->drep;
+}
+
 } // namespace pcx
 
 extern "C" pcx_status pcx_plan_create(const pcx_grid *grid, const pcx_options *opts, pcx_plan *out)
@@ -588,11 +602,6 @@ extern "C" pcx_status pcx_plan_create(const pcx_grid *grid, const pcx_options *o
         return fail(PCX_ERR_NOMEM, "workspace allocation failed");
     }
     plan_bind(P, ht, (char *)P->tables.dev, (char *)P->ws, L);
-    if (hipHostMalloc((void **)&P->hrep, (NSTAT + (size_t)P->grid.nz) * 8, hipHostMallocDefault) != hipSuccess ||
-        hipHostGetDevicePointer((void **)&P->drep, P->hrep, 0) != hipSuccess) {
-        P->drep = nullptr;
-        (void)hipGetLastError();
-    }
     *out = P;
     return PCX_OK;
 }
@@ -810,18 +819,19 @@ extern "C" pcx_status pcx_step(pcx_plan P, double dt, double rho0, const double 
     std::vector<double> ps(P->grid.nz);
     if (!report) return correct();
     // the statistics, with sums also the plane sums of p, once the stream is done
+    unsigned long long *const words = plan_host_words(P);
     auto fetch = [&](bool sums) -> pcx_status {
         const double *q = sums ? p_out : nullptr;
         const int nxy = P->grid.nx * P->grid.ny;
-        if (P->drep) {
-            HIPCHK(launch_report(P->stats, q, nxy, P->grid.nz, P->drep, s));
+        if (words) {
+            HIPCHK(launch_report(P->stats, q, nxy, P->grid.nz, words, s));
         } else {
             if (sums) HIPCHK(launch_plane_sums(q, nxy, P->grid.nz, P->psum, s));
             HIPCHK(hipMemcpyAsync(h.data(), P->stats, NSTAT * 8, hipMemcpyDeviceToHost, s));
             if (sums) HIPCHK(hipMemcpyAsync(ps.data(), P->psum, ps.size() * 8, hipMemcpyDeviceToHost, s));
         }
         HIPCHK(hipStreamSynchronize(s));
-        if (P->drep) {
+        if (words) {
             std::memcpy(h.data(), P->hrep, NSTAT * 8);
             if (sums) std::memcpy(ps.data(), P->hrep + NSTAT, ps.size() * 8);
         }

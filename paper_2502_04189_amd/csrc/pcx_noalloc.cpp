@@ -103,5 +103,6 @@ extern "C" pcx_status pcx_step_noalloc(const pcx_grid *grid, const pcx_options *
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return fail(PCX_ERR_HIP, std::string("table upload: ") + hipGetErrorString(e));
     plan_bind(&P, ht, base, base + tab, L);
+    P.hrep_tried = true; // no host memory either: a report copies
     return pcx_step(&P, dt, rho0, rho, p_star, u_in, v_in, w_in, u_out, v_out, w_out, p_out, stream, report);
 }

@@ -84,6 +84,9 @@ WsLayout plan_layout(const pcx_plan_s *P);
 // The layout with columns and z-lines rounded up to whole 128-byte lines, or
 // without the rounding where it alone would take the plan beyond `most` bytes.
 WsLayout plan_layout_within(pcx_plan_s *P, size_t most);
+// The plan's words of host memory by their device address (host: hrep); NULL
+// where no such memory can be had: the caller copies from the device instead.
+unsigned long long *plan_host_words(pcx_plan_s *P);
 void plan_bind(pcx_plan_s *P, const HostTables &ht, char *tables, char *ws, const WsLayout &L);
 } // namespace pcx
 
@@ -102,8 +105,12 @@ struct pcx_plan_s {
     double *r = nullptr;
     double *psum = nullptr;
     // statistics and plane sums of a report in host memory, host and device
-    // address (NULL: no such memory, a report copies them)
+    // address, and one word more for the flow or the projection that owns the
+    // plan; allocated by the first call that reads it (plan_host_words: 15-25
+    // us, as much as the rest of a small plan's creation takes)
     unsigned long long *hrep = nullptr, *drep = nullptr;
+    bool hrep_tried = false;
+    size_t owner_word() const { return pcx::NSTAT + (size_t)grid.nz; }
     double *ppart = nullptr;
     double *xpart = nullptr;
     double *spart = nullptr;

@@ -24,7 +24,6 @@ struct pcx_varcoef_s {
     double *tab = nullptr; // z metric tables (metric_tables)
     double *ws = nullptr;  // r, z, d, q
     double *red = nullptr; // partials (operator, update, dot), scalars
-    double *hres = nullptr, *dres = nullptr; // the residual in host memory, host and device address
     size_t ncell = 0;
     double *r, *z, *d, *q;
     ATiles T;
@@ -38,7 +37,6 @@ static void vc_free(pcx_varcoef V)
     if (V->tab) (void)hipFree(V->tab);
     if (V->ws) (void)hipFree(V->ws);
     if (V->red) (void)hipFree(V->red);
-    if (V->hres) (void)hipHostFree(V->hres);
     delete V;
 }
 
@@ -87,9 +85,7 @@ extern "C" pcx_status pcx_varcoef_create(const pcx_grid *grid, const pcx_options
     const size_t nred = 3 * 2 * (size_t)RED_MAX + NSC;
     if (hipMalloc(&V->tab, t.size() * sizeof(double)) != hipSuccess ||
         hipMalloc(&V->ws, 4 * V->ncell * sizeof(double)) != hipSuccess ||
-        hipMalloc(&V->red, nred * sizeof(double)) != hipSuccess ||
-        hipHostMalloc((void **)&V->hres, sizeof(double), hipHostMallocDefault) != hipSuccess ||
-        hipHostGetDevicePointer((void **)&V->dres, V->hres, 0) != hipSuccess) {
+        hipMalloc(&V->red, nred * sizeof(double)) != hipSuccess) {
         vc_free(V);
         return fail(PCX_ERR_NOMEM, "projection workspace allocation failed");
     }
@@ -163,6 +159,9 @@ extern "C" pcx_status pcx_varcoef_project(pcx_varcoef V, double dt, double rho0,
     const flow::FGrid &G = V->G;
     const VRed &R = V->R;
     double *p = p_out;
+    // the iteration's residual goes to the plan's word of host memory
+    unsigned long long *const words = plan_host_words(V->plan);
+    double *const dres = words ? (double *)(words + V->plan->owner_word()) : nullptr;
     int it = 0;
     double res = 0.0;
     auto nonfinite = [&]() {
@@ -188,10 +187,14 @@ extern "C" pcx_status pcx_varcoef_project(pcx_varcoef V, double dt, double rho0,
         while (it < maxit) {
             VCHK(launch_apply(G, V->T, rho, V->d, V->q, -1.0, &V->RA, s));
             VCHK(launch_update(G, p, V->d, V->r, V->q, V->RA, R, s));
-            VCHK(red_scal(R, MODE_RES, s, V->dres));
+            VCHK(red_scal(R, MODE_RES, s, dres));
             ++it;
-            VCHK(hipStreamSynchronize(s));
-            res = *(volatile double *)V->hres;
+            if (dres) {
+                VCHK(hipStreamSynchronize(s));
+                res = *(const volatile double *)(V->plan->hrep + V->plan->owner_word());
+            } else if ((st = read_sc(V, S_RES, s, &res)) != PCX_OK) {
+                return st;
+            }
             if (!std::isfinite(res)) return nonfinite();
             if (res <= tol) break;
             // the solve ignores the residual's mean (it removes the singular

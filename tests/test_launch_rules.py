@@ -1,5 +1,5 @@
 """Host-side checks of the rules that choose strides, tiles and chunks of
-planes, by compiling and running tests/hostcheck/*_check.cpp against the
+planes, and of what the create calls do without pinned memory, by compiling and running tests/hostcheck/*_check.cpp against the
 library's own headers and, where a rule is not in one, the library itself
 (host code only: no device call).  CPU only."""
 import os
@@ -10,12 +10,13 @@ import pytest
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 PKG = os.path.join(ROOT, "paper_2502_04189_amd")
-LINK = {"shapes": ["-L" + PKG, "-l:libpcx.so", "-Wl,-rpath," + PKG]}
+LIB = ["-L" + PKG, "-l:libpcx.so", "-Wl,-rpath," + PKG]
+LINK = {"shapes": LIB, "no_pinned": LIB}
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not available")
-@pytest.mark.parametrize("rule", ["z_stride", "shapes"])
+@pytest.mark.parametrize("rule", ["z_stride", "shapes", "no_pinned"])
 def test_rule(tmp_path, rule):
     exe = tmp_path / rule
     subprocess.check_call([HIPCC, "-O1", "-std=c++17", "-x", "hip", "--offload-arch=gfx950", "-I",
