@@ -210,26 +210,6 @@ void choose_shapes(const pcx_grid &g, int prec, const TuneParams *tp, Shapes &sh
     if (sh.yfix) sh.yth = fft_threads(g.ny, (int)csz);
 }
 
-// Planes per chunk of a marching launch of txy tiles per plane that has the
-// device (256 CUs, occ workgroups each) to itself: a workgroup takes about
-// one memory latency per plane and three to start, so the launch takes
-// rounds x (planes + 3).  At 32^3 the correction takes 13 us in 1-plane
-// chunks against 45 in 16-plane ones, at 108 x 162 x 75 33 (8) against 50
-// (16), at 256^3 220 (64) against 238 (16); at 512^3 1.69 ms (128) against
-// 1.86 (16), all in this order.
-static int lone_chunk(int nz, long txy, int occ)
-{
-    int best = nz;
-    long cost = -1;
-    for (int n = 1; n <= nz; ++n) {
-        const int ckc = (nz + n - 1) / n;
-        const long wgs = txy * ((nz + ckc - 1) / ckc), rounds = (wgs + 256L * occ - 1) / (256L * occ);
-        const long c = rounds * (ckc + 3);
-        if (cost < 0 || c < cost) { cost = c; best = ckc; }
-    }
-    return best;
-}
-
 // Domain descriptor and the host image of its device tables (eigenvalues, z
 // coefficients, twiddles); the table pointers of d are bound by bind_tables
 // once the image sits in device memory.
@@ -267,7 +247,7 @@ void make_domain(const pcx_grid &g, int prec, const Shapes &sh, const RadixChoic
         m.cntj = (ny + m.ctj - 1) / m.ctj;
         if (sh.batch) m.ckc = nz; // whole columns: batch items stay large
         else if (sh.ckc[q] > 0) m.ckc = (nz + (nz + sh.ckc[q] - 1) / sh.ckc[q] - 1) / ((nz + sh.ckc[q] - 1) / sh.ckc[q]);
-        else m.ckc = lone_chunk(nz, (long)m.cnti * m.cntj, q == 0 ? 2 : 1);
+        else m.ckc = q == 0 ? march_chunk(nz, (long)m.cnti * m.cntj, 2, 64) : march_chunk(nz, (long)m.cnti * m.cntj, 1, nz);
         m.cnk = (nz + m.ckc - 1) / m.ckc;
         m.ntiles = m.cnti * m.cntj * m.cnk;
         m.dcti = mkdiv(m.cti);

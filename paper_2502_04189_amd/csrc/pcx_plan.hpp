@@ -53,6 +53,35 @@ FastDiv mkdiv(uint32_t d);
 std::vector<int> default_radices(int n);
 void fill_fft(FftDesc &fd, int n, const std::vector<int> &rad);
 pcx_status validate_grid(const pcx_grid *g);
+// Planes per chunk of a marching launch of txy tiles per plane that has the
+// device (256 CUs, occ workgroups each) to itself: a workgroup takes about
+// one memory latency per plane and three to start, so the launch takes
+// rounds x (planes + 3).  At 32^3 the correction takes 12 us in 1-plane
+// chunks against 46 in 16-plane ones, at 108 x 162 x 75 31 (7) against 49
+// (16), at 256^3 229 (64) against 239 (16); at 512^3 1.62-1.65 ms in one
+// chunk of 512 against 1.69 (128) and 1.83-1.85 (16).
+// Chunks of more than `most` planes are whole columns only, of up to 128
+// planes or in four rounds or more.  For the RHS and the residual `most` is
+// 64: the columns of a launch drift apart, read halos their neighbours' cache
+// lines no longer hold, and with few rounds nothing follows that would fill
+// the CUs that are done early.  RHS at 512^3 (512 tiles a plane, one round of
+// whole columns) 1.25-1.29 ms, in chunks of 128 1.22-1.29, of 64 1.21-1.23, of
+// 16 1.26-1.28; 768 x 512 x 384 1.53 (192) and 1.49-1.50 (64); whole columns at
+// 512 x 512 x 100 0.249 against 0.26 in two halves, at 1024 x 1024 x 512 (four
+// rounds) 5.1-5.2 against 5.1-5.5 (64).  The correction has no such loss.
+inline int march_chunk(int nz, long txy, int occ, int most)
+{
+    int best = nz;
+    long cost = -1;
+    for (int n = 1; n <= nz; ++n) {
+        const int ckc = (nz + n - 1) / n;
+        const long wgs = txy * ((nz + ckc - 1) / ckc), rounds = (wgs + 256L * occ - 1) / (256L * occ);
+        const long c = rounds * (ckc + 3);
+        if (ckc > most && (ckc < nz || (nz > 128 && rounds < 4))) continue;
+        if (cost < 0 || c < cost) { cost = c; best = ckc; }
+    }
+    return best;
+}
 // lone: of a domain that has the device to itself
 void choose_shapes(const pcx_grid &g, int prec, const TuneParams *tp, Shapes &sh, bool batch, bool lone = false);
 void make_domain(const pcx_grid &g, int prec, const Shapes &sh, const RadixChoice *rc, HostTables &ht, Dom &d);
