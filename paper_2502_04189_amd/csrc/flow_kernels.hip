@@ -455,7 +455,7 @@ __device__ __forceinline__ void stage_regs_wall(const FArgs &A, const FTile &t, 
 // u, v, w and phi (tile and halo) in LDS, so a plane is fetched once per
 // chunk and not by the three tiles that read it: with one workgroup per tile
 // and plane a wave issued 62 vector memory instructions and the substep's
-// pass took 7.2 ms at 512^3; 5.9 here, of which the 24 fields it moves take
+// pass took 7.2 ms at 512^3; 6.1-6.2 here, of which the 24 fields it moves take
 // 5.0 at copy rate (taking a fifth of the arithmetic out of the former
 // changed nothing).  At 144 x 54 x 50 in a closed box 33 us either way.
 // The tiles along the walls run the same code on a stage that holds what the
@@ -595,21 +595,6 @@ hipError_t launch_flux(const FArgs &A, const TilePlan &tp, hipStream_t s)
 hipError_t launch_phase(const FArgs &A, const TilePlan &tp, hipStream_t s)
 {
     return FLOW_LAUNCH_PLAN(tp, k_flow_phase, s, A);
-}
-// The momentum launch: chunks of planes of every box.  Rounds of workgroups
-// (four per CU) times the planes each takes, two to start, is least; 32
-// planes at most (512^3: 6.04, 5.96, 5.85, 5.91 and 6.13 ms with 8, 16, 32,
-// 64 and 128; 144 x 54 x 50: 39, 37, 34 and 41 us with 1, 2, 3 and 4).
-static BoxList momentum_list(const TilePlan &tp)
-{
-    const BoxList L = box_list(tp, true, true);
-    int best = 1;
-    long cost = -1;
-    for (int c = 1; c <= 32; ++c) {
-        const long t = (box_chunks(L, c).grid + 1023L) / 1024 * (c + 2);
-        if (cost < 0 || t < cost) { cost = t; best = c; }
-    }
-    return box_chunks(L, best);
 }
 hipError_t launch_momentum(const FArgs &A, const TilePlan &tp, hipStream_t s)
 {

@@ -144,8 +144,8 @@ __host__ __device__ inline void box_tile(const TileBox &b, long t, int &it, int 
 }
 
 // The boxes of one launch: workgroup first[q] + w is workgroup w of box q
-// and owns partial-result slot slot0[q] + w (every box's workgroups are a
-// multiple of 8, so w & 7 is the workgroup's XCD as well).
+// (every box's workgroups are a multiple of 8, so w & 7 is the workgroup's XCD
+// as well).
 constexpr int MAXBOX = 7;
 struct BoxList {
     int n, grid;
@@ -187,6 +187,27 @@ inline BoxList box_chunks(BoxList L, int ck)
         L.grid += box_grid(L.box[q]);
     }
     return L;
+}
+
+// The momentum launch: chunks of planes of every box.  Rounds of workgroups
+// (three per CU: the kernel takes 164 registers) times the planes each takes,
+// three to start, is least; of lengths whose last chunk is rarely a short one
+// and whose starts stay aligned.  Kernel times, chunks of 4, 8, 16, 17 and 32
+// planes: 512^3 walls in z 6.18 ms (16), 6.12 (17), 6.19 (32), periodic 6.19,
+// 6.36, 6.18; 256^3 815, 790, 781, 778, 785 us (10 planes 845); 128^3 106,
+// 107, 111, 117, 138 (9 planes 117); 512 x 512 x 64 878, 828, 808, 854, 817 (7
+// planes 880); 64^3 24, 41 and 21.6, 18.9 in chunks of 1 and 2; 144 x 54 x 50
+// 36, 34, 32 and 38 in 1, 2, 3 and 4.
+inline BoxList momentum_list(const TilePlan &tp)
+{
+    const BoxList L = box_list(tp, true, true);
+    int best = 1;
+    long cost = -1;
+    for (int c : {1, 2, 3, 4, 6, 8, 16, 32}) {
+        const long t = (box_chunks(L, c).grid + 767L) / 768 * (c + 3);
+        if (cost < 0 || t < cost) { cost = t; best = c; }
+    }
+    return box_chunks(L, best);
 }
 
 // the box of this workgroup, its number in the box and its slot
