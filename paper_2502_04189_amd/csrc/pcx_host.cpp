@@ -378,13 +378,7 @@ size_t lds_x_general(const Dom &d, int prec)
 }
 size_t lds_x(const Dom &d, int prec)
 {
-    if (d.xlines) {
-        // rows of 512 FP64 points: three tiles per CU, not the four there is
-        // room for (512^3, forward + inverse: 382 + 428 us with three, 398 +
-        // 437 with four, 428 + 441 with two)
-        const size_t b = fft_lds(d.M, prec == PREC_F64 ? 16 : 8);
-        return prec == PREC_F64 && d.M == 256 && b < 41 * 1024 ? 41 * 1024 : b;
-    }
+    if (d.xlines) return fft_lds(d.M, prec == PREC_F64 ? 16 : 8);
     return lds_x_general(d, prec);
 }
 size_t lds_y(const Dom &d, int prec)

@@ -11,12 +11,12 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 PKG = os.path.join(ROOT, "paper_2502_04189_amd")
 LIB = ["-L" + PKG, "-l:libpcx.so", "-Wl,-rpath," + PKG]
-LINK = {"shapes": LIB, "no_pinned": LIB}
+LINK = {"shapes": LIB, "no_pinned": LIB, "fft_lds": LIB}
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not available")
-@pytest.mark.parametrize("rule", ["z_stride", "shapes", "no_pinned", "march_chunk", "momentum_chunk"])
+@pytest.mark.parametrize("rule", ["z_stride", "shapes", "no_pinned", "march_chunk", "momentum_chunk", "fft_lds"])
 def test_rule(tmp_path, rule):
     exe = tmp_path / rule
     subprocess.check_call([HIPCC, "-O1", "-std=c++17", "-x", "hip", "--offload-arch=gfx950", "-I",
