@@ -105,11 +105,15 @@ __host__ __device__ constexpr size_t fft_lds(int n, int csz)
 // Waves per SIMD that as many tiles as LDS has room for make up, between 4
 // (128 registers) and 7 (72): a few lengths take some registers more than
 // that leaves, and with them a tile per CU less (972 points forward in x:
-// 84 instead of 80, one tile instead of two, 142 us instead of 103).
+// 84 instead of 80, one tile instead of two, 142 us instead of 103).  FP64
+// tiles that would have to do with 80 registers to run three or more at once
+// may take a tile less: 324 points, three tiles, spilled 1 (x inverse) and 3
+// (y inverse) registers; with two, 648 x 324 x 320 cells with walls, 518 -> 485
+// us y inverse, 311 -> 301 x inverse, periodic 212 -> 207 and 231 -> 230.
 __host__ __device__ constexpr int fft_waves(int n, int csz)
 {
     const int w = fft_threads(n, csz) / 64, t = (int)(160 * 1024 / fft_lds(n, csz));
-    const int e = (t * w + 3) / 4;
+    const int all = (t * w + 3) / 4, e = csz == 16 && t >= 3 && all >= 6 ? ((t - 1) * w + 3) / 4 : all;
     return n <= FSMALL || e < 4 ? 4 : (e > 7 ? 7 : e);
 }
 
