@@ -98,9 +98,6 @@ static std::vector<std::vector<int>> radix_variants(int n)
 }
 
 namespace {
-// items of a timed grouped launch, at least (see prep_group)
-constexpr long GFILL = 1024;
-
 struct Scratch {
     std::vector<void *> ptrs;
     ~Scratch()
@@ -133,7 +130,14 @@ pcx_status autotune_class(const pcx_grid &g, int prec, hipStream_t s, TuneParams
         if (hipMemcpy(fld[i], ones.data(), ncell * 8, hipMemcpyHostToDevice) != hipSuccess)
             return fail(PCX_ERR_HIP, "autotune scratch copy failed");
     }
-    void *s1 = sc.alloc((nspec / g.ny) * ((g.ny + 15) & ~15) * csz), *s2 = sc.alloc((nspec / g.nz) * ((g.nz + 15) & ~15) * csz);
+    const size_t s2_bytes = ((nspec / g.nz) * ((g.nz + 15) & ~15) * csz + 255) & ~(size_t)255;
+    int zcopies = grouped ? tune_z_copies(s2_bytes) : 1;
+    void *s1 = sc.alloc((nspec / g.ny) * ((g.ny + 15) & ~15) * csz), *s2 = sc.alloc(zcopies * s2_bytes);
+    if (!s2 && zcopies > 1) {
+        (void)hipGetLastError();
+        zcopies = 1;
+        s2 = sc.alloc(s2_bytes);
+    }
     double *f = (double *)sc.alloc(ncell * 8);
     double *rr = (double *)sc.alloc(ncell * 8);
     unsigned long long *stats = (unsigned long long *)sc.alloc(NSTAT * 8);
@@ -146,11 +150,12 @@ pcx_status autotune_class(const pcx_grid &g, int prec, hipStream_t s, TuneParams
     if (!s1 || !s2 || !f || !rr || !stats || !ppart || !xpart) return fail(PCX_ERR_NOMEM, "autotune scratch allocation failed");
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) return fail(PCX_ERR_HIP, "hipEventCreate");
-    // grouped launches (the batch's kernels): a one-entry domain table and an
-    // item list of every tile of the pass, as the batch builds them
-    Dom *ddom = (Dom *)sc.alloc(sizeof(Dom));
+    // grouped launches (the batch's kernels): a domain table and an item list
+    // of every tile of the pass (tune_items), as the batch builds them
+    Dom *ddom = (Dom *)sc.alloc(zcopies * sizeof(Dom));
     const size_t max_items = (size_t)std::max<long>({(long)g.ny * g.nz, (long)nlx * g.nz, (long)nlx * g.ny,
-                                                     (long)(ncell / 64 + 64), GFILL}) + 64;
+                                                     (long)(ncell / 64 + 64), GFILL,
+                                                     ((long)nlx * g.ny / 4 + 1) * zcopies}) + 64;
     GItem *ditems = (GItem *)sc.alloc(max_items * sizeof(GItem));
     if (!ddom || !ditems) return fail(PCX_ERR_NOMEM, "autotune scratch allocation failed");
     std::vector<GItem> hitems;
@@ -158,25 +163,20 @@ pcx_status autotune_class(const pcx_grid &g, int prec, hipStream_t s, TuneParams
     auto prep_group = [&](const Dom &d, int kind, GVariant &v, GArgs &a, size_t &lds) {
         const long t = group_tiles(d, kind);
         if (t <= 0 || (size_t)t > max_items) return false;
-        // A small domain's tiles leave most of the device idle, and the shape
-        // that spreads them best is not the one that does the least work per
-        // cell, which is what counts when a batch fills the device: the list
-        // is repeated up to GFILL items (equal values written twice at the
-        // same place; the z solve's scratch lines are solved again).
-        const long reps = std::max(1L, GFILL / t);
-        hitems.resize(t * reps);
-        for (long q = 0; q < t * reps; ++q) hitems[q] = GItem{0u, (uint32_t)(kind == PK_Z ? t - 1 - q % t : q % t)};
-        if (hipMemcpy(ddom, &d, sizeof(Dom), hipMemcpyHostToDevice) != hipSuccess) return false;
-        if (hipMemcpy(ditems, hitems.data(), t * reps * sizeof(GItem), hipMemcpyHostToDevice) != hipSuccess) return false;
+        hitems = tune_items(kind, t, zcopies);
+        if (hitems.size() > max_items) return false;
+        std::vector<Dom> hdom(kind == PK_Z ? zcopies : 1, d);
+        for (size_t c = 0; c < hdom.size(); ++c) hdom[c].s2 = (char *)s2 + c * s2_bytes;
+        if (hipMemcpy(ddom, hdom.data(), hdom.size() * sizeof(Dom), hipMemcpyHostToDevice) != hipSuccess) return false;
+        if (hipMemcpy(ditems, hitems.data(), hitems.size() * sizeof(GItem), hipMemcpyHostToDevice) != hipSuccess) return false;
         v = variant_of(d, kind);
-        a = GArgs{ddom, ditems, (int)(t * reps), 0};
+        a = GArgs{ddom, ditems, (int)hitems.size(), 0};
         lds = group_lds(d, kind, prec);
         return true;
     };
     // times of a candidate are per item, times the items of one pass
     auto per_pass = [&](const Dom &d, int kind, float t) {
-        const long n = group_tiles(d, kind);
-        return grouped ? t / (float)std::max(1L, GFILL / n) : t;
+        return grouped ? t * (float)group_tiles(d, kind) / (float)hitems.size() : t;
     };
     // launches of pass kinds k1 (and k2) of d, grouped or single-domain
     auto passes = [&](const Dom &d, size_t lx, size_t ly, size_t lz, int k1, int k2) {
@@ -290,9 +290,11 @@ pcx_status autotune_class(const pcx_grid &g, int prec, hipStream_t s, TuneParams
             }
         }
     }
-    // z solve
+    // z solve: the default lanes unless others are 2 % faster, more than the
+    // timings of one differ
     {
-        float bt = 1e30f;
+        float bt = 1e30f, bt0 = 1e30f;
+        int bg = base.zg;
         for (int G = 1; G <= 64; G *= 2) {
             if (G > std::max(1, g.nz / 2) || (g.nz + G - 1) / G > 16) continue;
             TuneParams tp = best;
@@ -302,8 +304,10 @@ pcx_status autotune_class(const pcx_grid &g, int prec, hipStream_t s, TuneParams
             auto fn = passes(d, lx, ly, lz, PK_Z, -1);
             float t = fn ? per_pass(d, PK_Z, timeit(fn)) : 1e30f;
             (void)hipFree(tb.dev);
-            if (t < bt) { bt = t; best.zg = G; }
+            if (G == base.zg) bt0 = t;
+            if (t < bt) { bt = t; bg = G; }
         }
+        best.zg = bt < 0.98f * bt0 ? bg : base.zg;
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
