@@ -198,10 +198,10 @@ hipError_t launch_resid(const Dom &d, hipStream_t s)
     PCX_LAUNCH_B(k_resid, xcd_grid(d.mg[0].ntiles), MT, 0, s, d);
 }
 
-// A fixed-plan or z pass of a lone domain: one workgroup per tile.
 // The fixed-plan and z kernels are compiled in files of their own.  The
 // references are weak, so the host code (this file, plans, batches, tuner)
-// also links and runs without them; a launch is then refused.
+// also links and runs without them (the sanitizer test does); a launch is
+// then refused.  The library's build requires every one of these symbols.
 extern __attribute__((weak)) const void *fft_xfwd_kernel(int prec, int n);
 extern __attribute__((weak)) const void *fft_xinv_store_kernel(int prec, int n);
 extern __attribute__((weak)) const void *fft_xinv_accum_kernel(int prec, int n);
@@ -210,6 +210,7 @@ extern __attribute__((weak)) const void *fft_yinv_kernel(int prec, int n);
 extern __attribute__((weak)) const void *z_kernel(int prec, int levels);
 static const void *kernel_of(const void *(*table)(int, int), int prec, int n) { return table ? table(prec, n) : nullptr; }
 
+// A fixed-plan or z pass of a lone domain: one workgroup per tile.
 static hipError_t launch_fft(const void *fn, const Dom &d, int tiles, int threads, size_t lds, hipStream_t s, int resid = 0)
 {
     if (!fn) return hipErrorInvalidValue;
