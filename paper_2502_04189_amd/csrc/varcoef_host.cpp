@@ -4,6 +4,7 @@
 // solve, pcx_poisson_solve).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <string>
 #include <vector>
@@ -82,7 +83,9 @@ extern "C" pcx_status pcx_varcoef_create(const pcx_grid *grid, const pcx_options
     V->ncell = (size_t)nx * ny * nz;
     V->tp = flow::tile_plan(G);
     V->T = apply_tiles(G);
-    const size_t nred = 3 * 2 * (size_t)RED_MAX + NSC;
+    // partials of the operator (at most RED_MAX), of the update and of the dot
+    const int nv = vec_wgs(V->ncell);
+    const size_t npart = 2 * (size_t)std::max(nv, RED_MAX), nred = 2 * (size_t)RED_MAX + 2 * npart + 4 * RED_FOLD + NSC;
     if (hipMalloc(&V->tab, t.size() * sizeof(double)) != hipSuccess ||
         hipMalloc(&V->ws, 4 * V->ncell * sizeof(double)) != hipSuccess ||
         hipMalloc(&V->red, nred * sizeof(double)) != hipSuccess) {
@@ -96,11 +99,10 @@ extern "C" pcx_status pcx_varcoef_create(const pcx_grid *grid, const pcx_options
     V->z = V->ws + V->ncell;
     V->d = V->ws + 2 * V->ncell;
     V->q = V->ws + 3 * V->ncell;
-    double *sc0 = V->red + 3 * 2 * (size_t)RED_MAX;
-    const int nv = vec_wgs(V->ncell);
-    V->RA = VRed{V->red, sc0, V->T.wgs};
-    V->R = VRed{V->red + 2 * RED_MAX, sc0, nv};
-    V->RD = VRed{V->red + 4 * RED_MAX, sc0, nv};
+    double *fold = V->red + 2 * RED_MAX + 2 * npart, *sc0 = fold + 4 * RED_FOLD;
+    V->RA = VRed{V->red, sc0, V->T.wgs, nullptr};
+    V->R = VRed{V->red + 2 * RED_MAX, sc0, nv, fold};
+    V->RD = VRed{V->red + 2 * RED_MAX + npart, sc0, nv, fold + 2 * RED_FOLD};
     // the scalar slots start at zero but for the total weight nx ny sum(dzf)
     std::vector<double> sc(NSC, 0.0);
     sc[S_WTOT] = (double)nx * (double)ny * zsum;
@@ -202,7 +204,7 @@ extern "C" pcx_status pcx_varcoef_project(pcx_varcoef V, double dt, double rho0,
             st = pcx_poisson_solve(V->plan, V->r, V->z, stream);
             if (st != PCX_OK) return st;
             VCHK(launch_dot(G, V->r, V->z, rho0, V->RD, s));
-            VCHK(launch_dupd(G, V->z, V->d, rho0, V->RD, s));
+            VCHK(launch_dupd(G, V->z, V->d, rho0, V->RD, V->R.nb, s));
         }
     }
     // correction with p (its gradient does not see the mean), then the gauge

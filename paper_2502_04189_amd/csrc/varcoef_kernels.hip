@@ -202,30 +202,38 @@ __global__ __launch_bounds__(MAT) void k_vc_apply(FGrid G, ATiles T, const doubl
     if (want) put2<MAT>(R, acc, 0.0);
 }
 
-// The vector kernels take the cells in memory order with R.nb workgroups
-// (vec_wgs), four cells per thread and round, loaded before the first is
-// stored.  With one cell per thread every kernel left a partial per 256
-// cells, and each sum took two more launches (9 us of the iteration's chain
-// at 128^3, three times); the update takes 18 us (101 MB, 5.7 TB/s) as
-// before, the dot 10 instead of 12 without r to store.
+// The vector kernels take the cells in memory order, four per thread and
+// round, loaded before the first is stored.  With one cell per thread every
+// kernel left a partial per 256 cells, and each sum took two more launches (9
+// us of the iteration's chain at 128^3, three times); with RED_MAX workgroups
+// at most the update takes 18 us (101 MB, 5.7 TB/s) as before, the dot 10
+// instead of 12 without r to store.
+// Beyond 2^24 cells every workgroup takes 1024 consecutive cells in one round:
+// workgroups that come in order keep the launch's reads and writes together
+// in memory, and the two folds of their partials cost 10 us.  At 512^3 update
+// 1.23 -> 1.15 ms, direction 0.62 -> 0.55, dot 0.40 -> 0.35; an iteration of
+// 288 x 256 x 256 843 -> 828 us, of 384^3 2.39 -> 2.31 ms (256^3 alike either way).
 struct VCells {
-    unsigned n, plane, c, stride;
+    unsigned n, plane, c, step, next; // step: between the four cells of a round, next: between rounds
     __device__ explicit VCells(const FGrid &G)
         : n((unsigned)G.n[0] * (unsigned)G.n[1] * (unsigned)G.n[2]), plane((unsigned)G.n[0] * (unsigned)G.n[1]),
-          c(blockIdx.x * FT + threadIdx.x), stride(gridDim.x * FT) // n below 2^31 (grid validation)
+          next(4 * FT * gridDim.x) // n below 2^31 (grid validation)
     {
+        const bool blocks = gridDim.x > RED_MAX; // one round
+        c = blockIdx.x * (blocks ? 4 * FT : FT) + threadIdx.x;
+        step = blocks ? FT : gridDim.x * FT;
     }
     // f(cells, in[]): every round of the thread, cells past the end clamped
     // to the last one
     template <class F> __device__ __forceinline__ void each(F &&f)
     {
-        for (; c < n; c += 4 * stride) {
+        for (; c < n; c += next) {
             size_t x[4];
             bool in[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                in[u] = c + u * stride < n;
-                x[u] = in[u] ? c + u * stride : n - 1;
+                in[u] = c + u * step < n;
+                x[u] = in[u] ? c + u * step : n - 1;
             }
             f(x, in);
         }
@@ -411,6 +419,21 @@ __global__ __launch_bounds__(FT) void k_vc_correct(BoxList L, FGrid G, const dou
     wo[c] = wallf(G, 2, t.k) ? 0.0 : w[c] - dt * gz;
 }
 
+// the partials R.part in RED_FOLD pairs of sums
+__global__ __launch_bounds__(FT) void k_vc_fold(VRed R)
+{
+    double a = 0.0, b = 0.0;
+    for (int i = blockIdx.x * FT + threadIdx.x; i < R.nb; i += RED_FOLD * FT) {
+        a += R.part[i];
+        b += R.part[R.nb + i];
+    }
+    block_sum2<FT>(a, b);
+    if (threadIdx.x == 0) {
+        R.fold[blockIdx.x] = a;
+        R.fold[RED_FOLD + blockIdx.x] = b;
+    }
+}
+
 // the totals and the scalar step of the iteration, one workgroup
 __global__ __launch_bounds__(RED_MAX) void k_vc_scal(VRed R, int mode, double *host)
 {
@@ -442,6 +465,16 @@ __global__ __launch_bounds__(RED_MAX) void k_vc_scal(VRed R, int mode, double *h
     }
 }
 
+hipError_t launch_fold(const VRed &R, VRed &out, hipStream_t s)
+{
+    out = R;
+    if (R.nb <= RED_MAX) return hipSuccess;
+    if (!R.fold) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_vc_fold, dim3(RED_FOLD), dim3(FT), 0, s, R);
+    out.part = R.fold;
+    out.nb = RED_FOLD;
+    return hipGetLastError();
+}
 hipError_t launch_apply(const FGrid &G, const ATiles &T, const double *rho, const double *p, double *out, double sign,
                         const VRed *R, hipStream_t s)
 {
@@ -478,9 +511,12 @@ hipError_t launch_dot(const FGrid &G, const double *r, const double *z, double r
     hipLaunchKernelGGL(k_vc_dot, dim3(R.nb), dim3(FT), 0, s, G, r, z, rho0, R);
     return hipGetLastError();
 }
-hipError_t launch_dupd(const FGrid &G, const double *z, double *d, double rho0, const VRed &IN, hipStream_t s)
+hipError_t launch_dupd(const FGrid &G, const double *z, double *d, double rho0, const VRed &IN, int nv, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_vc_dupd, dim3(IN.nb), dim3(FT), 0, s, G, z, d, rho0, IN);
+    VRed t;
+    const hipError_t e = launch_fold(IN, t, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_vc_dupd, dim3(nv), dim3(FT), 0, s, G, z, d, rho0, t);
     return hipGetLastError();
 }
 hipError_t launch_pmean(const FGrid &G, const double *p, const VRed &R, hipStream_t s)
@@ -501,8 +537,10 @@ hipError_t launch_pshift(const FGrid &G, double *p, const VRed &R, hipStream_t s
 }
 hipError_t red_scal(const VRed &R, int mode, hipStream_t s, double *host)
 {
-    if (R.nb > RED_MAX) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_vc_scal, dim3(1), dim3(RED_MAX), 0, s, R, mode, host);
+    VRed t;
+    const hipError_t e = launch_fold(R, t, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_vc_scal, dim3(1), dim3(RED_MAX), 0, s, t, mode, host);
     return hipGetLastError();
 }
 

@@ -24,20 +24,24 @@ enum {
 };
 
 // Reductions: a partial-writing kernel stores the two sums of its workgroup
-// b at part[b] and part[nb + b], nb <= RED_MAX workgroups in all, and what
-// needs the total sums them in a fixed order: red_scal (one workgroup) into
-// the scalar slots, or every workgroup of the next kernel for itself, which
-// costs it about a microsecond and spares two launches in the chain.
-constexpr int RED_MAX = 1024;
+// b at part[b] and part[nb + b], and what needs the total sums them in a fixed
+// order: red_scal (one workgroup) into the scalar slots, or every workgroup of
+// the next kernel for itself, which costs it about a microsecond and spares
+// two launches in the chain.  More than RED_MAX partials are first folded to
+// RED_FOLD (launch_fold).
+constexpr int RED_MAX = 1024, RED_FOLD = 256;
 struct VRed {
     double *part; // 2 nb
     double *sc;   // NSC
     int nb;
+    double *fold; // 2 RED_FOLD (nb > RED_MAX)
 };
 
-// Workgroups of the vector kernels (256 cells each and round, RED_MAX at most)
+// Workgroups of the vector kernels: 256 cells each and round, RED_MAX at most;
+// beyond 2^24 cells a workgroup for every 1024 consecutive cells (VCells).
 inline int vec_wgs(size_t cells)
 {
+    if (cells > (size_t)1 << 24) return (int)((cells + 4 * flow::FT - 1) / (4 * flow::FT));
     const size_t n = (cells + flow::FT - 1) / flow::FT;
     return n < (size_t)RED_MAX ? (int)n : RED_MAX;
 }
@@ -80,12 +84,15 @@ hipError_t launch_dinit(const FGrid &G, const double *r, const double *z, double
 hipError_t launch_update(const FGrid &G, double *p, const double *d, double *r, const double *q, const VRed &IN,
                          const VRed &R, hipStream_t s);
 hipError_t launch_dot(const FGrid &G, const double *r, const double *z, double rho0, const VRed &R, hipStream_t s);
-hipError_t launch_dupd(const FGrid &G, const double *z, double *d, double rho0, const VRed &IN, hipStream_t s);
+// nv: the launch's workgroups (vec_wgs)
+hipError_t launch_dupd(const FGrid &G, const double *z, double *d, double rho0, const VRed &IN, int nv, hipStream_t s);
 hipError_t launch_pmean(const FGrid &G, const double *p, const VRed &R, hipStream_t s);
 hipError_t launch_correct(const FGrid &G, const TilePlan &tp, const double *rho, const double *p, const double *u,
                           const double *v, const double *w, double dt, double *uo, double *vo, double *wo,
                           hipStream_t s);
 hipError_t launch_pshift(const FGrid &G, double *p, const VRed &R, hipStream_t s);
+// R, or its partials folded to RED_FOLD where they are more than RED_MAX
+hipError_t launch_fold(const VRed &R, VRed &out, hipStream_t s);
 // the sums of the partials and the scalar step `mode`; MODE_RES also stores
 // the residual at *host (host memory the device can write)
 hipError_t red_scal(const VRed &R, int mode, hipStream_t s, double *host = nullptr);

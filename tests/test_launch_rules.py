@@ -16,7 +16,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not available")
-@pytest.mark.parametrize("rule", ["z_stride", "shapes", "no_pinned", "march_chunk", "momentum_chunk", "fft_lds", "tune_items"])
+@pytest.mark.parametrize("rule", ["z_stride", "shapes", "no_pinned", "march_chunk", "momentum_chunk", "fft_lds", "tune_items", "vec_wgs"])
 def test_rule(tmp_path, rule):
     exe = tmp_path / rule
     subprocess.check_call([HIPCC, "-O1", "-std=c++17", "-x", "hip", "--offload-arch=gfx950", "-I",
