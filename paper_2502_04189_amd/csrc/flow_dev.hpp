@@ -6,8 +6,10 @@
 // force, the regularization term that keeps mass and momentum consistent,
 // body force), all second-order on the staggered grid.
 //
-// One thread per cell; neighbours are read from memory (the cells of a
-// workgroup's neighbours are mostly in the XCD's L2).  Index rules:
+// Everything is written on an accessor, which says where the neighbours of
+// the thread's cell come from: memory by the rules below (Gen), memory of an
+// interior cell (Fast), or stages in LDS and registers that hold what the
+// rules give (StageAcc).  Index rules:
 //   cell scalars one cell outside: periodic wrap, or the cell itself across
 //   a wall (zero normal gradient);
 //   face component c in its own direction: faces -1 and n-1 of a wall

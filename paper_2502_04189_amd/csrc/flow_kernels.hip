@@ -538,7 +538,7 @@ template <bool PH> __device__ __forceinline__ void momentum_body(const BoxList &
         if (p.fast) momentum_march<PH, true>(A, t, ke, st, key);
         else momentum_march<PH, false>(A, t, ke, st, key);
     }
-    if constexpr (PH) key_to_slot(key, A.rho_part + p.slot);
+    if constexpr (PH) key_to_slot(key, A.rho_part + blockIdx.x);
 }
 
 __global__ __launch_bounds__(FT) void k_flow_momentum(BoxList L, FArgs A) { momentum_body<false>(L, A); }

@@ -19,7 +19,7 @@ struct FArgs {
     double *hphi, *hu, *hv, *hw;     // previous right-hand sides in, this substep's out
     double *phi_out, *us[3], *rho_new; // NULL: right-hand sides only
     unsigned long long *rho_min_key; // the minimum's key (in host memory the device can write, or the device's)
-    unsigned long long *rho_part;    // one key per workgroup of the phase pass (TilePlan::nslots), then MINWG more
+    unsigned long long *rho_part;    // one key per workgroup of the phase pass (TilePlan::nslots at most), then MINWG more
     const double *p1, *p2;           // pressures of the two previous substeps
     double r;
     double *pstar;                   // NULL: no extrapolation

@@ -34,9 +34,9 @@ inline int box_grid(const TileBox &b)
     return (int)(((n + 7) >> 3) << 3);
 }
 
-// The launches of one grid: box b runs with the interior accessor when
-// fast[b]; its workgroups own partial-result slots [slot0[b], slot0[b] +
-// box_grid(box[b])); nslots in all.
+// The boxes of one grid: box b runs with the interior accessor when fast[b].
+// A launch over all of them has at most nslots workgroups (slot0[b] is where
+// box b's start), each with a partial-result slot of its own number.
 struct TilePlan {
     int n;
     TileBox box[7];
@@ -151,7 +151,7 @@ struct BoxList {
     int n, grid;
     int fast; // box 0 is the interior box
     TileBox box[MAXBOX];
-    int slot0[MAXBOX], first[MAXBOX];
+    int first[MAXBOX];
     int ck, kend[MAXBOX]; // a list in chunks of ck planes: box[q].nk counts chunks, kend[q] is the box's last plane + 1
 };
 
@@ -166,7 +166,6 @@ inline BoxList box_list(const TilePlan &p, bool interior, bool walls)
         if (!(p.fast[b] ? interior : walls)) continue;
         if (p.fast[b]) L.fast = 1;
         L.box[L.n] = p.box[b];
-        L.slot0[L.n] = p.slot0[b];
         L.first[L.n] = L.grid;
         L.grid += box_grid(p.box[b]);
         ++L.n;
@@ -175,7 +174,7 @@ inline BoxList box_list(const TilePlan &p, bool interior, bool walls)
 }
 
 // The list with a workgroup per chunk of ck planes of a tile, for kernels
-// that march in z; slots in the order of the workgroups (no more than before).
+// that march in z (no more workgroups than before).
 inline BoxList box_chunks(BoxList L, int ck)
 {
     L.ck = ck;
@@ -183,7 +182,7 @@ inline BoxList box_chunks(BoxList L, int ck)
     for (int q = 0; q < L.n; ++q) {
         L.kend[q] = L.box[q].k0 + L.box[q].nk;
         L.box[q].nk = (L.box[q].nk + ck - 1) / ck;
-        L.slot0[q] = L.first[q] = L.grid;
+        L.first[q] = L.grid;
         L.grid += box_grid(L.box[q]);
     }
     return L;
@@ -210,21 +209,20 @@ inline BoxList momentum_list(const TilePlan &tp)
     return box_chunks(L, best);
 }
 
-// the box of this workgroup, its number in the box and its slot
+// the box of this workgroup and its number in the box
 struct BoxPick {
     TileBox b;
     unsigned w;
-    int slot;
     bool fast;
     int kend;
 };
 __device__ __forceinline__ BoxPick box_pick(const BoxList &L)
 {
-    BoxPick p{L.box[0], blockIdx.x, L.slot0[0] + (int)blockIdx.x, L.fast != 0, L.kend[0]};
+    BoxPick p{L.box[0], blockIdx.x, L.fast != 0, L.kend[0]};
 #pragma unroll
     for (int q = 1; q < MAXBOX; ++q)
         if (q < L.n && (int)blockIdx.x >= L.first[q])
-            p = BoxPick{L.box[q], blockIdx.x - L.first[q], L.slot0[q] + (int)blockIdx.x - L.first[q], false, L.kend[q]};
+            p = BoxPick{L.box[q], blockIdx.x - L.first[q], false, L.kend[q]};
     return p;
 }
 
