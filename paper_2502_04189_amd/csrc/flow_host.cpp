@@ -198,6 +198,7 @@ static pcx_status predictor(pcx_flow F, int32_t sub, double Dt, const double *ph
 {
     static const double GA[3] = {8.0 / 15.0, 5.0 / 12.0, 3.0 / 4.0};
     static const double ZE[3] = {0.0, -17.0 / 60.0, -5.0 / 12.0};
+    unsigned long long *const words = plan_host_words(F->plan);
     FArgs A = base_args(F, phi, u, v, w);
     A.Dt = Dt;
     A.ga = GA[sub - 1];
@@ -209,12 +210,11 @@ static pcx_status predictor(pcx_flow F, int32_t sub, double Dt, const double *ph
     A.rho_new = rho_new;
     A.p1 = p1; A.p2 = p2; A.r = r;
     A.pstar = pstar;
+    A.rho_min_key = words ? words + F->plan->owner_word() : F->part + F->tp.nslots + MINWG;
     FCHK(launch_normals(A, F->tpn, s));
     FCHK(launch_flux(A, F->tpn, s));
     // one pass: the momentum predictor and the phase update read the state at
     // the start of the substep only
-    unsigned long long *const words = plan_host_words(F->plan);
-    A.rho_min_key = words ? words + F->plan->owner_word() : F->part + F->tp.nslots + MINWG;
     FCHK(launch_momentum_phase(A, F->tp, s));
     unsigned long long key = 0;
     if (!words) FCHK(hipMemcpyAsync(&key, A.rho_min_key, sizeof(key), hipMemcpyDeviceToHost, s));

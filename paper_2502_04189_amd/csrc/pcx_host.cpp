@@ -538,9 +538,7 @@ unsigned long long *plan_host_words(pcx_plan_s *P)
     return P->drep;
 }
 
-} // namespace pcx
-
-extern "C" pcx_status pcx_plan_create(const pcx_grid *grid, const pcx_options *opts, pcx_plan *out)
+pcx_status plan_create(const pcx_grid *grid, const pcx_options *opts, pcx_plan *out, bool words)
 {
     if (!out) return fail(PCX_ERR_INVALID, "out is NULL");
     *out = nullptr;
@@ -576,8 +574,16 @@ extern "C" pcx_status pcx_plan_create(const pcx_grid *grid, const pcx_options *o
         return fail(PCX_ERR_NOMEM, "workspace allocation failed");
     }
     plan_bind(P, ht, (char *)P->tables.dev, (char *)P->ws, L);
+    if (words) (void)plan_host_words(P);
     *out = P;
     return PCX_OK;
+}
+
+} // namespace pcx
+
+extern "C" pcx_status pcx_plan_create(const pcx_grid *grid, const pcx_options *opts, pcx_plan *out)
+{
+    return plan_create(grid, opts, out, true);
 }
 
 extern "C" pcx_status pcx_plan_workspace_bytes(pcx_plan P, size_t *bytes)
@@ -739,6 +745,7 @@ extern "C" pcx_status pcx_step(pcx_plan P, double dt, double rho0, const double 
     d.dt = dt; d.rho0 = rho0; d.irho0 = 1.0 / rho0;
     d.rho = rho; d.ps = p_star; d.u = u_in; d.v = v_in; d.w = w_in;
     d.uo = u_out; d.vo = v_out; d.wo = w_out; d.po = p_out;
+    unsigned long long *const words = report ? plan_host_words(P) : nullptr;
     tmark(P, s, nullptr);
     HIPCHK(launch_zero(P->stats, NSTAT, s));
     int solves = 0;
@@ -793,7 +800,6 @@ extern "C" pcx_status pcx_step(pcx_plan P, double dt, double rho0, const double 
     std::vector<double> ps(P->grid.nz);
     if (!report) return correct();
     // the statistics, with sums also the plane sums of p, once the stream is done
-    unsigned long long *const words = plan_host_words(P);
     auto fetch = [&](bool sums) -> pcx_status {
         const double *q = sums ? p_out : nullptr;
         const int nxy = P->grid.nx * P->grid.ny;

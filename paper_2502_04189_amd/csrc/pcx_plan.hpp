@@ -113,8 +113,15 @@ WsLayout plan_layout(const pcx_plan_s *P);
 // The layout with columns and z-lines rounded up to whole 128-byte lines, or
 // without the rounding where it alone would take the plan beyond `most` bytes.
 WsLayout plan_layout_within(pcx_plan_s *P, size_t most);
-// The plan's words of host memory by their device address (host: hrep); NULL
-// where no such memory can be had: the caller copies from the device instead.
+// pcx_plan_create; words: with the plan's words of host memory.
+pcx_status plan_create(const pcx_grid *grid, const pcx_options *opts, pcx_plan *out, bool words);
+// The plan's words of host memory by their device address (host: hrep),
+// allocated by the first call; NULL where no such memory can be had: the
+// caller copies from the device instead.  The allocation takes 15-25 us, as
+// much as the rest of a small plan's creation, and a call in the middle of a
+// step waits for kernels on their way: a plan of a caller's and a flow's take
+// it at creation, since a report or a substep follows, a projection's with
+// its first iteration, of milliseconds.
 unsigned long long *plan_host_words(pcx_plan_s *P);
 void plan_bind(pcx_plan_s *P, const HostTables &ht, char *tables, char *ws, const WsLayout &L);
 } // namespace pcx
@@ -135,8 +142,7 @@ struct pcx_plan_s {
     double *psum = nullptr;
     // statistics and plane sums of a report in host memory, host and device
     // address, and one word more for the flow or the projection that owns the
-    // plan; allocated by the first call that reads it (plan_host_words: 15-25
-    // us, as much as the rest of a small plan's creation takes)
+    // plan (plan_host_words)
     unsigned long long *hrep = nullptr, *drep = nullptr;
     bool hrep_tried = false;
     size_t owner_word() const { return pcx::NSTAT + (size_t)grid.nz; }

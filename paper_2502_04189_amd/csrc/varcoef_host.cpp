@@ -62,7 +62,7 @@ extern "C" pcx_status pcx_varcoef_create(const pcx_grid *grid, const pcx_options
     V->zf.assign(grid->zf, grid->zf + nz + 1);
     pcx_grid g = *grid;
     g.zf = V->zf.data();
-    st = pcx_plan_create(&g, opts, &V->plan);
+    st = plan_create(&g, opts, &V->plan, false);
     if (st != PCX_OK) {
         V->plan = nullptr;
         vc_free(V);
